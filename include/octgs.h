@@ -389,7 +389,7 @@ OCTGS_API size_t octgs_photometric_workspace_bytes(int64_t n_images, int32_t hei
  * C2 = 0.03^2 (data range 1), windowed statistics over a zero-padded
  * same-size correlation, averaged over every pixel of every plane.  With
  * w_ssim = 0 the call is the L1 term alone and needs no workspace.  ws:
- * device, >= octgs_photometric_workspace_bytes (three derivative maps).
+ * device, >= octgs_photometric_workspace_bytes.
  * n_images <= 65535. */
 OCTGS_API int octgs_photometric_loss_grad(const float *img, const float *target,
                                           int64_t n_images, int32_t height, int32_t width,

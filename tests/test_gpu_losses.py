@@ -69,6 +69,21 @@ def test_photometric_parity(P, LO, shape):
     assert np.abs(g - rg).max() <= 1e-3 * np.abs(rg).max()
 
 
+@pytest.mark.parametrize("hw", [(1, 1), (1, 235), (7, 236), (8, 237), (9, 472), (18, 473),
+                                (19, 11), (137, 3), (300, 709)])
+def test_photometric_strip_edges(P, LO, hw):
+    """Image sizes at the edges of the kernel's strips (236 columns; 8, 18, ...
+    rows) and windows larger than the image, at the bars of the parity test."""
+    for planes in (1, 90):  # short strips, and the longest that this size takes
+        img, tgt = _images((planes,) + hw, 13 * hw[0] + hw[1])
+        say("photometric strip edges", planes, hw)
+        loss, g = _run(P, img, tgt, 0.8, 0.2)
+        rl, rg = LO.photometric_loss_grad(img, tgt, 0.8, 0.2)
+        assert abs(loss - rl) <= 2e-6
+        assert np.linalg.norm(g - rg) <= 1e-4 * np.linalg.norm(rg)
+        assert np.abs(g - rg).max() <= 1e-3 * np.abs(rg).max()
+
+
 def test_l1_only_and_identity(P, LO):
     img, tgt = _images((2, 3, 40, 70), 5)
     loss, g = _run(P, img, tgt, 1.0, 0.0)
