@@ -44,7 +44,7 @@ BF16_MFMA_PEAK_TFLOPS = 2500.0    # MI355X dense BF16 matrix peak
 FLOP_PER_BLEND = 21.0
 COMPOSITE_PMC = os.path.join(ROOT, "profiles", "composite_street1080p_hbm_bytes.txt")
 RASTER_PMC = os.path.join(ROOT, "profiles", "raster_street1080p_hbm_bytes.txt")
-RASTER_SOURCES = ("paper_2403_17898_amd/csrc/raster.hip", "paper_2403_17898_amd/csrc/sort.hip")
+RASTER_SOURCES = ("paper_2403_17898_amd/csrc/raster.hip", "paper_2403_17898_amd/csrc/bins.hip")
 COMPOSITE_BWD_PMC = os.path.join(ROOT, "profiles", "composite_bwd_train_c3_hbm_bytes.txt")
 BWD_SOURCES = ("paper_2403_17898_amd/csrc/raster_bwd.hip",)
 
@@ -1179,12 +1179,10 @@ def train_step_timing(args, P, S, torch, np, sc=None, views=None,
 # launches per view: (label, name substring, launches)
 VIEW_KERNELS = [("k_select_mark", "k_select_mark", 1), ("k_select_scatter", "k_select_scatter", 1),
                 ("k_decode_prep<BF16>", "k_decode_prep<true>", 1), ("k_decode<BF16>", "k_decode<true>", 1),
-                ("k_project_mark", "k_project_mark", 1), ("k_project_compact", "k_project_compact", 1),
-                ("depth sort passes", "k_sort_pass<1, 8>", 4), ("k_emit_scan", "k_emit_scan", 1),
-                ("k_emit_pairs", "k_emit_pairs", 1), ("tile sort passes", "k_sort_pass<1, 16>", 2),
-                ("k_ranges", "k_ranges", 1), ("k_composite", "k_composite<false>", 1)]
-RASTER_LABELS = ("k_project_mark", "k_project_compact", "depth sort passes", "k_emit_scan",
-                 "k_emit_pairs", "tile sort passes", "k_ranges", "k_composite")
+                ("k_project", "k_project<", 1), ("k_bin_sort", "k_bin_sort", 1),
+                ("k_tile_scan", "k_tile_scan", 1), ("k_tile_lists", "k_tile_lists", 1),
+                ("k_composite", "k_composite<false>", 1)]
+RASTER_LABELS = ("k_project", "k_bin_sort", "k_tile_scan", "k_tile_lists", "k_composite")
 
 
 def _csv_rows(d: str, suffix: str):
@@ -1245,8 +1243,8 @@ def summarize_profiles(trace_dir: str, fetch_dir: str, write_dir: str, views: in
     shas = [f"source_sha256 {os.path.basename(f)}: {sha256_of(f)}" for f in RASTER_SOURCES]
     cmd_txt = "\n".join("  " + c for c in cmds)
     raster = (
-        "HBM traffic of the whole rasterizer forward (projection, depth sort, pair emission, tile\n"
-        f"sort, ranges, compositing) on the street-scene benchmark (1920x1080, the {views} views of\n"
+        "HBM traffic of the whole rasterizer forward (projection, bin sort, tile scan, tile lists,\n"
+        f"compositing) on the street-scene benchmark (1920x1080, the {views} views of\n"
         "the zoom-out, one view in flight), per view:\n"
         "FETCH_SIZE and WRITE_SIZE (KiB per dispatch) scaled by what each counter reads for a plain\n"
         f"256 MiB device copy in the same run (x{sf:.3f} and x{sw:.3f}), over the dispatches of the\n"

@@ -149,10 +149,9 @@ typedef struct {
   uint32_t flags; /* OCTGS_RASTER_* bits */
 } octgs_raster_params;
 
-/* flags: the forward keeps what octgs_rasterize_bwd needs (each emitted
- * pair's slot, and each sorted pair's emission index, carried through the
- * tile sort); required for a later backward of the same frame, off for
- * rendering only (two fewer 4-byte writes per pair and a lighter sort). */
+/* flags: the forward keeps what octgs_rasterize_bwd needs (each listed pair's
+ * number, a Gaussian's being contiguous); required for a later backward of
+ * the same frame, off for rendering only. */
 #define OCTGS_RASTER_TRAIN 1u
 /* flags: before compositing, order each XCD's tiles by list length, longest
  * first (one small extra kernel), so the last blocks to run are short ones;
@@ -172,8 +171,8 @@ typedef struct {
   uint32_t n_pairs;       /* (tile, Gaussian) pairs listed: tiles the 3-sigma ellipse meets
                              (0 on overflow) */
   uint32_t pair_overflow; /* 1 if n_candidates exceeded the pair capacity (image incomplete) */
-  uint32_t sync_error;    /* 1 if a look-back wait (scans, sorts) hit its bound (output
-                             invalid); partitions are taken in the order blocks start, so
+  uint32_t sync_error;    /* 1 if a look-back wait (the tile scan's) hit its bound (output
+                             invalid); its blocks are numbered in the order they start, so
                              every wait is on a running block and this is not expected */
   uint32_t n_candidates;  /* tiles of the survivors' 3-sigma rectangles, tested against the
                              ellipse; the pair capacity must hold this many (saturates) */
@@ -291,8 +290,9 @@ OCTGS_API size_t octgs_raster_workspace_bytes(int64_t gauss_capacity, int64_t pa
  * The workspace keeps the sorted lists for octgs_rasterize_bwd and starts
  * with octgs_raster_stats.  stage_events (nullable): 2 * OCTGS_RASTER_STAGES
  * hipEvent_t created by the caller; events 2s and 2s+1 are recorded on
- * `stream` around stage s (0 project + compaction, 1 depth sort, 2 pair
- * emission, 3 tile sort + ranges, 4 composite) for per-stage timing.
+ * `stream` around stage s (0 projection and grouping by screen bin, 1 depth
+ * sort of each bin, 2 tile ranges, 3 tile lists and tile order, 4 composite)
+ * for per-stage timing.
  * OCTGS_EINVAL also for cam->z_near <= 0 (depth keys are the float bits of
  * positive depths), p->dilation < 0 or p->jac_clamp <= 0. */
 OCTGS_API int octgs_rasterize_fwd(const octgs_gaussians *g, const octgs_camera *cam,

@@ -110,26 +110,6 @@ __device__ __forceinline__ float wave_sum_f(float v) {
   return __uint_as_float(x) + __uint_as_float(y);
 }
 
-// Block-wide exclusive scan of one value per thread (256 threads); returns
-// the exclusive prefix and writes the block total to *total.  `tmp` is LDS of
-// at least 4 words.
-__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *tmp, uint32_t *total) {
-  int w = threadIdx.x / kWave, l = __lane_id();
-  uint32_t inc = wave_incl_scan(v);
-  if (l == 63) tmp[w] = inc;
-  __syncthreads();
-  uint32_t off = 0, tot = 0;
-#pragma unroll
-  for (int i = 0; i < kBlock / kWave; ++i) {
-    uint32_t s = tmp[i];
-    if (i < w) off += s;
-    tot += s;
-  }
-  __syncthreads();
-  *total = tot;
-  return off + inc - v;
-}
-
 // Sum of v over the 256 threads of a block, returned to thread 0 (LDS
 // scratch of 4 floats).
 __device__ __forceinline__ float block_sum_f(float v, float *red) {
@@ -208,77 +188,192 @@ __device__ __forceinline__ int32_t tile_of_block(uint32_t bid, int tiles_x, int 
 // rasterizer workspace
 // ---------------------------------------------------------------------------
 
-constexpr int kTicketScan = 0, kTicketEmit = 1, kTicketDepth = 2, kTicketTile = 6;
-constexpr int kTicketSlots = 10;
-
 struct RasterHeader {
   uint32_t n_slots, n_visible, n_pairs, pair_overflow, sync_error;
-  uint32_t n_candidates;  // rectangle tiles of the survivors (saturated at 2^32 - 1)
-  uint32_t n_cand_listed; // candidates written (n_candidates, or 0 on overflow)
+  uint32_t n_candidates;  // rectangle tiles of the survivors (saturated at kLbVal)
+  uint32_t n_emit;        // training: pair numbers handed out (holes of huge rectangles included)
   uint32_t n_listed;      // pairs in the sorted list (n_pairs, or 0 on overflow)
   uint32_t tile_ordered;  // 1 if the forward wrote tile_order (OCTGS_RASTER_TILE_ORDER)
-  // partition tickets of the kernels chained by look-back: candidate scan,
-  // emission, then the depth sort's 4 passes and the tile sort's passes
-  uint32_t ticket[kTicketSlots];
-  uint32_t reserved[23 - kTicketSlots];
+  uint32_t scan_ticket;   // tile scan: block numbers in the order blocks start
+  uint32_t bin_cursor;    // bin-list entries handed out
+  uint32_t n_over;        // bins whose list is longer than one block sorts (kBinCap)
+  uint32_t reserved[20];
 };
+
+// Screen bins: rectangles of 2^sx x 2^sy tiles (at most 32, one mask bit per
+// tile).  A Gaussian is handed to the bins its rectangle meets, each bin's
+// list is put into depth order by one block, and the bin's tiles take their
+// entries from the ordered list.
+struct BinGrid {
+  int32_t sx, sy;        // log2 of the bin's size in tiles
+  int32_t nx, ny;        // bins of the image
+  int32_t gx;            // bin columns that a rectangle (16-bit tile coordinates) can reach
+  int32_t band_rows;     // bin rows that one grouping pass covers (all, but for huge images)
+};
+
+constexpr int kGroupBins = 4;                     // bins that a slot hands itself to directly
+constexpr int kGroupCap = kChunk * kGroupBins;    // grouped entries of a block of kChunk slots
+constexpr uint32_t kKeepBits = 64;                // rectangle tiles that a slot's keep mask holds
+constexpr int kMaxBandBins = 8192;                // bins of one grouping pass
+constexpr int kMaxTileCoord = 65535;              // tiles past this column or row list nothing
+constexpr int kBinThreads = 1024;
+constexpr int kBinItems = 8;
+constexpr int kBinCap = kBinThreads * kBinItems;  // longest list that one block sorts at once
+constexpr int kScanTiles = 8;                     // tiles per thread of the tile scan
+constexpr int kPairRow = 10;                      // words per pair of gpair: 9 gradients, slot
 
 struct RasterWs {
   RasterHeader *hdr;
   uint64_t *vis_mask;     // [gcap / 64]
-  uint32_t *blk_cnt;      // [nblk_g]
+  uint32_t *blk_vis;      // [nblk_g] survivors of each block of kChunk slots
+  uint32_t *blk_cand;     // [nblk_g] their rectangle tiles (saturated at kLbVal)
+  uint32_t *blk_large;    // [nblk_g] survivors listed in large_slot
+  uint32_t *blk_pairs;    // [nblk_g] training: pair numbers of the block, then their prefix
   float4 *proj;           // [gcap][3]: (mx, my, A, B) (C, log2 opacity, r, g) (b, qa, qb, qc);
                           // A, B, C = conic scaled for exp2: -0.5 log2e ca, -log2e cb, -0.5 log2e cc;
                           // qa, qb, qc = the conic itself (tile test)
   uint32_t *depth;        // [gcap] float bits of camera z
-  uint64_t *rect;         // [gcap] packed u16 x0, y0, x1, y1
-  uint32_t *dkey[2];      // [gcap] depth-sort keys (ping-pong)
-  uint32_t *dval[2];      // [gcap] depth-sort values = slot ids
-  uint32_t *pair_off;     // [gcap] exclusive prefix of rectangle tiles, depth order
-  uint32_t *lb_emit;      // [nblk_g] look-back status of the candidate scan's chunks
-  uint32_t *run_first;    // [nruns] depth-order index of the survivor holding candidate kEmitRun r
-  uint32_t *lb_pair;      // [nruns] look-back status of the emission's runs
-  uint32_t *tkey[2];      // [pcap] tile keys (ping-pong)
-  uint32_t *tval[2];      // [pcap] slot ids
-  uint32_t *tpair[2];     // [pcap] each pair's emission index, carried by the tile sort
-  uint32_t *pair_slot;    // [pcap] slot of each pair in emission order (a Gaussian's pairs
-                          // are contiguous there)
+  ulonglong2 *rect;       // [gcap] x: packed u16 x0, y0, x1, y1; y: kept tiles of the rectangle,
+                          // row-major, where it has at most kKeepBits (else unused)
+  uint32_t *pair_base;    // [gcap] training: first pair number of the slot within its block's
+  uint16_t *group_off;    // [nblk_g][group_pitch] start of each bin's entries in the block's group
+  uint2 *group;           // [nblk_g][kGroupCap] (depth key, slot) grouped by bin
+  uint32_t *large_slot;   // [nblk_g][kChunk] survivors over more than kGroupBins bins or
+                          // kKeepBits tiles: every bin looks through these
+  uint2 *bin_range;       // [bins] start and length of the bin's list
+  uint32_t *bin_slot[2];  // [pcap] bin lists in depth order: slots ([1]: merged long lists)
+  uint32_t *bin_mask[2];  // [pcap] and the bin's tiles that each is listed in
+  uint32_t *over_bin;     // [pcap / kBinCap + 1] bins with longer lists
+  uint32_t *tile_count;   // [tiles], padded to whole scan blocks
+  uint32_t *lb_scan;      // [scan blocks] look-back status of the tile scan
+  uint32_t *tkey;         // [pcap] tile of each listed pair, in list order (bin keys of long
+                          // lists before)
+  uint32_t *tval;         // [pcap] its slot
+  uint32_t *tpair;        // [pcap] training: its pair number (a Gaussian's are contiguous)
   uint32_t *ranges;       // [tiles][2]
   uint32_t *tile_order;   // [tile_grid_blocks] tile of each compositing block (~0u: none),
                           // written only with OCTGS_RASTER_TILE_ORDER
-  uint32_t *hist;         // [kHistCopies][8][256] radix histograms (4 depth passes, then 1..4
-                          // tile passes); block b adds into copy b % kHistCopies
-  uint32_t *lookback;     // [4][ceil(gcap / kSortPart)][256] depth-sort look-back
-  uint32_t *lookback_t;   // [tile passes][ceil(pcap / kTileSortPart)][256] tile-sort look-back
   float *dproj;           // [gcap][9] backward: d(mx, my, ca, cb, cc, opacity, r, g, b)
-  float *gpair;           // [pcap][9] backward: the same per (tile, Gaussian) pair, emission order
+  float *gpair;           // [pcap][kPairRow] backward: the same per pair number, then the slot
   float *chunk_part;      // [ceil(pcap / 64)][2][9] backward: sums of a 64-pair chunk's first and
                           // last run where the run crosses the chunk's start or end
   uint32_t *chunk_info;   // [ceil(pcap / 64)] backward: which of those the chunk has
+  BinGrid bins;
   int64_t gcap, pcap;
-  int32_t tiles_x, tiles_y, nblk_g, nruns, tile_passes;
+  int32_t tiles_x, tiles_y, nblk_g, group_pitch, scan_blocks;
   float xmax, ymax;            // last pixel centre of the image: W - 0.5, H - 0.5
-  size_t lb_words, lbt_words;  // look-back words of the depth and tile sorts (all passes)
-  int64_t lb_parts, lbt_parts; // partitions per pass at capacity
   size_t bytes;
 };
 
-// Producers spread their histogram atomics over this many copies (one per
-// XCD for round-robin dispatch), which the sort sums: atomics on global
-// memory are performed at the memory side, and one copy served by every
-// block serialises them.
-constexpr int kHistCopies = 8;
-constexpr uint32_t kHistStride = 8 * 256;
+// Tile test, canonical FP32: does the 3-sigma ellipse q(p) <= 9,
+// q = qa dx^2 + 2 qb dx dy + qc dy^2 around (mx, my), meet the box of the
+// tile's pixel centres inside the image, [16 tx + 0.5, min(16 tx + 15.5,
+// W - 0.5)] x [16 ty + 0.5, min(16 ty + 15.5, H - 0.5)]?  (Pixels of a
+// partial edge tile past the image are not drawn, so they do not list a
+// Gaussian.)  The convex quadratic's minimum over the box is 0 with the mean
+// inside; otherwise it lies on an edge facing the mean, at the 1D minimiser
+// clamped to the edge:
+//   X0 = (float)(16 tx) + 0.5, X1 = fminf(X0 + 15, xmax) (Y alike)
+//   mean's x outside [X0, X1]: xe = nearer of X0, X1; dx = xe - mx;
+//     ys = min(max(my - (qb * dx) / qc, Y0), Y1); dy = ys - my;
+//     q1 = fmaf(qa * dx, dx, fmaf(2 * qb * dx, dy, qc * dy * dy))
+//   mean's y outside [Y0, Y1]: the same with the roles of x and y swapped
+//   keep iff min(q1, q2) <= 9.
+__device__ __forceinline__ bool tile_meets_ellipse(float mx, float my, float qa, float qb, float qc,
+                                                   uint32_t tx, uint32_t ty, float xmax,
+                                                   float ymax) {
+  const float X0 = (float)(16u * tx) + 0.5f, X1 = fminf(X0 + 15.0f, xmax);
+  const float Y0 = (float)(16u * ty) + 0.5f, Y1 = fminf(Y0 + 15.0f, ymax);
+  const bool in_x = !(mx < X0) && !(mx > X1), in_y = !(my < Y0) && !(my > Y1);
+  float q = INFINITY;
+  if (!in_x) {
+    const float xe = mx < X0 ? X0 : X1;
+    const float dx = xe - mx;
+    const float ys = fminf(fmaxf(my - (qb * dx) / qc, Y0), Y1);
+    const float dy = ys - my;
+    q = __builtin_fmaf(qa * dx, dx, __builtin_fmaf(2.0f * qb * dx, dy, qc * dy * dy));
+  }
+  if (!in_y) {
+    const float ye = my < Y0 ? Y0 : Y1;
+    const float dy = ye - my;
+    const float xs = fminf(fmaxf(mx - (qb * dy) / qa, X0), X1);
+    const float dx = xs - mx;
+    q = fminf(q, __builtin_fmaf(qa * dx, dx, __builtin_fmaf(2.0f * qb * dx, dy, qc * dy * dy)));
+  }
+  return (in_x && in_y) || q <= 9.0f;
+}
 
-constexpr int kEmitThreads = 1024;  // pair emission: threads per block
-constexpr int kEmitRun = 8192;      // candidate pairs per block of the emission
+// (x0, y0, x1, y1) of a packed rectangle, tiles, end exclusive.
+struct TileRect {
+  uint32_t x0, y0, x1, y1;
+};
+__device__ __forceinline__ uint64_t pack_rect(int x0, int y0, int x1, int y1) {
+  return (uint64_t)(uint16_t)x0 | ((uint64_t)(uint16_t)y0 << 16) | ((uint64_t)(uint16_t)x1 << 32) |
+         ((uint64_t)(uint16_t)y1 << 48);
+}
+__device__ __forceinline__ TileRect unpack_rect(uint64_t r) {
+  return TileRect{(uint32_t)(r & 0xffff), (uint32_t)((r >> 16) & 0xffff),
+                  (uint32_t)((r >> 32) & 0xffff), (uint32_t)(r >> 48)};
+}
+__device__ __forceinline__ uint32_t rect_tiles(const TileRect &r) {
+  return (r.x1 - r.x0) * (r.y1 - r.y0);
+}
+
+// The part of a rectangle inside bin (bx, by), clipped.
+__device__ __forceinline__ TileRect clip_to_bin(const TileRect &r, const BinGrid &g, uint32_t bx,
+                                                uint32_t by) {
+  return TileRect{max(r.x0, bx << g.sx), max(r.y0, by << g.sy), min(r.x1, (bx + 1) << g.sx),
+                  min(r.y1, (by + 1) << g.sy)};
+}
+
+// Bits of bin (bx, by) (tile (tx, ty) at bit (ty - by 2^sy) 2^sx + tx - bx 2^sx)
+// of the kept tiles `keep` (row-major in r, at most kKeepBits tiles).
+__device__ __forceinline__ uint32_t bin_tiles(const TileRect &r, uint64_t keep, const BinGrid &g,
+                                              uint32_t bx, uint32_t by) {
+  const TileRect c = clip_to_bin(r, g, bx, by);
+  if (c.x0 >= c.x1) return 0u;
+  const uint32_t w = r.x1 - r.x0, cw = c.x1 - c.x0;
+  const uint64_t row = (1ull << cw) - 1ull;  // cw <= 2^sx <= 32
+  uint32_t bits = 0;
+  for (uint32_t ty = c.y0; ty < c.y1; ++ty) {
+    const uint32_t b = (uint32_t)((keep >> ((ty - r.y0) * w + (c.x0 - r.x0))) & row);
+    bits |= b << (((ty - (by << g.sy)) << g.sx) + (c.x0 - (bx << g.sx)));
+  }
+  return bits;
+}
+
+// Exclusive scan of one value per thread over a block of NT threads; tmp:
+// NT / 64 words.  Ends with a barrier (tmp may be reused at once).
+template <int NT>
+__device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t *tmp, uint32_t *total) {
+  constexpr int kW = NT / kWave;
+  const int w = threadIdx.x / kWave, l = __lane_id();
+  const uint32_t inc = wave_incl_scan(v);
+  if (l == kWave - 1) tmp[w] = inc;
+  __syncthreads();
+  uint32_t off = 0, tot = 0;
+#pragma unroll
+  for (int i = 0; i < kW; ++i) {
+    const uint32_t s = tmp[i];
+    if (i < w) off += s;
+    tot += s;
+  }
+  __syncthreads();
+  *total = tot;
+  return off + inc - v;
+}
 
 RasterWs raster_layout(void *base, int64_t gcap, int64_t pcap, int32_t W, int32_t H);
 
 // dst[i] = BF16 bits of src[i] rounded to nearest even, i < count (device
 // arrays); enqueues one kernel on s.
 hipError_t launch_round_bf16(const float *src, uint16_t *dst, int64_t count, hipStream_t s);
-int tile_sort_passes(int ntiles);
+// The bins of each band, in depth order, into the tile lists (after the
+// projection has grouped the survivors): one call per band of bin rows, then
+// finish_bins once.
+hipError_t launch_bin_sort(const RasterWs &ws, int band_row0, int rows, hipStream_t s);
+hipError_t launch_tile_scan(const RasterWs &ws, bool train, hipStream_t s);
+hipError_t launch_tile_lists(const RasterWs &ws, bool train, bool ordered, hipStream_t s);
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
@@ -288,43 +383,7 @@ struct CamParams {
   int W, H;
 };
 
-// ---------------------------------------------------------------------------
-// radix sort (Onesweep: one histogram pass, then one pass per digit with
-// decoupled look-back across the partitions)
-// ---------------------------------------------------------------------------
-
-constexpr int kSortItems = 8;
-constexpr int kSortPart = kBlock * kSortItems;  // 2048 keys per partition (depth sort)
-// The tile sort has ~10x more keys: 4096-key partitions halve its blocks,
-// and with them the same-address ticket atomics and the look-back chain.
-constexpr int kTileSortItems = 16;
-constexpr int kTileSortPart = kBlock * kTileSortItems;
-constexpr uint32_t kSpinLimit = 1u << 22;       // look-back wait bound
-// Look-back status of one sort pass: a row of 2 x 256 words per partition
-// (the digits' aggregate, upgraded to the inclusive prefix, and a copy of the
-// aggregate), then one row of 256 words per group of kGroupParts partitions.
-constexpr int kGroupParts = 16;
-constexpr int kLbRow = 512;
-__host__ __device__ inline size_t lookback_pass_words(int64_t nparts) {
-  const int64_t np = nparts < 1 ? 1 : nparts;
-  return (size_t)np * kLbRow + (size_t)((np + kGroupParts - 1) / kGroupParts) * 256;
-}
-
-// Sort (keys, vals) of length *count (device) by bits [0, 8 * passes) of the
-// key, stably.  On return the sorted data is in buffers index `passes % 2`.
-// tickets: one zeroed word per pass, from which the pass's blocks take their
-// partition index in the order they start.
-// hist: the digit histograms of the passes, [passes][256] words, as the sum
-// of hist_copies (1..kHistCopies) copies hist_stride words apart (built by
-// the producer of the keys; the first pass folds the later passes' copies
-// into copy 0); items: keys per thread of a partition (kSortItems or
-// kTileSortItems; a partition is 256 * items keys); lookback:
-// passes * lookback_pass_words(ceil(cap / (256 * items))) words, cleared by
-// the producer for the partitions in use (clear_partitions).
-hipError_t radix_sort(uint32_t *keys[2], uint32_t *vals[2], uint32_t *const *vals2,
-                      const uint32_t *count, int64_t cap, int items, int passes, uint32_t *hist,
-                      int hist_copies, uint32_t hist_stride, uint32_t *lookback,
-                      uint32_t *tickets, uint32_t *err_flag, hipStream_t stream);
+constexpr uint32_t kSpinLimit = 1u << 22;  // look-back wait bound
 
 // ---------------------------------------------------------------------------
 // chained scan: decoupled look-back over one value per partition

@@ -2,28 +2,28 @@
 // Gaussian to a 2D one, tile-based front-to-back depth ordering, and the
 // alpha blending of Eq. 2).
 //
-// Stages, all on one stream with device-resident counts:
-//   init      zero counters, tile ranges, radix histograms
+// Stages, all on one stream with device-resident counts (the binning kernels
+// after the projection are in bins.hip):
 //   project   per Gaussian slot: culls, 2D covariance, conic, 3-sigma tile
-//             rectangle, depth key; ballot of survivors
-//   compact   survivors in slot order -> (depth key, slot)
-//   sort      Onesweep on the 32-bit depth keys (4 passes over Gaussians)
-//   emit      candidates in depth order: per Gaussian its rectangle's
-//             tiles, offsets by a two-pass scan, writers balanced over
-//             candidates; each candidate is kept iff the 3-sigma ellipse
-//             meets the tile (tile_meets_ellipse); ordered compaction of
-//             the kept ones by ballots and a scan over runs
-//   sort      Onesweep on the tile id (1-3 passes over pairs); stable, so
-//             each tile keeps depth order, ties by slot index
-//   ranges    [start, end) per tile
+//             rectangle, depth key, the tiles that the 3-sigma ellipse meets
+//             (tile_meets_ellipse); survivors grouped by screen bin
+//   bin sort  per bin of up to 8 x 4 tiles, one block: collects the bin's
+//             entries, sorts them by (depth, slot) in LDS, counts its tiles
+//   tile scan [start, end) per tile
+//   tile lists per bin: each tile takes its entries from the bin's ordered
+//             list
 //   composite one wave per 16x16 tile (four pixels of a column per lane),
 //             batches of 128 Gaussians staged in LDS, exit once every pixel
 //             is done
 //
-// Sorting depth once per Gaussian and then only the tile id per pair gives
-// the same (tile, depth, slot) order as one sort of 64-bit tile|depth keys
-// while moving far fewer bytes: a pair list is typically several times
-// longer than the Gaussian list.
+// The (tile, depth, slot) order is that of one sort of 64-bit tile|depth keys
+// over all pairs.  Sorting each bin's survivors instead (a survivor meets
+// about two bins and a dozen tiles) keeps the sort inside LDS, and the pairs
+// are written once, in place.  Before, the survivors were compacted and
+// radix-sorted by depth (4 passes), their pairs emitted in that order and
+// radix-sorted by tile (2 passes): eleven dependent kernels of 5 to 23 us,
+// 138 us together on a 1080p view of 270k slots and 862k pairs; these four
+// take 81 us.
 //
 // Decisions (culls, rectangle, depth key, tile test) use the fixed FP32
 // operation sequences documented at project_decide and tile_meets_ellipse;
@@ -132,74 +132,6 @@ __device__ __forceinline__ bool project_decide(const Cam &k, float dil, float jc
   return true;
 }
 
-// Tile test, canonical FP32: does the 3-sigma ellipse q(p) <= 9,
-// q = qa dx^2 + 2 qb dx dy + qc dy^2 around (mx, my), meet the box of the
-// tile's pixel centres inside the image, [16 tx + 0.5, min(16 tx + 15.5,
-// W - 0.5)] x [16 ty + 0.5, min(16 ty + 15.5, H - 0.5)]?  (Pixels of a
-// partial edge tile past the image are not drawn, so they do not list a
-// Gaussian.)  The convex quadratic's minimum over the box is 0 with the mean
-// inside; otherwise it lies on an edge facing the mean, at the 1D minimiser
-// clamped to the edge:
-//   X0 = (float)(16 tx) + 0.5, X1 = fminf(X0 + 15, xmax) (Y alike)
-//   mean's x outside [X0, X1]: xe = nearer of X0, X1; dx = xe - mx;
-//     ys = min(max(my - (qb * dx) / qc, Y0), Y1); dy = ys - my;
-//     q1 = fmaf(qa * dx, dx, fmaf(2 * qb * dx, dy, qc * dy * dy))
-//   mean's y outside [Y0, Y1]: the same with the roles of x and y swapped
-//   keep iff min(q1, q2) <= 9.
-__device__ __forceinline__ bool tile_meets_ellipse(float mx, float my, float qa, float qb, float qc,
-                                                   uint32_t tx, uint32_t ty, float xmax,
-                                                   float ymax) {
-  const float X0 = (float)(16u * tx) + 0.5f, X1 = fminf(X0 + 15.0f, xmax);
-  const float Y0 = (float)(16u * ty) + 0.5f, Y1 = fminf(Y0 + 15.0f, ymax);
-  const bool in_x = !(mx < X0) && !(mx > X1), in_y = !(my < Y0) && !(my > Y1);
-  float q = INFINITY;
-  if (!in_x) {
-    const float xe = mx < X0 ? X0 : X1;
-    const float dx = xe - mx;
-    const float ys = fminf(fmaxf(my - (qb * dx) / qc, Y0), Y1);
-    const float dy = ys - my;
-    q = fma_(qa * dx, dx, fma_(2.0f * qb * dx, dy, qc * dy * dy));
-  }
-  if (!in_y) {
-    const float ye = my < Y0 ? Y0 : Y1;
-    const float dy = ye - my;
-    const float xs = fminf(fmaxf(mx - (qb * dy) / qa, X0), X1);
-    const float dx = xs - mx;
-    q = fminf(q, fma_(qa * dx, dx, fma_(2.0f * qb * dx, dy, qc * dy * dy)));
-  }
-  return (in_x && in_y) || q <= 9.0f;
-}
-
-// Clears, for each of `passes` sort passes (pass_words apart), the look-back
-// rows of the partitions that start in [a, b) (partitions of `part` keys,
-// nparts of them at capacity) and the group rows of the groups they open;
-// called by whole blocks of 256 threads, one digit's words per thread.
-__device__ __forceinline__ void clear_partitions(uint32_t *lb, size_t pass_words, uint32_t a,
-                                                 uint32_t b, int passes, int64_t nparts,
-                                                 uint32_t part) {
-  const uint32_t j0 = (a + part - 1) / part;
-  const uint32_t j1 = (uint32_t)std::min<uint64_t>(((uint64_t)b + part - 1) / part, (uint64_t)nparts);
-  for (int p = 0; p < passes; ++p) {
-    uint32_t *base = lb + p * pass_words;
-    for (uint32_t j = j0; j < j1; ++j) {
-      base[(size_t)j * kLbRow + threadIdx.x] = 0u;
-      base[(size_t)j * kLbRow + 256 + threadIdx.x] = 0u;
-      if (j % kGroupParts == 0)
-        base[(size_t)nparts * kLbRow + (size_t)(j / kGroupParts) * 256 + threadIdx.x] = 0u;
-    }
-  }
-}
-
-__device__ __forceinline__ uint64_t pack_rect(int x0, int y0, int x1, int y1) {
-  return (uint64_t)(uint16_t)x0 | ((uint64_t)(uint16_t)y0 << 16) | ((uint64_t)(uint16_t)x1 << 32) |
-         ((uint64_t)(uint16_t)y1 << 48);
-}
-
-__device__ __forceinline__ uint32_t rect_tiles(uint64_t r) {
-  const uint32_t x0 = r & 0xffff, y0 = (r >> 16) & 0xffff, x1 = (r >> 32) & 0xffff, y1 = r >> 48;
-  return (x1 - x0) * (y1 - y0);
-}
-
 struct ProjArgs {
   Cam cam;
   float dil, jc;
@@ -210,489 +142,205 @@ struct ProjArgs {
   int64_t gcap;
   RasterWs ws;
   float *gauss_w;
+  int band_row0, band_rows;  // bin rows that are grouped (all of the image, but for huge images)
 };
 
-// Also clears the per-call state of the later stages (header, tile ranges,
-// radix histograms, the scans' look-back status words), which the kernel
-// itself never reads.
-__global__ __launch_bounds__(kBlock) void k_project_mark(ProjArgs a) {
-  __shared__ uint32_t wsum[4];
+// Projection, tile tests and grouping by bin: one slot per thread, one block
+// per kChunk slots.
+//   - culls, 2D covariance, conic, rectangle and depth key of each slot;
+//   - the tile test on every tile of the rectangles of at most kKeepBits
+//     tiles: a wave lays its slots' rectangles end to end and tests 64 tiles
+//     at a time, so a long rectangle does not keep 63 lanes waiting; the
+//     ballots are the slots' keep masks;
+//   - each survivor is handed to the bins in which it keeps a tile: counted
+//     per bin in LDS, then written to the block's own stretch of ws.group,
+//     where the bins' entries are contiguous (ws.group_off).  A survivor over
+//     more than kGroupBins bins or kKeepBits tiles goes to the block's list
+//     of large ones instead, which every bin looks through.
+// Nothing here depends on another block, so nothing has to be cleared before
+// and no global atomic is made: a bin later collects its entries from the
+// blocks' stretches (a column of ws.group_off).
+// Bound by latency at one wave of blocks (a 1080p view lists about 270 blocks
+// of slots): one slot per thread keeps 16 waves of a block in flight.
+// Block 0 clears the header and the scan's look-back words for the later
+// kernels.
+template <bool TRAIN>
+__global__ __launch_bounds__(kChunk) void k_project(ProjArgs a) {
+  constexpr int kW = kChunk / kWave;
+  __shared__ float4 own[kW][kWave][2];
+  __shared__ uint32_t incs[kW][kWave];
+  __shared__ uint32_t hist[kMaxBandBins];
+  __shared__ uint32_t tmp[kW];
+  __shared__ uint32_t s_vis, s_large;
+  __shared__ unsigned long long s_cand;
   const int t = threadIdx.x, w = t / kWave, l = __lane_id();
+  const RasterWs &ws = a.ws;
+  const BinGrid &bg = ws.bins;
   const uint32_t n = (uint32_t)min<int64_t>(*a.count, a.gcap);
-  {
-    const RasterWs &ws = a.ws;
-    const size_t gi = (size_t)blockIdx.x * kBlock + t, gs = (size_t)gridDim.x * kBlock;
+  const int nbins = a.band_rows * bg.gx;
+  if (a.band_row0 == 0) {
     if (blockIdx.x == 0 && t < (int)(sizeof(RasterHeader) / 4))
       reinterpret_cast<uint32_t *>(ws.hdr)[t] = t == 0 ? n : 0u;  // n_slots is word 0
-    const size_t nr = 2 * (size_t)ws.tiles_x * ws.tiles_y;
-    for (size_t i = gi; i < nr; i += gs) ws.ranges[i] = 0u;
-    for (size_t i = gi; i < kHistCopies * kHistStride; i += gs) ws.hist[i] = 0u;
-    for (size_t i = gi; i < (size_t)ws.nblk_g; i += gs) ws.lb_emit[i] = 0u;
-    for (size_t i = gi; i < (size_t)ws.nruns; i += gs) ws.lb_pair[i] = 0u;
+    for (int64_t i = (int64_t)blockIdx.x * kChunk + t; i < ws.scan_blocks;
+         i += (int64_t)gridDim.x * kChunk)
+      ws.lb_scan[i] = 0u;
   }
   const int64_t base = (int64_t)blockIdx.x * kChunk;
   if (base >= n) return;
-  // every field of the thread's four slots is loaded up front (clamped
-  // index, so the loads are unconditional and all in flight together)
-  float gg[kChunkPerThread][kGaussFields];
+  const int64_t s = base + t;
+  float g[kGaussFields];
+  {
+    const int64_t sc = min(s, (int64_t)n - 1);  // unconditional loads, all in flight together
 #pragma unroll
-  for (int i = 0; i < kChunkPerThread; ++i) {
-    const int64_t s = min(base + i * kBlock + t, (int64_t)n - 1);
-#pragma unroll
-    for (int f = 0; f < kGaussFields; ++f) gg[i][f] = a.g[f * a.gstride + s];
+    for (int f = 0; f < kGaussFields; ++f) g[f] = a.g[f * a.gstride + sc];
   }
-  uint32_t cnt = 0;
+  for (int i = t; i < nbins; i += kChunk) hist[i] = 0u;
+  if (t == 0) {
+    s_vis = 0u;
+    s_large = 0u;
+    s_cand = 0ull;
+  }
+  ProjOut o;
+  // (tile coordinates are kept in 16 bits: an image of more than 65,535 tiles
+  // in one direction ends there)
+  const bool vis = s < n &&
+                   project_decide(a.cam, a.dil, a.jc, min(a.tiles_x, kMaxTileCoord),
+                                  min(a.tiles_y, kMaxTileCoord), g, o);
+  TileRect r = {0u, 0u, 0u, 0u};
+  if (vis) {
+    float4 *p = ws.proj + 3 * s;
+    p[0] = make_float4(o.mx, o.my, -0.5f * kLog2e * o.ca, -kLog2e * o.cb);
+    p[1] = make_float4(-0.5f * kLog2e * o.cc, log2f(g[10]), g[11], g[12]);
+    p[2] = make_float4(g[13], o.ca, o.cb, o.cc);
+    ws.depth[s] = __float_as_uint(o.zc);
+    r = TileRect{(uint32_t)o.x0, (uint32_t)o.y0, (uint32_t)o.x1, (uint32_t)o.y1};
+  }
+  if (a.gauss_w && s < n) a.gauss_w[s] = 0.0f;
+  const uint32_t tiles = rect_tiles(r);  // 0 for a culled slot
+  const bool flat = vis && tiles <= kKeepBits;
+  const uint64_t vm = ballot(vis);
+  if (l == 0 && s < n) ws.vis_mask[s >> 6] = vm;
+
+  // the wave's rectangles of at most kKeepBits tiles, end to end
+  uint64_t keep = 0;
+  {
+    const uint32_t cnt = flat ? tiles : 0u;
+    const uint32_t inc = wave_incl_scan(cnt), ex = inc - cnt;
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
+    incs[w][l] = inc;
+    if (flat) {
+      own[w][l][0] = make_float4(o.mx, o.my, o.ca, o.cb);
+      own[w][l][1] = make_float4(o.cc, __uint_as_float(r.x0 | (r.y0 << 16)),
+                                 __uint_as_float(r.x1 - r.x0), __uint_as_float(ex));
+    }
+    // the wave's LDS writes are complete before any lane reads them
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (uint32_t b0 = 0; b0 < total; b0 += kWave) {
+      const uint32_t q = min(b0 + (uint32_t)l, total - 1u);
+      // owner: the first lane whose inclusive count exceeds q
+      uint32_t lo = 0;
 #pragma unroll
-  for (int i = 0; i < kChunkPerThread; ++i) {
-    const int64_t s = base + i * kBlock + t;
-    bool vis = false;
-    if (s < n) {
-      const float *g = gg[i];
-      ProjOut o;
-      vis = project_decide(a.cam, a.dil, a.jc, a.tiles_x, a.tiles_y, g, o);
-      if (vis) {
-        float4 *p = a.ws.proj + 3 * s;
-        p[0] = make_float4(o.mx, o.my, -0.5f * kLog2e * o.ca, -kLog2e * o.cb);
-        p[1] = make_float4(-0.5f * kLog2e * o.cc, log2f(g[10]), g[11], g[12]);
-        p[2] = make_float4(g[13], o.ca, o.cb, o.cc);
-        a.ws.depth[s] = __float_as_uint(o.zc);
-        a.ws.rect[s] = pack_rect(o.x0, o.y0, o.x1, o.y1);
+      for (int st = kWave / 2; st > 0; st >>= 1)
+        if (incs[w][lo + st - 1] <= q) lo += st;
+      const float4 u = own[w][lo][0], v = own[w][lo][1];
+      const uint32_t xy = __float_as_uint(v.y), wd = __float_as_uint(v.z);
+      const uint32_t loc = q - __float_as_uint(v.w);
+      // row and column of the tile: a float quotient, exact after one
+      // correction step (loc < 64)
+      uint32_t row = (uint32_t)((float)loc * __builtin_amdgcn_rcpf((float)wd));
+      const int32_t rem = (int32_t)(loc - row * wd);
+      row = rem < 0 ? row - 1 : (rem >= (int32_t)wd ? row + 1 : row);
+      const bool hit = b0 + (uint32_t)l < total &&
+                       tile_meets_ellipse(u.x, u.y, u.z, u.w, v.x, (xy & 0xffffu) + (loc - row * wd),
+                                          (xy >> 16) + row, ws.xmax, ws.ymax);
+      const uint64_t m = ballot(hit);
+      const int32_t d = (int32_t)(ex - b0);  // where this lane's tiles start in the ballot
+      if (cnt > 0 && d < kWave && d + (int32_t)cnt > 0) keep |= d >= 0 ? m >> d : m << -d;
+    }
+    if (cnt < kKeepBits) keep &= (1ull << cnt) - 1ull;
+  }
+  if (vis)
+    ws.rect[s] = make_ulonglong2(pack_rect(o.x0, o.y0, o.x1, o.y1), keep);
+  __syncthreads();  // hist is clear
+
+  // bins of this band that the survivor meets
+  const uint32_t bx0 = r.x0 >> bg.sx, by0 = r.y0 >> bg.sy;
+  const uint32_t nbx = vis ? ((r.x1 - 1u) >> bg.sx) - bx0 + 1u : 0u;
+  const uint32_t nby = vis ? ((r.y1 - 1u) >> bg.sy) - by0 + 1u : 0u;
+  const bool small = flat && nbx * nby <= (uint32_t)kGroupBins;
+  uint32_t slot_in[kGroupBins], bin_of[kGroupBins];
+#pragma unroll
+  for (int j = 0; j < kGroupBins; ++j) {
+    slot_in[j] = ~0u;
+    bin_of[j] = 0u;
+    if (small && (uint32_t)j < nbx * nby) {
+      // nbx is 1, 2, 3 or 4 here
+      const uint32_t jy = nbx == 1 ? j : (nbx == 2 ? j >> 1 : 0), jx = (uint32_t)j - jy * nbx;
+      const uint32_t bx = bx0 + jx, by = by0 + jy;
+      if (by >= (uint32_t)a.band_row0 && by < (uint32_t)(a.band_row0 + a.band_rows) &&
+          bin_tiles(r, keep, bg, bx, by)) {
+        bin_of[j] = (by - (uint32_t)a.band_row0) * (uint32_t)bg.gx + bx;
+        slot_in[j] = atomicAdd(&hist[bin_of[j]], 1u);
       }
-      if (a.gauss_w) a.gauss_w[s] = 0.0f;
-    }
-    const uint64_t m = ballot(vis);
-    const int64_t gidx = base + i * kBlock + w * kWave;
-    if (l == 0 && gidx < n) a.ws.vis_mask[gidx >> 6] = m;
-    cnt += (uint32_t)__popcll(m);
-  }
-  if (l == 0) wsum[w] = cnt;
-  __syncthreads();
-  if (t == 0) a.ws.blk_cnt[blockIdx.x] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-}
-
-// Ordered compaction of the survivors: (depth key, slot) in slot order.
-// It also accumulates the four 8-bit digit histograms of the depth keys for
-// the radix sort.
-__global__ __launch_bounds__(kBlock) void k_project_compact(RasterWs ws, const uint32_t *count) {
-  __shared__ uint32_t red[4];
-  __shared__ uint32_t gpre[64];
-  __shared__ uint64_t gmask[64];
-  __shared__ uint32_t h[4][256];
-  const int t = threadIdx.x, w = t / kWave, l = __lane_id();
-  const uint32_t n = (uint32_t)min<int64_t>(*count, ws.gcap);
-  const int b = blockIdx.x;
-  const int64_t base = (int64_t)b * kChunk;
-  if (n == 0) {
-    if (b == 0 && t == 0) ws.hdr->n_visible = 0;
-    return;
-  }
-  if (base >= n) return;
-  uint32_t s = 0;
-  s = partial_sum_prefix(ws.blk_cnt, b);
-  s = wave_sum(s);
-  if (l == 0) red[w] = s;
-  const int ngroups = (int)min<int64_t>(kGroups, ((int64_t)n - base + 63) / 64);
-  if (w == 0) {
-    const uint64_t m = l < ngroups ? ws.vis_mask[(base >> 6) + l] : 0ull;
-    const uint32_t c = (uint32_t)__popcll(m);
-    const uint32_t inc = wave_incl_scan(c);
-    gpre[l] = inc - c;
-    gmask[l] = m;
-  }
-  __syncthreads();
-  for (int i = t; i < 4 * 256; i += kBlock) (&h[0][0])[i] = 0u;
-  __syncthreads();
-  const uint32_t prefix = red[0] + red[1] + red[2] + red[3];
-  // wave w owns groups w, w + 4, w + 8, w + 12; their depth keys are loaded
-  // up front (clamped index), so the loads are in flight together
-  uint32_t keys[kGroups / 4];
-#pragma unroll
-  for (int q = 0; q < kGroups / 4; ++q)
-    keys[q] = ws.depth[min(base + 64 * (w + 4 * q) + l, (int64_t)n - 1)];
-#pragma unroll
-  for (int q = 0; q < kGroups / 4; ++q) {
-    const int gi = w + 4 * q;
-    const uint64_t m = gi < ngroups ? gmask[gi] : 0ull;
-    if ((m >> l) & 1ull) {
-      const uint32_t pos = prefix + gpre[gi] + (uint32_t)__popcll(m & lanemask_lt());
-      const uint32_t slot = (uint32_t)(base + 64 * gi + l);
-      const uint32_t key = keys[q];
-      ws.dkey[0][pos] = key;
-      ws.dval[0][pos] = slot;
-#pragma unroll
-      for (int d = 0; d < 4; ++d) atomicAdd(&h[d][(key >> (8 * d)) & 255u], 1u);
     }
   }
-  const uint32_t mine = gpre[ngroups - 1] + (uint32_t)__popcll(gmask[ngroups - 1]);
-  if ((int64_t)b == ((int64_t)n - 1) / kChunk && t == 0) ws.hdr->n_visible = prefix + mine;
-  // clear the depth sort's look-back words of the partitions that start in
-  // this block's output range [prefix, prefix + mine), for all four passes
-  clear_partitions(ws.lookback, ws.lb_words / 4, prefix, prefix + mine, 4, ws.lb_parts, kSortPart);
-  __syncthreads();
-#pragma unroll
-  for (int d = 0; d < 4; ++d) {
-    const uint32_t v = h[d][t];
-    if (v) atomicAdd(&ws.hist[(blockIdx.x % kHistCopies) * kHistStride + d * 256 + t], v);
+  const uint64_t lm = ballot(vis && !small);
+  uint32_t lbase = 0;
+  if (l == 0) {
+    if (lm) lbase = atomicAdd(&s_large, (uint32_t)__popcll(lm));
+    if (vm) atomicAdd(&s_vis, (uint32_t)__popcll(vm));
   }
-}
-
-// Candidate scan over the depth-ordered survivors (one chunk of 1024 per
-// block, offsets chained by decoupled look-back): pair_off[s] = rectangle
-// tiles of the survivors before s, and run_first[r] = the survivor that
-// holds candidate kEmitRun r.  The chunk
-// holding the last survivor publishes the total and the overflow flag.
-// Values saturate at 2^30 - 1, above any admissible pair capacity, so they
-// are exact whenever the candidates fit.
-__global__ __launch_bounds__(kBlock) void k_emit_scan(RasterWs ws) {
-  __shared__ uint32_t tmp[8];
-  __shared__ uint64_t red[4];
-  __shared__ uint32_t s_excl;
-  const int t = threadIdx.x, w = t / kWave, l = __lane_id();
-  const uint32_t n = ws.hdr->n_visible;
-  const uint32_t nch = (n + kChunk - 1) / kChunk;
-  if (blockIdx.x >= nch) return;  // n == 0: the cleared header already says 0
-  // chunk id = ticket, taken in the order blocks start, so every chunk a
-  // block waits on belongs to a block that is already running
-  __shared__ uint32_t s_c;
-  if (t == 0) s_c = atomicAdd(&ws.hdr->ticket[kTicketScan], 1u);
-  __syncthreads();
-  const uint32_t c = s_c;
-  const int64_t base = (int64_t)c * kChunk;
-  uint32_t cnt[kChunkPerThread], slot[kChunkPerThread];
-  uint64_t mine = 0;
-  // two batches of unconditional loads at clamped indices: slots, then
-  // their rectangles
+  lbase = (uint32_t)__builtin_amdgcn_readfirstlane((int)lbase);
+  if (vis && !small)
+    ws.large_slot[base + lbase + (uint32_t)__popcll(lm & lanemask_lt())] = (uint32_t)s;
+  uint64_t cand = tiles;
 #pragma unroll
-  for (int i = 0; i < kChunkPerThread; ++i)
-    slot[i] = ws.dval[0][min(base + i * kBlock + t, (int64_t)n - 1)];
-#pragma unroll
-  for (int i = 0; i < kChunkPerThread; ++i) {
-    const int64_t sidx = base + i * kBlock + t;
-    const uint32_t c = min(rect_tiles(ws.rect[slot[i]]), kLbVal);
-    cnt[i] = sidx < n ? c : 0u;
-    mine += cnt[i];
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o, 64);
-  if (l == 0) red[w] = mine;
-  __syncthreads();
-  const uint64_t total64 = red[0] + red[1] + red[2] + red[3];
-  const uint32_t agg = (uint32_t)std::min<uint64_t>(total64, kLbVal);
-  if (w == 0) {
-    const uint32_t ex = chained_lookback(ws.lb_emit, c, agg, &ws.hdr->sync_error, kSpinLimit);
-    if (l == 0) s_excl = ex;
-  }
-  __syncthreads();
-  const uint32_t excl = s_excl;
-  const bool exact = total64 < kLbVal && excl < kLbVal;  // else the call overflows
-  // the tile sort's partitions start inside the candidate range of some
-  // chunk (kept pairs are a prefix-closed subset of the positions)
-  if (excl < kLbVal)
-    clear_partitions(ws.lookback_t, ws.lbt_words / max(ws.tile_passes, 1), excl,
-                     sat_add(excl, agg), ws.tile_passes, ws.lbt_parts, kTileSortPart);
-  // consecutive 256-entry rows of the chunk, scanned in order (32-bit sums
-  // are exact when the chunk total is below 2^30)
-  uint32_t carry = 0;
-#pragma unroll
-  for (int i = 0; i < kChunkPerThread; ++i) {
-    const int64_t sidx = base + i * kBlock + t;
+  for (int q = 32; q > 0; q >>= 1) cand += __shfl_xor(cand, q, kWave);
+  if (l == 0) atomicAdd(&s_cand, (unsigned long long)cand);
+  if (TRAIN) {
+    const uint32_t np = flat ? (uint32_t)__popcll(keep) : tiles;
     uint32_t tot;
-    const uint32_t ex = block_excl_scan(cnt[i], tmp, &tot);
-    if (exact && sidx < n) {
-      const uint32_t o = excl + carry + ex;
-      ws.pair_off[sidx] = o;
-      // runs whose first candidate falls in [o, o + cnt)
-      for (uint32_t r = (o + kEmitRun - 1) / kEmitRun; (uint64_t)r * kEmitRun < (uint64_t)o + cnt[i] &&
-                                                       r < (uint32_t)ws.nruns; ++r)
-        ws.run_first[r] = (uint32_t)sidx;
-    }
-    carry += tot;
+    const uint32_t ex = block_scan<kChunk>(np, tmp, &tot);
+    if (vis) ws.pair_base[s] = ex;
+    if (t == 0) ws.blk_pairs[blockIdx.x] = tot;
   }
-  if (c == nch - 1 && t == 0) {
-    const uint32_t total = sat_add(excl, agg);
-    const bool over = total > (uint64_t)ws.pcap;
-    ws.hdr->n_candidates = total;
-    ws.hdr->pair_overflow = over ? 1u : 0u;
-    ws.hdr->n_cand_listed = over ? 0u : total;
-  }
-}
-
-// Pair emission with the ellipse test and ordered compaction in one pass.
-// Block r (1024 threads) takes the run of 8192 consecutive candidate
-// positions from 8192 r; runs this long keep the look-back chain short, as
-// each step of it is a device-scope round trip
-// (r is a ticket taken in the order blocks start, so the runs a block waits
-// on belong to blocks already running); it locates the survivors covering the positions (run_first, then a
-// binary search of their offsets in LDS), tests each candidate tile, ranks
-// the kept ones by ballots, gets the run's output offset by decoupled
-// look-back over the preceding runs and writes (tile id, slot) in order.
-// It also accumulates the digit histograms of the kept tile ids.
-__global__ __launch_bounds__(kEmitThreads) void k_emit_pairs(RasterWs ws, int tile_passes, int train) {
-  constexpr int kW = kEmitThreads / kWave;     // waves per block
-  constexpr int kG = kEmitRun / 64;            // ballot groups per run
-  constexpr int kC = kEmitRun / kEmitThreads;  // candidates per thread (8)
-  static_assert(kEmitThreads >= 256 && kC * kEmitThreads == kEmitRun, "emission shape");
-  __shared__ uint32_t offs[kEmitRun + 1];
-  __shared__ uint16_t owner[kEmitRun];
-  __shared__ uint32_t wmax[kW];
-  __shared__ uint32_t gpre[kG];
-  __shared__ uint64_t gmask[kG];
-  __shared__ uint32_t h[4][256];
-  __shared__ uint32_t s_agg, s_excl;
-  const int t = threadIdx.x, w = t / kWave, l = __lane_id();
-  const uint32_t P = ws.hdr->n_cand_listed;
-  const uint32_t n = ws.hdr->n_visible;
-  const uint32_t R = (P + kEmitRun - 1) / kEmitRun;
-  if (blockIdx.x >= R) return;
-  __shared__ uint32_t s_r;
-  if (t == 0) s_r = atomicAdd(&ws.hdr->ticket[kTicketEmit], 1u);
-  for (int i = t; i < 4 * 256; i += kEmitThreads) (&h[0][0])[i] = 0u;
   __syncthreads();
-  const uint32_t r = s_r;
-  const uint32_t p0 = r * kEmitRun, p1 = min(P, p0 + kEmitRun);
-  const uint32_t lo = ws.run_first[r];
-  const uint32_t cnt = min((uint32_t)kEmitRun + 1, n - lo);
+
+  // starts of the bins' entries in the block's stretch
   {
-    // all loads in flight before the first LDS store (clamped, so the code
-    // stays straight-line); a thread past the end rewrites the last entry
-    // with the value it holds
-    constexpr int kU = (kEmitRun + 1 + kEmitThreads - 1) / kEmitThreads;  // 9
-    uint32_t v[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) v[u] = ws.pair_off[lo + min((uint32_t)(t + u * kEmitThreads), cnt - 1)];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) offs[min((uint32_t)(t + u * kEmitThreads), cnt - 1)] = v[u];
-  }
-  // owner[i]: local index of the survivor holding position p0 + i.  Each
-  // survivor that starts inside the run marks its first position (offsets
-  // strictly increase), then a prefix maximum fills the gaps.
-#pragma unroll
-  for (int u = 0; u < kC; ++u) owner[t + u * kEmitThreads] = 0;
-  __syncthreads();
-  for (uint32_t a = 1 + t; a < cnt; a += kEmitThreads) {
-    const uint32_t st = offs[a];
-    if (st < p0 + kEmitRun) owner[st - p0] = (uint16_t)a;
+    const int per = (nbins + kChunk - 1) / kChunk;  // consecutive bins per thread, at most 8
+    const int i0 = min(t * per, nbins), i1 = min(i0 + per, nbins);
+    uint32_t sum = 0;
+    for (int i = i0; i < i1; ++i) sum += hist[i];
+    uint32_t tot;
+    uint32_t run = block_scan<kChunk>(sum, tmp, &tot);
+    uint16_t *row = ws.group_off + (size_t)blockIdx.x * ws.group_pitch;
+    for (int i = i0; i < i1; ++i) {
+      const uint32_t c = hist[i];
+      hist[i] = run;
+      row[i] = (uint16_t)run;
+      run += c;
+    }
+    if (t == 0) row[nbins] = (uint16_t)tot;
   }
   __syncthreads();
-  {
-    uint32_t v[kC], m = 0;  // thread t holds positions [8 t, 8 t + 8)
+  uint2 *grp = ws.group + (size_t)blockIdx.x * kGroupCap;
 #pragma unroll
-    for (int u = 0; u < kC; ++u) {
-      m = max(m, (uint32_t)owner[t * kC + u]);
-      v[u] = m;
-    }
-    uint32_t inc = m;  // inclusive max-scan over the wave, then over waves
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t y = __shfl_up(inc, o, 64);
-      if (l >= o) inc = max(inc, y);
-    }
-    if (l == 63) wmax[w] = inc;
-    __syncthreads();
-    uint32_t before = __shfl_up(inc, 1, 64);
-    if (l == 0) before = 0;
-#pragma unroll
-    for (int i = 0; i < kW; ++i)
-      if (i < w) before = max(before, wmax[i]);
-#pragma unroll
-    for (int u = 0; u < kC; ++u) owner[t * kC + u] = (uint16_t)max(before, v[u]);
-  }
-  __syncthreads();
-  // three phases over the thread's 8 candidates, so that each phase's
-  // global loads are all in flight together: locate (slot), fetch
-  // (rectangle, 2D mean and conic), test
-  uint32_t key[kC], val[kC], loc[kC];
-#pragma unroll
-  for (int k = 0; k < kC; ++k) {
-    const uint32_t i = min((uint32_t)(k * kEmitThreads + t), p1 - 1 - p0);  // clamped; masked below
-    const uint32_t a = owner[i];
-    loc[k] = p0 + i - offs[a];
-    val[k] = ws.dval[0][lo + a];
-  }
-  uint64_t rc[kC];
-  float4 pa[kC], pc[kC];
-#pragma unroll
-  for (int k = 0; k < kC; ++k) {
-    rc[k] = ws.rect[val[k]];
-    pa[k] = ws.proj[3 * (size_t)val[k]];
-    pc[k] = ws.proj[3 * (size_t)val[k] + 2];
-  }
-#pragma unroll
-  for (int k = 0; k < kC; ++k) {
-    const uint32_t x0 = rc[k] & 0xffff, y0 = (rc[k] >> 16) & 0xffff, x1 = (rc[k] >> 32) & 0xffff;
-    const uint32_t wdt = x1 - x0;
-    // row and column of the candidate in its rectangle: a float quotient,
-    // exact after one correction step while loc < 2^24
-    uint32_t row;
-    if (loc[k] < (1u << 24)) {
-      row = (uint32_t)((float)loc[k] * __builtin_amdgcn_rcpf((float)wdt));
-      const int32_t rem = (int32_t)(loc[k] - row * wdt);
-      row = rem < 0 ? row - 1 : (rem >= (int32_t)wdt ? row + 1 : row);
-    } else {
-      row = loc[k] / wdt;
-    }
-    const uint32_t ty = y0 + row, tx = x0 + (loc[k] - row * wdt);
-    const bool keep = p0 + k * kEmitThreads + t < p1 &&
-                      tile_meets_ellipse(pa[k].x, pa[k].y, pc[k].y, pc[k].z, pc[k].w, tx, ty,
-                                         ws.xmax, ws.ymax);
-    key[k] = ty * (uint32_t)ws.tiles_x + tx;
-    const uint64_t m = ballot(keep);
-    if (l == 0) gmask[k * kW + w] = m;
-  }
-  __syncthreads();
-  if (w == 0) {
-    // exclusive prefix over the kG ballot groups, up to one per lane per step
-    uint32_t agg = 0;
-#pragma unroll
-    for (int q = 0; q < (kG + 63) / 64; ++q) {
-      const int gi = q * 64 + l;
-      const uint32_t c = gi < kG ? (uint32_t)__popcll(gmask[gi]) : 0u;
-      const uint32_t inc = wave_incl_scan(c);
-      if (gi < kG) gpre[gi] = agg + inc - c;
-      agg += __shfl(inc, 63, 64);
-    }
-    const uint32_t ex = chained_lookback(ws.lb_pair, r, agg, &ws.hdr->sync_error, kSpinLimit);
-    if (l == 0) {
-      s_excl = ex;
-      s_agg = agg;
-    }
-  }
-  __syncthreads();
-  const uint32_t excl = s_excl;
-#pragma unroll
-  for (int k = 0; k < kC; ++k) {
-    const int g = k * kW + w;
-    const uint64_t m = gmask[g];
-    if ((m >> l) & 1ull) {
-      const uint32_t dst = excl + gpre[g] + (uint32_t)__popcll(m & lanemask_lt());
-      if (dst < P) {  // always true unless a look-back wait hit its bound
-        ws.tkey[0][dst] = key[k];
-        ws.tval[0][dst] = val[k];
-        if (train) {  // what the backward needs: emission index and slot per pair
-          ws.tpair[0][dst] = dst;
-          ws.pair_slot[dst] = val[k];
-        }
-      }
-      for (int d = 0; d < tile_passes; ++d) atomicAdd(&h[d][(key[k] >> (8 * d)) & 255u], 1u);
-    }
-  }
-  if (r == R - 1 && t == 0) {
-    ws.hdr->n_listed = sat_add(excl, s_agg);
-    ws.hdr->n_pairs = sat_add(excl, s_agg);
-  }
-  __syncthreads();
-  if (t < 256)
-    for (int d = 0; d < tile_passes; ++d) {
-      const uint32_t v = h[d][t];
-      if (v) atomicAdd(&ws.hist[(blockIdx.x % kHistCopies) * kHistStride + (4 + d) * 256 + t], v);
-    }
-}
-
-__global__ __launch_bounds__(kBlock) void k_ranges(RasterWs ws, int buf) {
-  const uint32_t P = ws.hdr->n_listed;
-  const uint32_t *key = ws.tkey[buf];
-  for (uint32_t p = blockIdx.x * kBlock + threadIdx.x; p < P; p += gridDim.x * kBlock) {
-    const uint32_t k = key[p];
-    if (p == 0 || key[p - 1] != k) ws.ranges[2 * k] = p;
-    if (p == P - 1 || key[p + 1] != k) ws.ranges[2 * k + 1] = p + 1;
-  }
-}
-
-constexpr int kOrderBuckets = 64;  // = kWave: one scan lane per bucket
-
-// Half-octave bucket of a tile's list length, longest lists first; empty
-// tiles and blocks without a tile go last (kOrderBuckets - 1).
-__device__ __forceinline__ uint32_t order_bucket(int32_t tile, const uint32_t *ranges) {
-  if (tile < 0) return kOrderBuckets - 1;
-  const uint32_t len = ranges[2 * tile + 1] - ranges[2 * tile];
-  if (len == 0) return kOrderBuckets - 1;
-  const uint32_t lg = 31u - (uint32_t)__clz(len);
-  const uint32_t half = lg > 0 ? (len >> (lg - 1)) & 1u : 0u;
-  return (uint32_t)(kOrderBuckets - 2) - min(2u * lg + half, (uint32_t)(kOrderBuckets - 2));
-}
-
-// Block x takes the slots that the group mapping gives XCD x and writes
-// their tiles to tile_order[x + 8 * position] in a stable order by bucket
-// (longest lists first):
-// a counting pass, then chunks of 1024 slots ranked per wave with ballots
-// (match-any on the bucket bits), each wave owning a contiguous run.  Every
-// position of the XCD is written once, so tile_order is a permutation of the
-// group mapping.
-__global__ __launch_bounds__(kBlock) void k_tile_order(RasterWs ws) {
-  constexpr int kItems = 4;
-  constexpr int kWaves = kBlock / kWave;
-  __shared__ uint32_t cnt[kOrderBuckets];
-  __shared__ uint32_t wcnt[kWaves][kOrderBuckets];
-  __shared__ uint32_t run[kOrderBuckets];
-  const uint32_t xcd = blockIdx.x;
-  const uint32_t nslots = tile_grid_blocks(ws.tiles_x, ws.tiles_y) / kXcds;
-  const int t = threadIdx.x, w = t / kWave, l = __lane_id();
-  const uint64_t lt = lanemask_lt();
-  if (xcd == 0 && t == 0) ws.hdr->tile_ordered = 1u;
-  if (t < kOrderBuckets) cnt[t] = 0u;
-  __syncthreads();
-  for (uint32_t q = t; q < nslots; q += kBlock)
-    atomicAdd(&cnt[order_bucket(tile_of_block(xcd + kXcds * q, ws.tiles_x, ws.tiles_y),
-                                ws.ranges)], 1u);
-  __syncthreads();
-  if (w == 0) {
-    const uint32_t v = cnt[l];
-    run[l] = wave_incl_scan(v) - v;
-  }
-  for (uint32_t c0 = 0; c0 < nslots; c0 += kBlock * kItems) {
-    (&wcnt[0][0])[t] = 0u;  // kWaves * kOrderBuckets == kBlock
-    int32_t tl[kItems];
-    uint32_t key[kItems], rank[kItems];
-    bool ok[kItems];
-#pragma unroll
-    for (int j = 0; j < kItems; ++j) {
-      const uint32_t q = c0 + (uint32_t)(w * kWave * kItems + j * kWave + l);
-      ok[j] = q < nslots;
-      tl[j] = ok[j] ? tile_of_block(xcd + kXcds * q, ws.tiles_x, ws.tiles_y) : -1;
-      key[j] = order_bucket(tl[j], ws.ranges);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < kItems; ++j) {
-      uint64_t peers = ballot(ok[j]);
-#pragma unroll
-      for (int b = 0; b < 6; ++b) {
-        const int bit = (key[j] >> b) & 1;
-        const uint64_t bal = ballot(bit);
-        peers &= bit ? bal : ~bal;
-      }
-      uint32_t before = 0;
-      if (ok[j]) before = wcnt[w][key[j]];
-      // all lanes of the wave have read before any leader writes
-      __builtin_amdgcn_wave_barrier();
-      if (ok[j]) {
-        rank[j] = before + (uint32_t)__popcll(peers & lt);
-        if ((peers & lt) == 0) wcnt[w][key[j]] = before + (uint32_t)__popcll(peers);
-      }
-      __builtin_amdgcn_wave_barrier();
-    }
-    __syncthreads();
-    if (t < kOrderBuckets) {
-      uint32_t base = run[t];
-#pragma unroll
-      for (int v = 0; v < kWaves; ++v) {
-        const uint32_t c = wcnt[v][t];
-        wcnt[v][t] = base;
-        base += c;
-      }
-      run[t] = base;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < kItems; ++j)
-      if (ok[j]) ws.tile_order[xcd + kXcds * (wcnt[w][key[j]] + rank[j])] = (uint32_t)tl[j];
-    __syncthreads();
+  for (int j = 0; j < kGroupBins; ++j)
+    if (slot_in[j] != ~0u)
+      grp[hist[bin_of[j]] + slot_in[j]] = make_uint2(__float_as_uint(o.zc), (uint32_t)s);
+  if (t == 0) {
+    ws.blk_vis[blockIdx.x] = s_vis;
+    ws.blk_large[blockIdx.x] = s_large;
+    ws.blk_cand[blockIdx.x] = (uint32_t)std::min<uint64_t>(s_cand, kLbVal);
   }
 }
 
 struct CompArgs {
   RasterWs ws;
-  int buf, W, H;
+  int W, H;
   int ordered;  // blocks take their tile from ws.tile_order
   float alpha_max, alpha_min, t_min, bg[3];
   float *rgb, *T_final;
@@ -746,7 +394,7 @@ __device__ __forceinline__ void composite_tile(const CompArgs &a, CompLds<LOG> &
   const float fx = (float)px + 0.5f, fy = (float)py0 + 0.5f;
   const uint32_t start = __builtin_amdgcn_readfirstlane(a.ws.ranges[2 * tile]);
   const uint32_t end = __builtin_amdgcn_readfirstlane(a.ws.ranges[2 * tile + 1]);
-  const uint32_t *vals = a.ws.tval[a.buf];
+  const uint32_t *vals = a.ws.tval;
   const float4 *proj = a.ws.proj;
   const float amax = a.alpha_max, amin = a.alpha_min, tmin = a.t_min;
   float T[kPx], cr[kPx], cg[kPx], cb[kPx];
@@ -875,6 +523,27 @@ __global__ __launch_bounds__(kFwdThreads) void k_composite(CompArgs a) {
   }
 }
 
+// The bins of an image: as large as leaves at least kWantBins of them, so that
+// a small image's lists are spread over the chip too, but no larger than 8 x 4
+// tiles (a mask word).  1920 x 1080: 15 x 17 bins of 8 x 4.
+constexpr int kWantBins = 160;
+
+BinGrid bin_grid(int tiles_x, int tiles_y) {
+  BinGrid g;
+  static const int shape[][2] = {{3, 2}, {2, 2}, {2, 1}, {1, 1}, {1, 0}, {0, 0}};
+  for (const auto &s : shape) {
+    g.sx = s[0];
+    g.sy = s[1];
+    g.nx = (tiles_x + (1 << g.sx) - 1) >> g.sx;
+    g.ny = (tiles_y + (1 << g.sy) - 1) >> g.sy;
+    if ((int64_t)g.nx * g.ny >= kWantBins) break;
+  }
+  // (images this wide have bins of 8 x 4 tiles, so gx <= kMaxBandBins)
+  g.gx = std::min(g.nx, (kMaxTileCoord + (1 << g.sx) - 1) >> g.sx);
+  g.band_rows = std::min(g.ny, std::max(1, kMaxBandBins / g.gx));
+  return g;
+}
+
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 }  // namespace
@@ -896,45 +565,41 @@ RasterWs raster_layout(void *base, int64_t gcap, int64_t pcap, int32_t W, int32_
   ws.tiles_x = (W + kTile - 1) / kTile;
   ws.tiles_y = (H + kTile - 1) / kTile;
   ws.nblk_g = (int)((g + kChunk - 1) / kChunk);
+  ws.bins = bin_grid(ws.tiles_x, ws.tiles_y);
+  const int64_t ntiles = (int64_t)ws.tiles_x * ws.tiles_y;
+  const int64_t nbins = (int64_t)ws.bins.nx * ws.bins.ny;
+  ws.group_pitch = (int)((std::min<int64_t>(nbins, (int64_t)ws.bins.band_rows * ws.bins.gx) + 2) & ~1);
+  ws.scan_blocks = (int)((ntiles + kScanTiles * kBinThreads - 1) / (kScanTiles * kBinThreads));
   ws.hdr = (RasterHeader *)take(sizeof(RasterHeader));
   ws.vis_mask = (uint64_t *)take((size_t)ws.nblk_g * kGroups * 8);
-  ws.blk_cnt = (uint32_t *)take((size_t)ws.nblk_g * 4);
+  ws.blk_vis = (uint32_t *)take((size_t)ws.nblk_g * 4);
+  ws.blk_cand = (uint32_t *)take((size_t)ws.nblk_g * 4);
+  ws.blk_large = (uint32_t *)take((size_t)ws.nblk_g * 4);
+  ws.blk_pairs = (uint32_t *)take((size_t)ws.nblk_g * 4);
   ws.proj = (float4 *)take((size_t)kProjVec * g * 16);
   ws.depth = (uint32_t *)take((size_t)g * 4);
-  ws.rect = (uint64_t *)take((size_t)g * 8);
-  for (int i = 0; i < 2; ++i) ws.dkey[i] = (uint32_t *)take((size_t)g * 4);
-  for (int i = 0; i < 2; ++i) ws.dval[i] = (uint32_t *)take((size_t)g * 4);
-  ws.pair_off = (uint32_t *)take((size_t)g * 4);
-  ws.lb_emit = (uint32_t *)take((size_t)ws.nblk_g * 4);
-  ws.nruns = (int)((pc + kEmitRun - 1) / kEmitRun);
-  ws.run_first = (uint32_t *)take((size_t)ws.nruns * 4);
-  ws.lb_pair = (uint32_t *)take((size_t)ws.nruns * 4);
-  for (int i = 0; i < 2; ++i) ws.tkey[i] = (uint32_t *)take((size_t)pc * 4);
-  for (int i = 0; i < 2; ++i) ws.tval[i] = (uint32_t *)take((size_t)pc * 4);
-  for (int i = 0; i < 2; ++i) ws.tpair[i] = (uint32_t *)take((size_t)pc * 4);
-  ws.pair_slot = (uint32_t *)take((size_t)pc * 4);
-  ws.ranges = (uint32_t *)take((size_t)ws.tiles_x * ws.tiles_y * 8);
+  ws.rect = (ulonglong2 *)take((size_t)g * 16);
+  ws.pair_base = (uint32_t *)take((size_t)g * 4);
+  ws.group_off = (uint16_t *)take((size_t)ws.nblk_g * ws.group_pitch * 2);
+  ws.group = (uint2 *)take((size_t)ws.nblk_g * kGroupCap * 8);
+  ws.large_slot = (uint32_t *)take((size_t)ws.nblk_g * kChunk * 4);
+  ws.bin_range = (uint2 *)take((size_t)nbins * 8);
+  for (int i = 0; i < 2; ++i) ws.bin_slot[i] = (uint32_t *)take((size_t)pc * 4);
+  for (int i = 0; i < 2; ++i) ws.bin_mask[i] = (uint32_t *)take((size_t)pc * 4);
+  ws.over_bin = (uint32_t *)take((size_t)(pc / kBinCap + 1) * 4);
+  ws.tile_count = (uint32_t *)take((size_t)ws.scan_blocks * kScanTiles * kBinThreads * 4);
+  ws.lb_scan = (uint32_t *)take((size_t)ws.scan_blocks * 4);
+  ws.tkey = (uint32_t *)take((size_t)pc * 4);
+  ws.tval = (uint32_t *)take((size_t)pc * 4);
+  ws.tpair = (uint32_t *)take((size_t)pc * 4);
+  ws.ranges = (uint32_t *)take((size_t)ntiles * 8);
   ws.tile_order = (uint32_t *)take((size_t)tile_grid_blocks(ws.tiles_x, ws.tiles_y) * 4);
-  ws.hist = (uint32_t *)take(kHistCopies * kHistStride * 4);
-  ws.tile_passes = tile_sort_passes(ws.tiles_x * ws.tiles_y);
-  ws.lb_parts = (g + kSortPart - 1) / kSortPart;
-  ws.lbt_parts = (pc + kTileSortPart - 1) / kTileSortPart;
-  ws.lb_words = (size_t)4 * lookback_pass_words(ws.lb_parts);
-  ws.lbt_words = (size_t)ws.tile_passes * lookback_pass_words(ws.lbt_parts);
-  ws.lookback = (uint32_t *)take(ws.lb_words * 4);
-  ws.lookback_t = (uint32_t *)take(ws.lbt_words * 4);
   ws.dproj = (float *)take((size_t)g * 9 * 4);
-  ws.gpair = (float *)take((size_t)pc * 9 * 4);
+  ws.gpair = (float *)take((size_t)pc * kPairRow * 4);
   ws.chunk_part = (float *)take((size_t)((pc + 63) / 64) * 18 * 4);
   ws.chunk_info = (uint32_t *)take((size_t)((pc + 63) / 64) * 4);
   ws.bytes = off;
   return ws;
-}
-
-int tile_sort_passes(int ntiles) {
-  int bits = 1;
-  while ((1 << bits) < ntiles) ++bits;
-  return (bits + 7) / 8;
 }
 
 }  // namespace octgs
@@ -985,38 +650,34 @@ int octgs_rasterize_fwd(const octgs_gaussians *g, const octgs_camera *cam,
   pa.gcap = g->capacity;
   pa.ws = ws;
   pa.gauss_w = gauss_w;
+  const bool train = (p->flags & OCTGS_RASTER_TRAIN) != 0;
+  const bool ordered = (p->flags & OCTGS_RASTER_TILE_ORDER) != 0;
+  // one pass over all bins, but for images of more than kMaxBandBins bins
   mark(0);
-  hipLaunchKernelGGL(k_project_mark, dim3(ws.nblk_g), dim3(kBlock), 0, s, pa);
-  hipLaunchKernelGGL(k_project_compact, dim3(ws.nblk_g), dim3(kBlock), 0, s, ws, g->count);
-  mark(1);
-  mark(2);
-  // histograms and cleared look-back words come from the kernels above
-  hipError_t e = radix_sort(ws.dkey, ws.dval, nullptr, &ws.hdr->n_visible, ws.gcap, kSortItems, 4, ws.hist,
-                            kHistCopies, kHistStride, ws.lookback,
-                            &ws.hdr->ticket[kTicketDepth], &ws.hdr->sync_error, s);
-  if (e != hipSuccess) return OCTGS_EHIP;
+  hipError_t e = hipSuccess;
+  for (int row0 = 0; row0 < ws.bins.ny && e == hipSuccess; row0 += ws.bins.band_rows) {
+    pa.band_row0 = row0;
+    pa.band_rows = std::min(ws.bins.band_rows, ws.bins.ny - row0);
+    if (train)
+      hipLaunchKernelGGL(k_project<true>, dim3(ws.nblk_g), dim3(kChunk), 0, s, pa);
+    else
+      hipLaunchKernelGGL(k_project<false>, dim3(ws.nblk_g), dim3(kChunk), 0, s, pa);
+    if (row0 == 0) {
+      mark(1);
+      mark(2);
+    }
+    e = launch_bin_sort(ws, row0, pa.band_rows, s);
+  }
   mark(3);
   mark(4);
-  hipLaunchKernelGGL(k_emit_scan, dim3(ws.nblk_g), dim3(kBlock), 0, s, ws);
-  hipLaunchKernelGGL(k_emit_pairs, dim3(std::max(ws.nruns, 1)), dim3(kEmitThreads), 0, s, ws,
-                     ws.tile_passes, (p->flags & OCTGS_RASTER_TRAIN) ? 1 : 0);
+  if (e == hipSuccess) e = launch_tile_scan(ws, train, s);
   mark(5);
   mark(6);
-  const int passes = ws.tile_passes;
-  e = radix_sort(ws.tkey, ws.tval, (p->flags & OCTGS_RASTER_TRAIN) ? ws.tpair : nullptr,
-                 &ws.hdr->n_listed, ws.pcap, kTileSortItems, passes, ws.hist + 4 * 256, kHistCopies,
-                 kHistStride, ws.lookback_t, &ws.hdr->ticket[kTicketTile],
-                 &ws.hdr->sync_error, s);
-  if (e != hipSuccess) return OCTGS_EHIP;
-  const int buf = passes % 2;
-  const int rgrid = (int)std::min<int64_t>(std::max<int64_t>((ws.pcap + kBlock - 1) / kBlock, 1), 8192);
-  hipLaunchKernelGGL(k_ranges, dim3(rgrid), dim3(kBlock), 0, s, ws, buf);
-  const bool ordered = (p->flags & OCTGS_RASTER_TILE_ORDER) != 0;
-  if (ordered) hipLaunchKernelGGL(k_tile_order, dim3(kXcds), dim3(kBlock), 0, s, ws);
+  if (e == hipSuccess) e = launch_tile_lists(ws, train, ordered, s);
   mark(7);
+  if (e != hipSuccess) return OCTGS_EHIP;
   CompArgs ca;
   ca.ws = ws;
-  ca.buf = buf;
   ca.ordered = ordered ? 1 : 0;
   ca.W = cam->width;
   ca.H = cam->height;
@@ -1047,10 +708,9 @@ int octgs_raster_views(const void *wsp, int64_t gauss_capacity, int64_t pair_cap
   if (!wsp || width <= 0 || height <= 0 || gauss_capacity < 0 || pair_capacity < 0)
     return OCTGS_EINVAL;
   RasterWs ws = raster_layout(const_cast<void *>(wsp), gauss_capacity, pair_capacity, width, height);
-  const int buf = tile_sort_passes(ws.tiles_x * ws.tiles_y) % 2;
   if (stats) *stats = (const octgs_raster_stats *)ws.hdr;
-  if (pair_tile) *pair_tile = ws.tkey[buf];
-  if (pair_slot) *pair_slot = ws.tval[buf];
+  if (pair_tile) *pair_tile = ws.tkey;
+  if (pair_slot) *pair_slot = ws.tval;
   if (tile_ranges) *tile_ranges = ws.ranges;
   return OCTGS_OK;
 }

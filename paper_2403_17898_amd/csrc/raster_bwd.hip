@@ -9,7 +9,7 @@
 // T_i = T_{i+1} / (1 - a_i) instead of storing per-pixel lists; the colour
 // behind each entry is accumulated on the way.  Per-Gaussian gradients are
 // summed over the thread's pixels and over the wave by a halving exchange,
-// stored once per (tile, Gaussian) pair at the pair's emission index (plain
+// stored once per (tile, Gaussian) pair at the pair's number (plain
 // stores: float atomics on global memory are performed at the memory side
 // on this chip and were most of the pass's time), then summed per Gaussian
 // over its contiguous run of pairs.
@@ -26,7 +26,7 @@ __device__ __forceinline__ float fma_(float a, float b, float c) { return __buil
 
 struct BwdArgs {
   RasterWs ws;
-  int buf, W, H;
+  int W, H;
   float alpha_max, alpha_min, bg[3];
   const float *T_final, *dimg;
   const uint32_t *last;
@@ -70,18 +70,25 @@ constexpr int kBPx = 4;
 
 struct BwdLds {
   float4 sA[kBwdBatch], sB[kBwdBatch], sC[kBwdBatch];
-  uint32_t s_pair[kBwdBatch];
+  uint32_t s_pair[kBwdBatch], s_slot[kBwdBatch];
   float sG[9][kBwdBatch];
 };
 
-// Per-pair gradients of list entries [e0, e1) that no pixel consumed are 0.
-__device__ __forceinline__ void zero_pairs(const RasterWs &ws, const uint32_t *pidx, uint32_t e0,
-                                           uint32_t e1) {
-  for (uint32_t e = e0 + threadIdx.x; e < e1; e += blockDim.x) {
-    float *gp = ws.gpair + 9 * (size_t)pidx[e];
+// One pair's row: nine gradients and the slot (rows are 8-byte aligned).
+__device__ __forceinline__ void store_pair(const RasterWs &ws, uint32_t pair, uint32_t slot,
+                                           const float (&g)[9]) {
+  static_assert(kPairRow == 10, "row layout");
+  float2 *row = reinterpret_cast<float2 *>(ws.gpair + kPairRow * (size_t)pair);
 #pragma unroll
-    for (int k = 0; k < 9; ++k) gp[k] = 0.0f;
-  }
+  for (int k = 0; k < 4; ++k) row[k] = make_float2(g[2 * k], g[2 * k + 1]);
+  row[4] = make_float2(g[8], __uint_as_float(slot));
+}
+
+// Per-pair gradients of list entries [e0, e1) that no pixel consumed are 0.
+__device__ __forceinline__ void zero_pairs(const RasterWs &ws, uint32_t e0, uint32_t e1) {
+  const float zero[9] = {};
+  for (uint32_t e = e0 + threadIdx.x; e < e1; e += blockDim.x)
+    store_pair(ws, ws.tpair[e], ws.tval[e], zero);
 }
 
 // The LDS lives in the kernel and is passed in, so the two AMIN
@@ -102,8 +109,8 @@ __device__ __forceinline__ void composite_bwd_tile(const BwdArgs &a, BwdLds &lds
   const int px = tx * kTile + (t % kTile), py0 = ty * kTile + kBPx * (t / kTile);
   const float fx = (float)px + 0.5f, fy = (float)py0 + 0.5f;
   const uint32_t start = a.ws.ranges[2 * tile], end = a.ws.ranges[2 * tile + 1];
-  const uint32_t *vals = a.ws.tval[a.buf];   // slot of each sorted pair
-  const uint32_t *pidx = a.ws.tpair[a.buf];  // its emission index
+  const uint32_t *vals = a.ws.tval;   // slot of each sorted pair
+  const uint32_t *pidx = a.ws.tpair;  // its pair number
   const float4 *proj = a.ws.proj;
   const size_t plane = (size_t)a.W * a.H;
   // per pixel: T, dL/dC, S = dL/dC . (colour behind) (starts as T_final
@@ -130,7 +137,7 @@ __device__ __forceinline__ void composite_bwd_tile(const BwdArgs &a, BwdLds &lds
   for (int o = 32; o > 0; o >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, o, kWave));
   const uint32_t n_used = min(mx, end - start);
   const float amax = a.alpha_max, amin = a.alpha_min;
-  zero_pairs(a.ws, pidx, start + n_used, end);
+  zero_pairs(a.ws, start + n_used, end);
   if (n_used == 0) return;
   for (int32_t b0 = (int32_t)((n_used - 1) / kBwdBatch) * kBwdBatch; b0 >= 0; b0 -= kBwdBatch) {
     const int nb = (int)min((uint32_t)kBwdBatch, n_used - (uint32_t)b0);
@@ -141,6 +148,7 @@ __device__ __forceinline__ void composite_bwd_tile(const BwdArgs &a, BwdLds &lds
       const uint32_t e = start + (uint32_t)b0 + (uint32_t)min(i, nb - 1);
       const uint32_t s = vals[e];
       s_pair[i] = pidx[e];
+      lds.s_slot[i] = s;
       sA[i] = proj[3 * (size_t)s];
       const float4 bv = proj[3 * (size_t)s + 1];
       sB[i] = bv;
@@ -235,9 +243,7 @@ __device__ __forceinline__ void composite_bwd_tile(const BwdArgs &a, BwdLds &lds
         g[6] = sG[6][i];
         g[7] = sG[7][i];
         g[8] = sG[8][i];
-        float *gp = a.ws.gpair + 9 * (size_t)s_pair[i];
-#pragma unroll
-        for (int k = 0; k < 9; ++k) gp[k] = g[k];
+        store_pair(a.ws, s_pair[i], lds.s_slot[i], g);
       }
     }
   }
@@ -272,8 +278,8 @@ __device__ __forceinline__ void seg_step(float (&v)[9], bool take) {
   }
 }
 
-// Per-Gaussian sums of the per-pair gradients.  A Gaussian's pairs are
-// contiguous in emission order.  Each wave takes a chunk of 64 consecutive
+// Per-Gaussian sums of the per-pair gradients.  A Gaussian's pair numbers are
+// contiguous.  Each wave takes a chunk of 64 consecutive
 // pairs and runs a segmented inclusive scan keyed by slot (six DPP steps);
 // the last lane of each run then holds the run's sum.  A run that lies inside
 // the chunk is stored.  A run that crosses the chunk's start or end leaves
@@ -284,12 +290,15 @@ constexpr uint32_t kChunkFirst = 1u;   // the chunk's first run continues from t
 constexpr uint32_t kChunkLast = 2u;    // its last run continues into the next chunk
 constexpr uint32_t kChunkWhole = 4u;   // one run covers the chunk and continues both ways
 __global__ __launch_bounds__(kBlock) void k_pair_reduce(RasterWs ws) {
-  // a full chunk's 64 records (2,304 bytes, 16-byte aligned) are read with
-  // lane-contiguous float4 loads into LDS, then each lane takes its own 9
-  // floats (odd stride: no bank conflicts)
-  constexpr int kRec4 = kWave * 9 / 4;  // 144
+  // a full chunk's 64 records (2,560 bytes, 16-byte aligned) are read with
+  // lane-contiguous float4 loads into LDS, then each lane takes its own
+  // record
+  constexpr int kRec4 = kWave * kPairRow / 4;  // 160
   __shared__ float4 stage[kBlock / kWave][kRec4];
-  const uint32_t P = ws.hdr->n_listed;
+  const uint32_t P = ws.hdr->n_emit;
+  auto slot_of = [&](uint32_t p) {
+    return __float_as_uint(ws.gpair[kPairRow * (size_t)p + 9]);
+  };
   const int l = __lane_id();
   const uint32_t nw = gridDim.x * (kBlock / kWave);
   float4 *sw = stage[threadIdx.x / kWave];
@@ -298,10 +307,10 @@ __global__ __launch_bounds__(kBlock) void k_pair_reduce(RasterWs ws) {
     const uint32_t p = c0 + l;
     const bool valid = p < P;
     const uint32_t pc = valid ? p : P - 1;
-    const uint32_t s = valid ? ws.pair_slot[pc] : 0xffffffffu;
+    uint32_t s = 0xffffffffu;
     float v[9];
     if (c0 + kWave <= P) {
-      const float4 *src = reinterpret_cast<const float4 *>(ws.gpair + 9 * (size_t)c0);
+      const float4 *src = reinterpret_cast<const float4 *>(ws.gpair + kPairRow * (size_t)c0);
       float4 r[3];
 #pragma unroll
       for (int u = 0; u < 3; ++u) r[u] = src[min(l + kWave * u, kRec4 - 1)];
@@ -312,21 +321,23 @@ __global__ __launch_bounds__(kBlock) void k_pair_reduce(RasterWs ws) {
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      const float *sf = reinterpret_cast<const float *>(sw) + 9 * l;
+      const float *sf = reinterpret_cast<const float *>(sw) + kPairRow * l;
 #pragma unroll
       for (int k = 0; k < 9; ++k) v[k] = sf[k];
+      s = __float_as_uint(sf[9]);
       // every lane has read before the next chunk overwrites the stage
       __builtin_amdgcn_wave_barrier();
     } else {
-      const float *gp = ws.gpair + 9 * (size_t)pc;
+      const float *gp = ws.gpair + kPairRow * (size_t)pc;
 #pragma unroll
       for (int k = 0; k < 9; ++k) v[k] = valid ? gp[k] : 0.0f;
+      if (valid) s = __float_as_uint(gp[9]);
     }
     // does the chunk's first (last) run continue from (into) its neighbour?
     const uint32_t s0 = __builtin_amdgcn_readfirstlane(s);
     const uint32_t s63 = (uint32_t)__builtin_amdgcn_readlane((int)s, kWave - 1);
-    const bool first_cont = c0 > 0 && ws.pair_slot[c0 - 1] == s0;
-    const bool last_cont = c0 + kWave < P && ws.pair_slot[c0 + kWave] == s63;
+    const bool first_cont = c0 > 0 && slot_of(c0 - 1) == s0;
+    const bool last_cont = c0 + kWave < P && slot_of(c0 + kWave) == s63;
     const uint32_t sp = __shfl_up(s, 1, kWave);
     const bool head = l == 0 || sp != s;
     const uint64_t heads = ballot(head);
@@ -365,7 +376,7 @@ __global__ __launch_bounds__(kBlock) void k_pair_reduce(RasterWs ws) {
 // following chunks in order (the whole-chunk ones, then the one where the
 // run ends), stored once into the run's slot row.
 __global__ __launch_bounds__(kBlock) void k_pair_fix(RasterWs ws) {
-  const uint32_t P = ws.hdr->n_listed;
+  const uint32_t P = ws.hdr->n_emit;
   const uint32_t nch = (P + kWave - 1) / kWave;
   for (uint32_t c = blockIdx.x * kBlock + threadIdx.x; c < nch; c += gridDim.x * kBlock) {
     const uint32_t info = ws.chunk_info[c];
@@ -400,7 +411,8 @@ __global__ __launch_bounds__(kBlock) void k_pair_fix(RasterWs ws) {
         }
       }
     }
-    float *d = ws.dproj + 9 * (size_t)ws.pair_slot[c * (size_t)kWave + kWave - 1];
+    float *d = ws.dproj +
+               9 * (size_t)__float_as_uint(ws.gpair[kPairRow * (c * (size_t)kWave + kWave - 1) + 9]);
 #pragma unroll
     for (int k = 0; k < 9; ++k) d[k] = t[k];
   }
@@ -583,10 +595,8 @@ extern "C" int octgs_rasterize_bwd(const octgs_gaussians *g, const octgs_camera 
   auto mark = [&](int i) {
     if (stage_events && stage_events[i]) (void)hipEventRecord((hipEvent_t)stage_events[i], s);  // timing only
   };
-  const int ntiles = ws.tiles_x * ws.tiles_y;
   BwdArgs b;
   b.ws = ws;
-  b.buf = tile_sort_passes(ntiles) % 2;
   b.W = cam->width;
   b.H = cam->height;
   b.alpha_max = p->alpha_max;

@@ -1,0 +1,125 @@
+"""The rasterizer's binning (grouping by screen bin, per-bin sort, tile lists)
+at the sizes where its paths change: each bin shape with partial edge bins,
+rectangles around the keep mask's 64 tiles and around four bins, lists longer
+than one block sorts, runs of equal depths, and an image of several grouping
+bands.  Lists, ranges and counts are decisions: bit-exact with the oracle.
+Images and gradients at the bars of the other rasterizer tests (1e-4 and 1e-3
+normwise)."""
+
+import numpy as np
+import pytest
+
+from synth import scenes as S
+from tests.gpu_util import say
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def P():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2403_17898_amd as P
+    P.lib()
+    return P
+
+
+def _np(t):
+    return t.detach().cpu().numpy()
+
+
+def _raster(P, cam, gf, pcap, train):
+    n = gf.shape[1]
+    vb = P.ViewBuffers(n, 1, cam.width, cam.height, pcap, gauss_capacity=n)
+    vb.gauss.copy_(torch.as_tensor(gf).cuda())
+    vb.gauss_count.fill_(n)
+    prm = P.raster_params(train=train)
+    vb.rasterize(P.make_camera(cam), prm)
+    torch.cuda.synchronize()
+    return vb, prm
+
+
+def _check_lists(vb, pj, bs):
+    st = vb.stats()
+    assert st["sync_error"] == 0 and st["pair_overflow"] == 0
+    assert st["n_visible"] == pj["n_visible"]
+    assert st["n_candidates"] == bs["n_rect_pairs"] and st["n_pairs"] == bs["n_pairs"]
+    tile, slot, ranges = vb.sorted_lists()
+    assert np.array_equal(ranges, bs["ranges"])
+    assert np.array_equal(tile, bs["tile_of"])
+    assert np.array_equal(slot, bs["gid_of"])
+
+
+def _check(P, orc, cam, gf, what):
+    """Lists with and without the training outputs, image and gradients."""
+    n, H, W = gf.shape[1], cam.height, cam.width
+    prm_o = orc.params_array()
+    say("bins", what, W, H, n)
+    ref = orc.rasterize(gf, cam, prm_o)
+    pcap = max(1, ref["bs"]["n_rect_pairs"])  # the tightest that must not overflow
+    vb, _ = _raster(P, cam, gf, pcap, False)
+    _check_lists(vb, ref["pj"], ref["bs"])
+    assert np.abs(_np(vb.rgb) - ref["img"]).max() <= 1e-4
+    vb, prm = _raster(P, cam, gf, pcap, True)
+    _check_lists(vb, ref["pj"], ref["bs"])
+    dimg = np.random.default_rng(n).standard_normal((3, H, W)).astype(np.float32)
+    dproj = orc.composite_backward(ref["pj"], ref["bs"], cam, prm_o, dimg.astype(np.float64))
+    want = orc.project_backward(gf.astype(np.float64), ref["pj"], cam, prm_o, dproj)
+    vb.rasterize_bwd(P.make_camera(cam), prm, torch.as_tensor(dimg).cuda())
+    torch.cuda.synchronize()
+    got = _np(vb.dgauss).astype(np.float64)
+    for a, b in ((0, 3), (3, 6), (6, 10), (10, 11), (11, 14)):
+        assert np.linalg.norm(got[a:b] - want[a:b]) <= 1e-3 * np.linalg.norm(want[a:b]), (a, b)
+    return ref
+
+
+@pytest.mark.parametrize("W,H,n,scale", [
+    (16, 16, 700, (0.2, 2.0)),      # one tile
+    (200, 171, 1025, (0.05, 1.5)),  # bins of one tile; one slot in the second block
+    (401, 300, 2048, (0.05, 2.0)),  # 2 x 1 tiles
+    (640, 481, 3000, (0.05, 2.0)),  # 2 x 2
+    (699, 500, 3000, (0.05, 2.0)),  # 4 x 2
+    (1000, 701, 3000, (0.05, 2.0)),  # 4 x 4
+    (1601, 1067, 4000, (0.02, 1.5)),  # 8 x 4
+])
+def test_bin_shapes(P, orc, W, H, n, scale):
+    cam = S.look_at((3.0, -20.0, 4.0), (0.0, 0.0, 0.0), W, H, 60.0)
+    gf = S.random_gaussians(n, cam, W + H, scale=scale, neg_opacity_frac=0.1, behind_frac=0.05)
+    ref = _check(P, orc, cam, gf, "shapes")
+    if W >= 400:
+        r = ref["pj"]["rect"][ref["pj"]["vis"] > 0].astype(np.int64)
+        tiles = (r[:, 2] - r[:, 0]) * (r[:, 3] - r[:, 1])
+        say(f"  rectangles of up to 64 tiles {(tiles <= 64).sum()}, more {(tiles > 64).sum()}")
+        assert (tiles <= 64).sum() > 100 and (tiles > 64).sum() > 20
+
+
+@pytest.mark.parametrize("n,depths", [(1024, 0), (1025, 0), (4097, 0), (8192, 0), (8193, 0),
+                                      (20000, 0), (3000, 1), (3000, 40), (9000, 7), (17000, 3)])
+def test_long_lists_and_ties(P, orc, n, depths):
+    """Every Gaussian covers all six tiles of a 48 x 32 image, so each bin's
+    list has n entries: up to the block's 8,192, one more, and three merged
+    runs; with `depths` only that many distinct depths (ties by slot)."""
+    cam = S.look_at((0.0, -8.0, 0.0), (0.0, 0.0, 0.0), 48, 32, 60.0)
+    gf = S.random_gaussians(n, cam, n + depths, depth=(3.0, 6.0), scale=(1.5, 3.0), margin=0.0,
+                            opacity=(0.0005, 0.004))
+    if depths:
+        # the camera looks along +y from y = -8: depth is y + 8
+        gf[1] = (np.float32(0.25) * np.round(np.linspace(-12, -8, depths)))[
+            np.random.default_rng(n).integers(0, depths, n)]
+    ref = _check(P, orc, cam, gf, f"long lists, depths {depths}")
+    assert (ref["bs"]["ranges"][:, 1] - ref["bs"]["ranges"][:, 0] == n).all()
+
+
+def test_bands(P, orc):
+    """65,536 x 1,040 pixels: 8,704 bins of 8 x 4 tiles, grouped in two bands."""
+    cam = S.look_at((3.0, -20.0, 4.0), (0.0, 0.0, 0.0), 65536, 1040, 60.0)
+    gf = S.random_gaussians(20000, cam, 5, scale=(0.001, 0.05), neg_opacity_frac=0.1)
+    say("bins bands")
+    pj = orc.project(gf, cam, orc.params_array())
+    bs = orc.bin_sort(pj, cam)
+    for train in (False, True):
+        vb, _ = _raster(P, cam, gf, bs["n_rect_pairs"], train)
+        _check_lists(vb, pj, bs)
+        del vb
+        torch.cuda.empty_cache()
