@@ -14,7 +14,7 @@
 // with A1 = 2 mu_x mu_y + C1, A2 = 2 s_xy + C2, B1 = mu_x^2 + mu_y^2 + C1,
 // B2 = s_xx + s_yy + C2, so dS/dx = w * m0 + 2 x (w * m1) + y (w * m2).
 //
-// One kernel does both correlations.  A block of 256 threads walks down a
+// Large images: one kernel does both correlations.  A block of 256 threads walks down a
 // strip of kOutW = 236 output columns (236 + 2 x 10 image columns, one per
 // thread), two image rows per step:
 //   - the rows' (m, d, m^2, d^2) with m = (x + y) / 2 and d = x - y go to LDS
@@ -81,6 +81,7 @@ __device__ __forceinline__ float fma_(float a, float b, float c) { return __buil
 
 struct SsimArgs {
   const float *x, *y;
+  float *m0, *m1, *m2;  // derivative maps (workspace; tiled passes)
   float *part;  // per-block loss partial sums: [2][blocks] (workspace)
   float *dimg, *loss;
   int H, W, rows;
@@ -243,6 +244,185 @@ __global__ __launch_bounds__(kBlock) void k_ssim(SsimArgs a) {
   if (t == 0) a.part[(int64_t)gridDim.x * gridDim.y * gridDim.z + block_index()] = l1 * acc_l1;
 }
 
+// ---- small images: two tiled passes -----------------------------------------
+// A strip takes rows / 2 + 11 steps of about a microsecond one after the other
+// however small the image, so an image that does not fill the chip with strips
+// is done in 64 x 16 tiles instead, all at once: pass 1 writes the three
+// derivative maps to the workspace, pass 2 correlates them.  Each stages its
+// input with a 5-pixel halo in LDS and runs the window as a horizontal then a
+// vertical sweep, each thread producing four adjacent outputs from one
+// register window.
+constexpr int kSW = 64, kSH = 16;
+constexpr int kRW = kSW + 2 * kR, kRH = kSH + 2 * kR;  // 74 x 26 staged region
+
+int64_t tile_blocks(int64_t n_images, int32_t height, int32_t width) {
+  return (int64_t)((width + kSW - 1) / kSW) * ((height + kSH - 1) / kSH) * n_images;
+}
+
+// Largest call done in tiles.  Measured (us, tiles / strips): 3 x 51 x 88 15 / 24,
+// 3 x 480 x 640 35 / 48, 3 x 540 x 960 (1.56M) 42 / 43, 3 x 720 x 1280 (2.76M)
+// 69 / 52, 3 x 1066 x 1600 115 / 72.
+constexpr int64_t kTileElements = 1600000;
+
+// Stage `nmaps` planes of the (kRH x kRW) region around the block's tile
+// (zeros outside the image).
+template <int NM>
+__device__ __forceinline__ void stage(const float *const *src, int64_t base, int H, int W,
+                                      float (*dst)[kRH][kRW]) {
+  const int x0 = blockIdx.x * kSW - kR, y0 = blockIdx.y * kSH - kR;
+  for (int i = threadIdx.x; i < kRH * kRW; i += kBlock) {
+    const int r = i / kRW, c = i - r * kRW;
+    const int gy = y0 + r, gx = x0 + c;
+    const bool in = gy >= 0 && gy < H && gx >= 0 && gx < W;
+    const int64_t o = base + (int64_t)(in ? gy : 0) * W + (in ? gx : 0);
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+      const float v = src[m][o];
+      dst[m][r][c] = in ? v : 0.0f;
+    }
+  }
+}
+
+__global__ __launch_bounds__(kBlock) void k_ssim_fwd(SsimArgs a) {
+  __shared__ float in[2][kRH][kRW];
+  __shared__ float hs[5][kRH][kSW];
+  __shared__ float red[4];
+  const int t = threadIdx.x;
+  const int64_t base = (int64_t)blockIdx.z * a.H * a.W;
+  {
+    const float *src[2] = {a.x, a.y};
+    stage<2>(src, base, a.H, a.W, in);
+  }
+  __syncthreads();
+  // horizontal sweep: rows of the region, 4 outputs per task
+  for (int task = t; task < kRH * (kSW / 4); task += kBlock) {
+    const int r = task / (kSW / 4), j0 = (task % (kSW / 4)) * 4;
+    float xv[kTaps + 3], yv[kTaps + 3];
+#pragma unroll
+    for (int q = 0; q < kTaps + 3; ++q) {
+      xv[q] = in[0][r][j0 + q];
+      yv[q] = in[1][r][j0 + q];
+    }
+#pragma unroll
+    for (int o = 0; o < 4; ++o) {
+      float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f, s4 = 0.0f;
+#pragma unroll
+      for (int q = 0; q < kTaps; ++q) {
+        const float X = xv[o + q], Y = yv[o + q];
+        const float gX = a.g[q] * X, gY = a.g[q] * Y;
+        s0 += gX;
+        s1 += gY;
+        s2 = fma_(gX, X, s2);
+        s3 = fma_(gY, Y, s3);
+        s4 = fma_(gX, Y, s4);
+      }
+      hs[0][r][j0 + o] = s0; hs[1][r][j0 + o] = s1; hs[2][r][j0 + o] = s2;
+      hs[3][r][j0 + o] = s3; hs[4][r][j0 + o] = s4;
+    }
+  }
+  __syncthreads();
+  // vertical sweep: 4 rows per thread at one column; SSIM and its partials
+  const int j = t % kSW, r0 = (t / kSW) * 4;
+  float st[5][4];
+#pragma unroll
+  for (int k = 0; k < 5; ++k) {
+    float v[kTaps + 3];
+#pragma unroll
+    for (int q = 0; q < kTaps + 3; ++q) v[q] = hs[k][r0 + q][j];
+#pragma unroll
+    for (int o = 0; o < 4; ++o) {
+      float s = 0.0f;
+#pragma unroll
+      for (int q = 0; q < kTaps; ++q) s = fma_(a.g[q], v[o + q], s);
+      st[k][o] = s;
+    }
+  }
+  const int gx = blockIdx.x * kSW + j;
+  const float coef = -a.w_ssim * a.inv_n;
+  float acc = 0.0f;
+#pragma unroll
+  for (int o = 0; o < 4; ++o) {
+    const int gy = blockIdx.y * kSH + r0 + o;
+    if (gx < a.W && gy < a.H) {
+      const float mx = st[0][o], my = st[1][o];
+      const float sxx = st[2][o] - mx * mx, syy = st[3][o] - my * my, sxy = st[4][o] - mx * my;
+      const float A1 = fma_(2.0f * mx, my, kC1), A2 = fma_(2.0f, sxy, kC2);
+      const float B1 = fma_(mx, mx, fma_(my, my, kC1)), B2 = sxx + syy + kC2;
+      const float iA1 = 1.0f / A1, iA2 = 1.0f / A2, iB1 = 1.0f / B1, iB2 = 1.0f / B2;
+      const float S = A1 * A2 * iB1 * iB2;
+      acc += S;
+      const int64_t o_ = base + (int64_t)gy * a.W + gx;
+      a.m0[o_] = coef * S * 2.0f * (my * (iA1 - iA2) + mx * (iB2 - iB1));
+      a.m1[o_] = coef * (-S * iB2);
+      a.m2[o_] = coef * (2.0f * S * iA2);
+    }
+  }
+  acc = block_sum_f(acc, red);
+  if (t == 0) a.part[block_index()] = coef * acc;
+}
+
+__global__ __launch_bounds__(kBlock) void k_ssim_bwd(SsimArgs a) {
+  __shared__ float in[3][kRH][kRW];
+  __shared__ float hs[3][kRH][kSW];
+  __shared__ float red[4];
+  const int t = threadIdx.x;
+  const int64_t base = (int64_t)blockIdx.z * a.H * a.W;
+  {
+    const float *src[3] = {a.m0, a.m1, a.m2};
+    stage<3>(src, base, a.H, a.W, in);
+  }
+  __syncthreads();
+  for (int task = t; task < kRH * (kSW / 4); task += kBlock) {
+    const int r = task / (kSW / 4), j0 = (task % (kSW / 4)) * 4;
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+      float v[kTaps + 3];
+#pragma unroll
+      for (int q = 0; q < kTaps + 3; ++q) v[q] = in[m][r][j0 + q];
+#pragma unroll
+      for (int o = 0; o < 4; ++o) {
+        float s = 0.0f;
+#pragma unroll
+        for (int q = 0; q < kTaps; ++q) s = fma_(a.g[q], v[o + q], s);
+        hs[m][r][j0 + o] = s;
+      }
+    }
+  }
+  __syncthreads();
+  const int j = t % kSW, r0 = (t / kSW) * 4;
+  float cv[3][4];
+#pragma unroll
+  for (int m = 0; m < 3; ++m) {
+    float v[kTaps + 3];
+#pragma unroll
+    for (int q = 0; q < kTaps + 3; ++q) v[q] = hs[m][r0 + q][j];
+#pragma unroll
+    for (int o = 0; o < 4; ++o) {
+      float s = 0.0f;
+#pragma unroll
+      for (int q = 0; q < kTaps; ++q) s = fma_(a.g[q], v[o + q], s);
+      cv[m][o] = s;
+    }
+  }
+  const int gx = blockIdx.x * kSW + j;
+  const float l1 = a.w_l1 * a.inv_n;
+  float acc = 0.0f;
+#pragma unroll
+  for (int o = 0; o < 4; ++o) {
+    const int gy = blockIdx.y * kSH + r0 + o;
+    if (gx < a.W && gy < a.H) {
+      const int64_t o_ = base + (int64_t)gy * a.W + gx;
+      const float X = a.x[o_], Y = a.y[o_];
+      const float d = X - Y;
+      const float sg = d > 0.0f ? l1 : (d < 0.0f ? -l1 : 0.0f);
+      a.dimg[o_] = fma_(2.0f * X, cv[1][o], fma_(Y, cv[2][o], cv[0][o])) + sg;
+      acc += fabsf(d);
+    }
+  }
+  acc = block_sum_f(acc, red);
+  if (t == 0) a.part[(int64_t)gridDim.x * gridDim.y * gridDim.z + block_index()] = l1 * acc;
+}
+
 // One block: *loss += w_ssim + the per-block partial sums, added in double
 // in a fixed order (the loss is the same bit for bit on every run).
 __global__ __launch_bounds__(kBlock) void k_loss_finish(const float *__restrict__ part, int64_t n,
@@ -326,12 +506,12 @@ extern "C" {
 
 size_t octgs_photometric_workspace_bytes(int64_t n_images, int32_t height, int32_t width) {
   if (n_images < 0 || height < 0 || width < 0) return 0;
-  // Three planes per image and two words per 64 x 16 tile: the size that the
-  // ABI has always asked for.  The kernel writes 2 * ssim_blocks partial sums
-  // only, fewer than the three planes hold (a block has at least 8 x 236
-  // pixels, or is an image's only one in that direction).
-  const int64_t tiles = (int64_t)((width + 63) / 64) * ((height + 15) / 16) * n_images;
-  return (size_t)(3 * n_images * (int64_t)height * width + 2 * tiles) * sizeof(float) + 256;
+  // Three maps and two partial sums per tile, as the tiled passes use.  The
+  // strip kernel writes 2 * ssim_blocks partial sums only, fewer than the
+  // maps hold (a block has at least 8 x 236 pixels, or is an image's only one
+  // in that direction).
+  return (size_t)(3 * n_images * (int64_t)height * width +
+                  2 * tile_blocks(n_images, height, width)) * sizeof(float) + 256;
 }
 
 int octgs_photometric_loss_grad(const float *img, const float *target, int64_t n_images,
@@ -354,7 +534,9 @@ int octgs_photometric_loss_grad(const float *img, const float *target, int64_t n
   if (ws_bytes < octgs_photometric_workspace_bytes(n_images, height, width)) return OCTGS_ENOSPC;
   SsimArgs a;
   a.x = img; a.y = target;
-  a.part = (float *)ws;
+  const bool tiled = n <= kTileElements;
+  a.m0 = (float *)ws; a.m1 = a.m0 + n; a.m2 = a.m1 + n;
+  a.part = tiled ? a.m2 + n : (float *)ws;
   a.dimg = dimg; a.loss = loss;
   a.H = height; a.W = width;
   a.rows = strip_rows(n_images, height, width);
@@ -366,10 +548,18 @@ int octgs_photometric_loss_grad(const float *img, const float *target, int64_t n
     sum += gs[q];
   }
   for (int q = 0; q < kTaps; ++q) a.g[q] = (float)(gs[q] / sum);
-  const dim3 grid((width + kOutW - 1) / kOutW, (height + a.rows - 1) / a.rows, (unsigned)n_images);
-  hipLaunchKernelGGL(k_ssim, grid, dim3(kBlock), 0, s, a);
-  hipLaunchKernelGGL(k_loss_finish, dim3(1), dim3(kBlock), 0, s, a.part,
-                     2 * ssim_blocks(n_images, height, width), w_ssim, loss);
+  int64_t parts;
+  if (tiled) {
+    const dim3 grid((width + kSW - 1) / kSW, (height + kSH - 1) / kSH, (unsigned)n_images);
+    hipLaunchKernelGGL(k_ssim_fwd, grid, dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_ssim_bwd, grid, dim3(kBlock), 0, s, a);
+    parts = tile_blocks(n_images, height, width);
+  } else {
+    const dim3 grid((width + kOutW - 1) / kOutW, (height + a.rows - 1) / a.rows, (unsigned)n_images);
+    hipLaunchKernelGGL(k_ssim, grid, dim3(kBlock), 0, s, a);
+    parts = ssim_blocks(n_images, height, width);
+  }
+  hipLaunchKernelGGL(k_loss_finish, dim3(1), dim3(kBlock), 0, s, a.part, 2 * parts, w_ssim, loss);
   return hipGetLastError() == hipSuccess ? OCTGS_OK : OCTGS_EHIP;
 }
 

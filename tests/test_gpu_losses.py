@@ -69,12 +69,14 @@ def test_photometric_parity(P, LO, shape):
     assert np.abs(g - rg).max() <= 1e-3 * np.abs(rg).max()
 
 
-@pytest.mark.parametrize("hw", [(1, 1), (1, 235), (7, 236), (8, 237), (9, 472), (18, 473),
-                                (19, 11), (137, 3), (300, 709)])
+@pytest.mark.parametrize("hw", [(1, 235), (7, 236), (8, 237), (9, 472), (18, 473), (19, 11),
+                                (137, 3), (300, 709)])
 def test_photometric_strip_edges(P, LO, hw):
-    """Image sizes at the edges of the kernel's strips (236 columns; 8, 18, ...
-    rows) and windows larger than the image, at the bars of the parity test."""
-    for planes in (1, 90):  # short strips, and the longest that this size takes
+    """Image sizes at the edges of the strip kernel's blocks (236 columns; 8,
+    18, ... rows) and windows larger than the image, with as many planes as
+    take the call past the 1.6M elements that are done in tiles; one plane
+    takes the tiled passes.  Bars of the parity test."""
+    for planes in (1, 1600000 // (hw[0] * hw[1]) + 1):
         img, tgt = _images((planes,) + hw, 13 * hw[0] + hw[1])
         say("photometric strip edges", planes, hw)
         loss, g = _run(P, img, tgt, 0.8, 0.2)
