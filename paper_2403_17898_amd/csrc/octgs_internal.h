@@ -46,15 +46,24 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
 
 __device__ __forceinline__ uint64_t ballot(int pred) { return __ballot(pred); }
 
-// Inclusive prefix sum across the 64 lanes of a wave.
+// v plus the DPP-moved v of the rows in ROWMASK (lanes the move does not reach
+// add 0).
+template <int CTRL, int ROWMASK>
+__device__ __forceinline__ uint32_t dpp_add(uint32_t v) {
+  return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWMASK, 0xF, true);
+}
+
+// Inclusive prefix sum across the 64 lanes of a wave, by DPP alone: shifts by
+// 1, 2, 4 and 8 within each 16-lane row, then the last lane of rows 0 and 2
+// into rows 1 and 3, then lane 31 into rows 2 and 3 (shuffles through LDS cost
+// six dependent round trips).
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
-  int l = __lane_id();
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    uint32_t t = __shfl_up(v, o, 64);
-    if (l >= o) v += t;
-  }
-  return v;
+  v = dpp_add<0x111, 0xF>(v);
+  v = dpp_add<0x112, 0xF>(v);
+  v = dpp_add<0x114, 0xF>(v);
+  v = dpp_add<0x118, 0xF>(v);
+  v = dpp_add<0x142, 0xA>(v);
+  return dpp_add<0x143, 0xC>(v);
 }
 
 // Cross-lane moves without LDS: DPP within 16-lane rows, permlane swaps
@@ -211,35 +220,39 @@ struct BinGrid {
   int32_t band_rows;     // bin rows that one grouping pass covers (all, but for huge images)
 };
 
-constexpr int kGroupBins = 4;                     // bins that a slot hands itself to directly
-constexpr int kGroupCap = kChunk * kGroupBins;    // grouped entries of a block of kChunk slots
+constexpr int kSlots = 512;                       // Gaussian slots per projection block
+constexpr int kGroupCap = 4 * kSlots;             // grouped entries of a block of kSlots slots
+constexpr uint32_t kGroupBins = 16;               // bins that a survivor hands itself to directly
+constexpr uint32_t kGroupBinsFull = 4;            // ... where the block's would not fit kGroupCap
+constexpr uint32_t kTilesUnknown = ~0u;
 constexpr uint32_t kKeepBits = 64;                // rectangle tiles that a slot's keep mask holds
 constexpr int kMaxBandBins = 8192;                // bins of one grouping pass
 constexpr int kMaxTileCoord = 65535;              // tiles past this column or row list nothing
-constexpr int kBinThreads = 1024;
+constexpr int kBinThreads = 512;
 constexpr int kBinItems = 8;
 constexpr int kBinCap = kBinThreads * kBinItems;  // longest list that one block sorts at once
-constexpr int kScanTiles = 8;                     // tiles per thread of the tile scan
+constexpr int kScanThreads = 1024, kScanTiles = 8;  // tile scan: threads, tiles per thread
 constexpr int kPairRow = 10;                      // words per pair of gpair: 9 gradients, slot
 
 struct RasterWs {
   RasterHeader *hdr;
   uint64_t *vis_mask;     // [gcap / 64]
-  uint32_t *blk_vis;      // [nblk_g] survivors of each block of kChunk slots
+  uint32_t *blk_vis;      // [nblk_g] survivors of each block of kSlots slots
   uint32_t *blk_cand;     // [nblk_g] their rectangle tiles (saturated at kLbVal)
-  uint32_t *blk_large;    // [nblk_g] survivors listed in large_slot
+  uint32_t *blk_large;    // [nblk_g] survivors listed in large
   uint32_t *blk_pairs;    // [nblk_g] training: pair numbers of the block, then their prefix
   float4 *proj;           // [gcap][3]: (mx, my, A, B) (C, log2 opacity, r, g) (b, qa, qb, qc);
                           // A, B, C = conic scaled for exp2: -0.5 log2e ca, -log2e cb, -0.5 log2e cc;
                           // qa, qb, qc = the conic itself (tile test)
-  uint32_t *depth;        // [gcap] float bits of camera z
   ulonglong2 *rect;       // [gcap] x: packed u16 x0, y0, x1, y1; y: kept tiles of the rectangle,
                           // row-major, where it has at most kKeepBits (else unused)
   uint32_t *pair_base;    // [gcap] training: first pair number of the slot within its block's
+                          // (slot_block)
   uint16_t *group_off;    // [nblk_g][group_pitch] start of each bin's entries in the block's group
-  uint2 *group;           // [nblk_g][kGroupCap] (depth key, slot) grouped by bin
-  uint32_t *large_slot;   // [nblk_g][kChunk] survivors over more than kGroupBins bins or
-                          // kKeepBits tiles: every bin looks through these
+  uint4 *group;           // [nblk_g][kGroupCap] grouped by bin: depth key, slot, the bin's tiles
+                          // that it is listed in (kTilesUnknown: to be tested)
+  uint4 *large;           // [nblk_g][kSlots] survivors over more bins than that: rectangle (2
+                          // words), depth key, slot; every bin looks through these
   uint2 *bin_range;       // [bins] start and length of the bin's list
   uint32_t *bin_slot[2];  // [pcap] bin lists in depth order: slots ([1]: merged long lists)
   uint32_t *bin_mask[2];  // [pcap] and the bin's tiles that each is listed in
@@ -249,7 +262,6 @@ struct RasterWs {
   uint32_t *tkey;         // [pcap] tile of each listed pair, in list order (bin keys of long
                           // lists before)
   uint32_t *tval;         // [pcap] its slot
-  uint32_t *tpair;        // [pcap] training: its pair number (a Gaussian's are contiguous)
   uint32_t *ranges;       // [tiles][2]
   uint32_t *tile_order;   // [tile_grid_blocks] tile of each compositing block (~0u: none),
                           // written only with OCTGS_RASTER_TILE_ORDER
@@ -319,6 +331,24 @@ __device__ __forceinline__ uint32_t rect_tiles(const TileRect &r) {
   return (r.x1 - r.x0) * (r.y1 - r.y0);
 }
 
+// Blocks of slots in use by a view of n slots, and the block that projects a
+// slot: waves of 64 consecutive slots are dealt over the blocks in turn, since
+// neighbouring slots are of one octree level and their rectangles of one size.
+__host__ __device__ inline uint32_t slot_blocks(uint32_t n) { return (n + kSlots - 1) / kSlots; }
+__device__ __forceinline__ uint32_t slot_block(uint32_t slot, uint32_t nblk) {
+  return (slot / kWave) % nblk;
+}
+
+// First pair number of a slot's pairs, and of its tile (tx, ty): the tile's
+// rank among the kept tiles of the rectangle (row-major), or, where it has more
+// than kKeepBits tiles, its place among all of them.
+__device__ __forceinline__ uint32_t pair_rank(const TileRect &r, uint64_t keep, uint32_t tx,
+                                              uint32_t ty) {
+  const uint32_t loc = (ty - r.y0) * (r.x1 - r.x0) + (tx - r.x0);
+  return rect_tiles(r) > kKeepBits ? loc
+                                   : (uint32_t)__popcll(keep & ((1ull << (loc & 63u)) - 1ull));
+}
+
 // The part of a rectangle inside bin (bx, by), clipped.
 __device__ __forceinline__ TileRect clip_to_bin(const TileRect &r, const BinGrid &g, uint32_t bx,
                                                 uint32_t by) {
@@ -342,6 +372,14 @@ __device__ __forceinline__ uint32_t bin_tiles(const TileRect &r, uint64_t keep, 
   return bits;
 }
 
+// Barrier that orders LDS only: global loads and atomics stay in flight across
+// it (__syncthreads waits for them).
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // Exclusive scan of one value per thread over a block of NT threads; tmp:
 // NT / 64 words.  Ends with a barrier (tmp may be reused at once).
 template <int NT>
@@ -350,7 +388,7 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t *tmp, uint32
   const int w = threadIdx.x / kWave, l = __lane_id();
   const uint32_t inc = wave_incl_scan(v);
   if (l == kWave - 1) tmp[w] = inc;
-  __syncthreads();
+  lds_barrier();
   uint32_t off = 0, tot = 0;
 #pragma unroll
   for (int i = 0; i < kW; ++i) {
@@ -358,9 +396,47 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t *tmp, uint32
     if (i < w) off += s;
     tot += s;
   }
-  __syncthreads();
+  lds_barrier();
   *total = tot;
   return off + inc - v;
+}
+
+// Two exclusive scans over a block of NT threads at once.
+template <int NT>
+__device__ __forceinline__ void block_scan2(uint32_t &a, uint32_t &b, uint32_t *ta, uint32_t *tb,
+                                            uint32_t &total_a, uint32_t &total_b) {
+  const int w = threadIdx.x / kWave, l = __lane_id();
+  const uint32_t ia = wave_incl_scan(a), ib = wave_incl_scan(b);
+  if (l == kWave - 1) {
+    ta[w] = ia;
+    tb[w] = ib;
+  }
+  lds_barrier();
+  uint32_t oa = 0, ob = 0, sa = 0, sb = 0;
+#pragma unroll
+  for (int i = 0; i < NT / kWave; ++i) {
+    const uint32_t va = ta[i], vb = tb[i];
+    if (i < w) {
+      oa += va;
+      ob += vb;
+    }
+    sa += va;
+    sb += vb;
+  }
+  lds_barrier();
+  a = oa + ia - a;
+  b = ob + ib - b;
+  total_a = sa;
+  total_b = sb;
+}
+
+// Block number -> item so that each XCD's blocks (b % kXcds) take consecutive
+// items: neighbouring bins' data share cache lines.  Items are n; the grid is
+// xcd_blocks(n), and a block whose result is >= n has no item.
+__host__ __device__ inline uint32_t xcd_blocks(uint32_t n) { return (n + kXcds - 1) / kXcds * kXcds; }
+__device__ __forceinline__ uint32_t xcd_item(uint32_t b, uint32_t n) {
+  const uint32_t per = (n + kXcds - 1) / kXcds;
+  return b % kXcds * per + b / kXcds;
 }
 
 RasterWs raster_layout(void *base, int64_t gcap, int64_t pcap, int32_t W, int32_t H);

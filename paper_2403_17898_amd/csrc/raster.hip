@@ -23,7 +23,7 @@
 // radix-sorted by depth (4 passes), their pairs emitted in that order and
 // radix-sorted by tile (2 passes): eleven dependent kernels of 5 to 23 us,
 // 138 us together on a 1080p view of 270k slots and 862k pairs; these four
-// take 81 us.
+// take 66 us (25, 25, 6 and 10).
 //
 // Decisions (culls, rectangle, depth key, tile test) use the fixed FP32
 // operation sequences documented at project_decide and tile_meets_ellipse;
@@ -146,31 +146,38 @@ struct ProjArgs {
 };
 
 // Projection, tile tests and grouping by bin: one slot per thread, one block
-// per kChunk slots.
+// per kSlots slots.
 //   - culls, 2D covariance, conic, rectangle and depth key of each slot;
 //   - the tile test on every tile of the rectangles of at most kKeepBits
-//     tiles: a wave lays its slots' rectangles end to end and tests 64 tiles
-//     at a time, so a long rectangle does not keep 63 lanes waiting; the
-//     ballots are the slots' keep masks;
+//     tiles: the block lays its survivors' rectangles end to end and its
+//     threads take a tile each, so that neither a wave nor its lanes wait for
+//     a long rectangle; the ballots are the slots' keep masks;
 //   - each survivor is handed to the bins in which it keeps a tile: counted
 //     per bin in LDS, then written to the block's own stretch of ws.group,
 //     where the bins' entries are contiguous (ws.group_off).  A survivor over
-//     more than kGroupBins bins or kKeepBits tiles goes to the block's list
-//     of large ones instead, which every bin looks through.
+//     more than kGroupBins bins goes to the block's list of large ones
+//     instead, which every bin looks through.  (A block whose direct entries
+//     would not fit its stretch keeps those of up to kGroupBinsFull bins,
+//     which always fit.)
 // Nothing here depends on another block, so nothing has to be cleared before
 // and no global atomic is made: a bin later collects its entries from the
 // blocks' stretches (a column of ws.group_off).
-// Bound by latency at one wave of blocks (a 1080p view lists about 270 blocks
-// of slots): one slot per thread keeps 16 waves of a block in flight.
+// Waves of 64 consecutive slots are dealt over the blocks in turn
+// (slot_block): anchors lie in level order, and blocks of neighbours differed
+// tenfold in the tiles that they test.
+// Bound by latency and the tests' vector work: a 1080p view lists about 530
+// blocks, all resident at once (three blocks of 8 waves per compute unit).
 // Block 0 clears the header and the scan's look-back words for the later
 // kernels.
 template <bool TRAIN>
-__global__ __launch_bounds__(kChunk) void k_project(ProjArgs a) {
-  constexpr int kW = kChunk / kWave;
-  __shared__ float4 own[kW][kWave][2];
-  __shared__ uint32_t incs[kW][kWave];
-  __shared__ uint32_t hist[kMaxBandBins];
-  __shared__ uint32_t tmp[kW];
+__global__ __launch_bounds__(kSlots) void k_project(ProjArgs a) {
+  constexpr int kW = kSlots / kWave;
+  __shared__ float4 own[kSlots][2];
+  __shared__ unsigned long long keeps[kSlots];
+  __shared__ uint32_t start[kSlots + 1];
+  __shared__ uint8_t mark[kW][kWave];
+  extern __shared__ uint32_t hist[];  // the band's bins
+  __shared__ uint32_t tmp[kW], tmp2[kW];
   __shared__ uint32_t s_vis, s_large;
   __shared__ unsigned long long s_cand;
   const int t = threadIdx.x, w = t / kWave, l = __lane_id();
@@ -181,20 +188,21 @@ __global__ __launch_bounds__(kChunk) void k_project(ProjArgs a) {
   if (a.band_row0 == 0) {
     if (blockIdx.x == 0 && t < (int)(sizeof(RasterHeader) / 4))
       reinterpret_cast<uint32_t *>(ws.hdr)[t] = t == 0 ? n : 0u;  // n_slots is word 0
-    for (int64_t i = (int64_t)blockIdx.x * kChunk + t; i < ws.scan_blocks;
-         i += (int64_t)gridDim.x * kChunk)
+    for (int64_t i = (int64_t)blockIdx.x * kSlots + t; i < ws.scan_blocks;
+         i += (int64_t)gridDim.x * kSlots)
       ws.lb_scan[i] = 0u;
   }
-  const int64_t base = (int64_t)blockIdx.x * kChunk;
-  if (base >= n) return;
-  const int64_t s = base + t;
+  const uint32_t nblk = slot_blocks(n);
+  if (blockIdx.x >= nblk) return;
+  const uint32_t s = ((uint32_t)w * nblk + blockIdx.x) * (uint32_t)kWave + (uint32_t)l;
   float g[kGaussFields];
   {
-    const int64_t sc = min(s, (int64_t)n - 1);  // unconditional loads, all in flight together
+    const uint32_t sc = min(s, n - 1u);  // unconditional loads, all in flight together
 #pragma unroll
     for (int f = 0; f < kGaussFields; ++f) g[f] = a.g[f * a.gstride + sc];
   }
-  for (int i = t; i < nbins; i += kChunk) hist[i] = 0u;
+  for (int i = t; i < nbins; i += kSlots) hist[i] = 0u;
+  mark[w][l] = 0;
   if (t == 0) {
     s_vis = 0u;
     s_large = 0u;
@@ -208,11 +216,10 @@ __global__ __launch_bounds__(kChunk) void k_project(ProjArgs a) {
                                   min(a.tiles_y, kMaxTileCoord), g, o);
   TileRect r = {0u, 0u, 0u, 0u};
   if (vis) {
-    float4 *p = ws.proj + 3 * s;
+    float4 *p = ws.proj + 3 * (size_t)s;
     p[0] = make_float4(o.mx, o.my, -0.5f * kLog2e * o.ca, -kLog2e * o.cb);
     p[1] = make_float4(-0.5f * kLog2e * o.cc, log2f(g[10]), g[11], g[12]);
     p[2] = make_float4(g[13], o.ca, o.cb, o.cc);
-    ws.depth[s] = __float_as_uint(o.zc);
     r = TileRect{(uint32_t)o.x0, (uint32_t)o.y0, (uint32_t)o.x1, (uint32_t)o.y1};
   }
   if (a.gauss_w && s < n) a.gauss_w[s] = 0.0f;
@@ -220,102 +227,133 @@ __global__ __launch_bounds__(kChunk) void k_project(ProjArgs a) {
   const bool flat = vis && tiles <= kKeepBits;
   const uint64_t vm = ballot(vis);
   if (l == 0 && s < n) ws.vis_mask[s >> 6] = vm;
+  const uint32_t csum = wave_sum(tiles);  // an image has at most 2^24 tiles
 
-  // the wave's rectangles of at most kKeepBits tiles, end to end
+  // the block's rectangles of at most kKeepBits tiles, end to end
   uint64_t keep = 0;
   {
-    const uint32_t cnt = flat ? tiles : 0u;
-    const uint32_t inc = wave_incl_scan(cnt), ex = inc - cnt;
-    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
-    incs[w][l] = inc;
+    uint32_t ci = flat ? 1u : 0u, ex = flat ? tiles : 0u, nflat, total;
+    block_scan2<kSlots>(ci, ex, tmp, tmp2, nflat, total);
     if (flat) {
-      own[w][l][0] = make_float4(o.mx, o.my, o.ca, o.cb);
-      own[w][l][1] = make_float4(o.cc, __uint_as_float(r.x0 | (r.y0 << 16)),
-                                 __uint_as_float(r.x1 - r.x0), __uint_as_float(ex));
+      start[ci] = ex;
+      keeps[ci] = 0ull;
+      own[ci][0] = make_float4(o.mx, o.my, o.ca, o.cb);
+      own[ci][1] = make_float4(o.cc, __uint_as_float(r.x0 | (r.y0 << 16)),
+                               __uint_as_float(r.x1 - r.x0), __uint_as_float(tiles));
     }
-    // the wave's LDS writes are complete before any lane reads them
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    for (uint32_t b0 = 0; b0 < total; b0 += kWave) {
-      const uint32_t q = min(b0 + (uint32_t)l, total - 1u);
-      // owner: the first lane whose inclusive count exceeds q
-      uint32_t lo = 0;
-#pragma unroll
-      for (int st = kWave / 2; st > 0; st >>= 1)
-        if (incs[w][lo + st - 1] <= q) lo += st;
-      const float4 u = own[w][lo][0], v = own[w][lo][1];
+    if (t == 0) start[nflat] = total;
+    lds_barrier();
+    // each wave takes consecutive stretches of 64 tiles
+    const uint32_t per = ((total + kWave - 1) / kWave + kW - 1) / kW * kWave;
+    const uint32_t q0 = min((uint32_t)w * per, total), q1 = min(q0 + per, total);
+    uint32_t of = 0;  // owner of the stretch's first tile: the last that starts at or before it
+    for (uint32_t st = kSlots / 2; st > 0; st >>= 1)
+      if (of + st < nflat && start[of + st] <= q0) of += st;
+    for (uint32_t b0 = q0; b0 < q1; b0 += kWave) {
+      // rectangles that start in the stretch mark their first tile
+      const uint32_t p = start[min(of + (uint32_t)l, nflat)] - b0;
+      if (l > 0 && p < (uint32_t)kWave) mark[w][p] = 1;
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      const uint64_t sm = ballot(mark[w][l] != 0);
+      __builtin_amdgcn_wave_barrier();
+      mark[w][l] = 0;
+      const bool in = b0 + (uint32_t)l < q1;
+      const uint32_t lo = min(of + (uint32_t)__popcll(sm & (lanemask_lt() | (1ull << l))), nflat - 1u);
+      of += (uint32_t)__popcll(sm);
+      const float4 u = own[lo][0], v = own[lo][1];
       const uint32_t xy = __float_as_uint(v.y), wd = __float_as_uint(v.z);
-      const uint32_t loc = q - __float_as_uint(v.w);
+      const uint32_t loc = min(b0 + (uint32_t)l, total - 1u) - start[lo];
       // row and column of the tile: a float quotient, exact after one
       // correction step (loc < 64)
       uint32_t row = (uint32_t)((float)loc * __builtin_amdgcn_rcpf((float)wd));
       const int32_t rem = (int32_t)(loc - row * wd);
       row = rem < 0 ? row - 1 : (rem >= (int32_t)wd ? row + 1 : row);
-      const bool hit = b0 + (uint32_t)l < total &&
-                       tile_meets_ellipse(u.x, u.y, u.z, u.w, v.x, (xy & 0xffffu) + (loc - row * wd),
-                                          (xy >> 16) + row, ws.xmax, ws.ymax);
+      const bool hit = in && tile_meets_ellipse(u.x, u.y, u.z, u.w, v.x,
+                                                (xy & 0xffffu) + (loc - row * wd),
+                                                (xy >> 16) + row, ws.xmax, ws.ymax);
       const uint64_t m = ballot(hit);
-      const int32_t d = (int32_t)(ex - b0);  // where this lane's tiles start in the ballot
-      if (cnt > 0 && d < kWave && d + (int32_t)cnt > 0) keep |= d >= 0 ? m >> d : m << -d;
-    }
-    if (cnt < kKeepBits) keep &= (1ull << cnt) - 1ull;
-  }
-  if (vis)
-    ws.rect[s] = make_ulonglong2(pack_rect(o.x0, o.y0, o.x1, o.y1), keep);
-  __syncthreads();  // hist is clear
-
-  // bins of this band that the survivor meets
-  const uint32_t bx0 = r.x0 >> bg.sx, by0 = r.y0 >> bg.sy;
-  const uint32_t nbx = vis ? ((r.x1 - 1u) >> bg.sx) - bx0 + 1u : 0u;
-  const uint32_t nby = vis ? ((r.y1 - 1u) >> bg.sy) - by0 + 1u : 0u;
-  const bool small = flat && nbx * nby <= (uint32_t)kGroupBins;
-  uint32_t slot_in[kGroupBins], bin_of[kGroupBins];
-#pragma unroll
-  for (int j = 0; j < kGroupBins; ++j) {
-    slot_in[j] = ~0u;
-    bin_of[j] = 0u;
-    if (small && (uint32_t)j < nbx * nby) {
-      // nbx is 1, 2, 3 or 4 here
-      const uint32_t jy = nbx == 1 ? j : (nbx == 2 ? j >> 1 : 0), jx = (uint32_t)j - jy * nbx;
-      const uint32_t bx = bx0 + jx, by = by0 + jy;
-      if (by >= (uint32_t)a.band_row0 && by < (uint32_t)(a.band_row0 + a.band_rows) &&
-          bin_tiles(r, keep, bg, bx, by)) {
-        bin_of[j] = (by - (uint32_t)a.band_row0) * (uint32_t)bg.gx + bx;
-        slot_in[j] = atomicAdd(&hist[bin_of[j]], 1u);
+      // the owner's first lane in the wave adds its stretch of the ballot
+      if (in && (l == 0 || loc == 0)) {
+        const uint32_t len = min(__float_as_uint(v.w) - loc, (uint32_t)(kWave - l));
+        const uint64_t bits = (m >> l) & (len < 64u ? (1ull << len) - 1ull : ~0ull);
+        if (bits) atomicOr(&keeps[lo], (unsigned long long)(bits << loc));
       }
     }
+    lds_barrier();
+    if (flat) keep = keeps[ci];
+  }
+  if (vis) ws.rect[s] = make_ulonglong2(pack_rect(o.x0, o.y0, o.x1, o.y1), keep);
+
+  // bins of this band that the survivor meets
+  const uint32_t row0 = (uint32_t)a.band_row0, row1 = row0 + (uint32_t)a.band_rows;
+  const uint32_t bx0 = r.x0 >> bg.sx, nbx = vis ? ((r.x1 - 1u) >> bg.sx) - bx0 + 1u : 0u;
+  const uint32_t by0 = r.y0 >> bg.sy, nby = vis ? ((r.y1 - 1u) >> bg.sy) - by0 + 1u : 0u;
+  const uint32_t nb = nbx * nby;
+  uint32_t direct, pn = TRAIN ? (flat ? (uint32_t)__popcll(keep) : tiles) : 0u, pairs;
+  uint32_t want = nb <= kGroupBins ? nb : 0u;
+  block_scan2<kSlots>(want, pn, tmp, tmp2, direct, pairs);
+  const uint32_t most = direct <= (uint32_t)kGroupCap ? kGroupBins : kGroupBinsFull;
+  const bool small = vis && nb <= most;
+  if (TRAIN) {
+    if (vis) ws.pair_base[s] = pn;
+    if (t == 0) ws.blk_pairs[blockIdx.x] = pairs;
+  }
+  // place among the bin's entries and tiles there, for up to kInReg bins; more
+  // are rare and worked out twice
+  constexpr int kInReg = 4;
+  uint32_t at[kInReg], bits[kInReg], bin[kInReg];
+  uint32_t meets = 0;  // more bins: bit j, the j-th of the rectangle (row-major) gets it
+  const bool few = small && nb <= (uint32_t)kInReg;
+  // (the tests' staging is done with)
+  uint16_t (*placed)[kGroupBins] = reinterpret_cast<uint16_t (*)[kGroupBins]>(own);
+  static_assert(sizeof(own) >= kSlots * kGroupBins * 2, "places fit the staging");
+#pragma unroll
+  for (int j = 0; j < kInReg; ++j) {
+    at[j] = bits[j] = bin[j] = 0u;
+    if (few && (uint32_t)j < nb) {
+      const uint32_t jy = nbx == 1 ? j : (nbx == 2 ? j >> 1 : 0);  // nbx <= 4 here
+      const uint32_t x = bx0 + (uint32_t)j - jy * nbx, y = by0 + jy;
+      if (y >= row0 && y < row1) bits[j] = flat ? bin_tiles(r, keep, bg, x, y) : kTilesUnknown;
+      if (bits[j]) {
+        bin[j] = (y - row0) * (uint32_t)bg.gx + x;
+        at[j] = atomicAdd(&hist[bin[j]], 1u);
+      }
+    }
+  }
+  if (small && !few) {
+    uint32_t j = 0;
+    for (uint32_t y = by0; y < by0 + nby; ++y)
+      for (uint32_t x = bx0; x < bx0 + nbx; ++x, ++j)
+        if (y >= row0 && y < row1 && (!flat || bin_tiles(r, keep, bg, x, y))) {
+          meets |= 1u << j;
+          placed[t][j] = (uint16_t)atomicAdd(&hist[(y - row0) * (uint32_t)bg.gx + x], 1u);
+        }
   }
   const uint64_t lm = ballot(vis && !small);
   uint32_t lbase = 0;
   if (l == 0) {
     if (lm) lbase = atomicAdd(&s_large, (uint32_t)__popcll(lm));
     if (vm) atomicAdd(&s_vis, (uint32_t)__popcll(vm));
+    if (csum) atomicAdd(&s_cand, (unsigned long long)csum);
   }
   lbase = (uint32_t)__builtin_amdgcn_readfirstlane((int)lbase);
-  if (vis && !small)
-    ws.large_slot[base + lbase + (uint32_t)__popcll(lm & lanemask_lt())] = (uint32_t)s;
-  uint64_t cand = tiles;
-#pragma unroll
-  for (int q = 32; q > 0; q >>= 1) cand += __shfl_xor(cand, q, kWave);
-  if (l == 0) atomicAdd(&s_cand, (unsigned long long)cand);
-  if (TRAIN) {
-    const uint32_t np = flat ? (uint32_t)__popcll(keep) : tiles;
-    uint32_t tot;
-    const uint32_t ex = block_scan<kChunk>(np, tmp, &tot);
-    if (vis) ws.pair_base[s] = ex;
-    if (t == 0) ws.blk_pairs[blockIdx.x] = tot;
+  if (vis && !small) {
+    const uint64_t rc = pack_rect(o.x0, o.y0, o.x1, o.y1);
+    ws.large[(size_t)blockIdx.x * kSlots + lbase + (uint32_t)__popcll(lm & lanemask_lt())] =
+        make_uint4((uint32_t)rc, (uint32_t)(rc >> 32), __float_as_uint(o.zc), s);
   }
-  __syncthreads();
+  lds_barrier();
 
   // starts of the bins' entries in the block's stretch
   {
-    const int per = (nbins + kChunk - 1) / kChunk;  // consecutive bins per thread, at most 8
+    const int per = (nbins + kSlots - 1) / kSlots;  // consecutive bins per thread
     const int i0 = min(t * per, nbins), i1 = min(i0 + per, nbins);
     uint32_t sum = 0;
     for (int i = i0; i < i1; ++i) sum += hist[i];
     uint32_t tot;
-    uint32_t run = block_scan<kChunk>(sum, tmp, &tot);
+    uint32_t run = block_scan<kSlots>(sum, tmp, &tot);
     uint16_t *row = ws.group_off + (size_t)blockIdx.x * ws.group_pitch;
     for (int i = i0; i < i1; ++i) {
       const uint32_t c = hist[i];
@@ -325,12 +363,20 @@ __global__ __launch_bounds__(kChunk) void k_project(ProjArgs a) {
     }
     if (t == 0) row[nbins] = (uint16_t)tot;
   }
-  __syncthreads();
-  uint2 *grp = ws.group + (size_t)blockIdx.x * kGroupCap;
+  lds_barrier();
+  uint4 *grp = ws.group + (size_t)blockIdx.x * kGroupCap;
+  const uint32_t key = __float_as_uint(o.zc);
 #pragma unroll
-  for (int j = 0; j < kGroupBins; ++j)
-    if (slot_in[j] != ~0u)
-      grp[hist[bin_of[j]] + slot_in[j]] = make_uint2(__float_as_uint(o.zc), (uint32_t)s);
+  for (int j = 0; j < kInReg; ++j)
+    if (bits[j]) grp[hist[bin[j]] + at[j]] = make_uint4(key, s, bits[j], 0u);
+  if (meets) {
+    uint32_t j = 0;
+    for (uint32_t y = by0; y < by0 + nby; ++y)
+      for (uint32_t x = bx0; x < bx0 + nbx; ++x, ++j)
+        if ((meets >> j) & 1u)
+          grp[hist[(y - row0) * (uint32_t)bg.gx + x] + placed[t][j]] =
+              make_uint4(key, s, flat ? bin_tiles(r, keep, bg, x, y) : kTilesUnknown, 0u);
+  }
   if (t == 0) {
     ws.blk_vis[blockIdx.x] = s_vis;
     ws.blk_large[blockIdx.x] = s_large;
@@ -564,34 +610,32 @@ RasterWs raster_layout(void *base, int64_t gcap, int64_t pcap, int32_t W, int32_
   ws.ymax = (float)H - 0.5f;
   ws.tiles_x = (W + kTile - 1) / kTile;
   ws.tiles_y = (H + kTile - 1) / kTile;
-  ws.nblk_g = (int)((g + kChunk - 1) / kChunk);
+  ws.nblk_g = (int)((g + kSlots - 1) / kSlots);
   ws.bins = bin_grid(ws.tiles_x, ws.tiles_y);
   const int64_t ntiles = (int64_t)ws.tiles_x * ws.tiles_y;
   const int64_t nbins = (int64_t)ws.bins.nx * ws.bins.ny;
   ws.group_pitch = (int)((std::min<int64_t>(nbins, (int64_t)ws.bins.band_rows * ws.bins.gx) + 2) & ~1);
-  ws.scan_blocks = (int)((ntiles + kScanTiles * kBinThreads - 1) / (kScanTiles * kBinThreads));
+  ws.scan_blocks = (int)((ntiles + kScanTiles * kScanThreads - 1) / (kScanTiles * kScanThreads));
   ws.hdr = (RasterHeader *)take(sizeof(RasterHeader));
-  ws.vis_mask = (uint64_t *)take((size_t)ws.nblk_g * kGroups * 8);
+  ws.vis_mask = (uint64_t *)take((size_t)ws.nblk_g * (kSlots / kWave) * 8);
   ws.blk_vis = (uint32_t *)take((size_t)ws.nblk_g * 4);
   ws.blk_cand = (uint32_t *)take((size_t)ws.nblk_g * 4);
   ws.blk_large = (uint32_t *)take((size_t)ws.nblk_g * 4);
   ws.blk_pairs = (uint32_t *)take((size_t)ws.nblk_g * 4);
   ws.proj = (float4 *)take((size_t)kProjVec * g * 16);
-  ws.depth = (uint32_t *)take((size_t)g * 4);
   ws.rect = (ulonglong2 *)take((size_t)g * 16);
   ws.pair_base = (uint32_t *)take((size_t)g * 4);
   ws.group_off = (uint16_t *)take((size_t)ws.nblk_g * ws.group_pitch * 2);
-  ws.group = (uint2 *)take((size_t)ws.nblk_g * kGroupCap * 8);
-  ws.large_slot = (uint32_t *)take((size_t)ws.nblk_g * kChunk * 4);
+  ws.group = (uint4 *)take((size_t)ws.nblk_g * kGroupCap * 16);
+  ws.large = (uint4 *)take((size_t)ws.nblk_g * kSlots * 16);
   ws.bin_range = (uint2 *)take((size_t)nbins * 8);
   for (int i = 0; i < 2; ++i) ws.bin_slot[i] = (uint32_t *)take((size_t)pc * 4);
   for (int i = 0; i < 2; ++i) ws.bin_mask[i] = (uint32_t *)take((size_t)pc * 4);
   ws.over_bin = (uint32_t *)take((size_t)(pc / kBinCap + 1) * 4);
-  ws.tile_count = (uint32_t *)take((size_t)ws.scan_blocks * kScanTiles * kBinThreads * 4);
+  ws.tile_count = (uint32_t *)take((size_t)ws.scan_blocks * kScanTiles * kScanThreads * 4);
   ws.lb_scan = (uint32_t *)take((size_t)ws.scan_blocks * 4);
   ws.tkey = (uint32_t *)take((size_t)pc * 4);
   ws.tval = (uint32_t *)take((size_t)pc * 4);
-  ws.tpair = (uint32_t *)take((size_t)pc * 4);
   ws.ranges = (uint32_t *)take((size_t)ntiles * 8);
   ws.tile_order = (uint32_t *)take((size_t)tile_grid_blocks(ws.tiles_x, ws.tiles_y) * 4);
   ws.dproj = (float *)take((size_t)g * 9 * 4);
@@ -658,10 +702,11 @@ int octgs_rasterize_fwd(const octgs_gaussians *g, const octgs_camera *cam,
   for (int row0 = 0; row0 < ws.bins.ny && e == hipSuccess; row0 += ws.bins.band_rows) {
     pa.band_row0 = row0;
     pa.band_rows = std::min(ws.bins.band_rows, ws.bins.ny - row0);
+    const size_t lds = (size_t)pa.band_rows * ws.bins.gx * sizeof(uint32_t);
     if (train)
-      hipLaunchKernelGGL(k_project<true>, dim3(ws.nblk_g), dim3(kChunk), 0, s, pa);
+      hipLaunchKernelGGL(k_project<true>, dim3(ws.nblk_g), dim3(kSlots), lds, s, pa);
     else
-      hipLaunchKernelGGL(k_project<false>, dim3(ws.nblk_g), dim3(kChunk), 0, s, pa);
+      hipLaunchKernelGGL(k_project<false>, dim3(ws.nblk_g), dim3(kSlots), lds, s, pa);
     if (row0 == 0) {
       mark(1);
       mark(2);

@@ -74,6 +74,14 @@ struct BwdLds {
   float sG[9][kBwdBatch];
 };
 
+// Number of the pair (slot, tile): a slot's numbers are contiguous.
+__device__ __forceinline__ uint32_t pair_number(const RasterWs &ws, uint32_t slot, uint32_t nblk,
+                                                uint32_t tx, uint32_t ty) {
+  const ulonglong2 rm = ws.rect[slot];
+  return ws.blk_pairs[slot_block(slot, nblk)] + ws.pair_base[slot] +
+         pair_rank(unpack_rect(rm.x), rm.y, tx, ty);
+}
+
 // One pair's row: nine gradients and the slot (rows are 8-byte aligned).
 __device__ __forceinline__ void store_pair(const RasterWs &ws, uint32_t pair, uint32_t slot,
                                            const float (&g)[9]) {
@@ -85,10 +93,13 @@ __device__ __forceinline__ void store_pair(const RasterWs &ws, uint32_t pair, ui
 }
 
 // Per-pair gradients of list entries [e0, e1) that no pixel consumed are 0.
-__device__ __forceinline__ void zero_pairs(const RasterWs &ws, uint32_t e0, uint32_t e1) {
+__device__ __forceinline__ void zero_pairs(const RasterWs &ws, uint32_t nblk, uint32_t tx,
+                                           uint32_t ty, uint32_t e0, uint32_t e1) {
   const float zero[9] = {};
-  for (uint32_t e = e0 + threadIdx.x; e < e1; e += blockDim.x)
-    store_pair(ws, ws.tpair[e], ws.tval[e], zero);
+  for (uint32_t e = e0 + threadIdx.x; e < e1; e += blockDim.x) {
+    const uint32_t s = ws.tval[e];
+    store_pair(ws, pair_number(ws, s, nblk, tx, ty), s, zero);
+  }
 }
 
 // The LDS lives in the kernel and is passed in, so the two AMIN
@@ -109,8 +120,8 @@ __device__ __forceinline__ void composite_bwd_tile(const BwdArgs &a, BwdLds &lds
   const int px = tx * kTile + (t % kTile), py0 = ty * kTile + kBPx * (t / kTile);
   const float fx = (float)px + 0.5f, fy = (float)py0 + 0.5f;
   const uint32_t start = a.ws.ranges[2 * tile], end = a.ws.ranges[2 * tile + 1];
-  const uint32_t *vals = a.ws.tval;   // slot of each sorted pair
-  const uint32_t *pidx = a.ws.tpair;  // its pair number
+  const uint32_t *vals = a.ws.tval;  // slot of each sorted pair
+  const uint32_t nblk = slot_blocks(a.ws.hdr->n_slots);
   const float4 *proj = a.ws.proj;
   const size_t plane = (size_t)a.W * a.H;
   // per pixel: T, dL/dC, S = dL/dC . (colour behind) (starts as T_final
@@ -137,7 +148,7 @@ __device__ __forceinline__ void composite_bwd_tile(const BwdArgs &a, BwdLds &lds
   for (int o = 32; o > 0; o >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, o, kWave));
   const uint32_t n_used = min(mx, end - start);
   const float amax = a.alpha_max, amin = a.alpha_min;
-  zero_pairs(a.ws, start + n_used, end);
+  zero_pairs(a.ws, nblk, (uint32_t)tx, (uint32_t)ty, start + n_used, end);
   if (n_used == 0) return;
   for (int32_t b0 = (int32_t)((n_used - 1) / kBwdBatch) * kBwdBatch; b0 >= 0; b0 -= kBwdBatch) {
     const int nb = (int)min((uint32_t)kBwdBatch, n_used - (uint32_t)b0);
@@ -147,7 +158,7 @@ __device__ __forceinline__ void composite_bwd_tile(const BwdArgs &a, BwdLds &lds
       const int i = t + q * kBwdThreads;
       const uint32_t e = start + (uint32_t)b0 + (uint32_t)min(i, nb - 1);
       const uint32_t s = vals[e];
-      s_pair[i] = pidx[e];
+      s_pair[i] = pair_number(a.ws, s, nblk, (uint32_t)tx, (uint32_t)ty);
       lds.s_slot[i] = s;
       sA[i] = proj[3 * (size_t)s];
       const float4 bv = proj[3 * (size_t)s + 1];

@@ -94,11 +94,11 @@ def test_bin_shapes(P, orc, W, H, n, scale):
         assert (tiles <= 64).sum() > 100 and (tiles > 64).sum() > 20
 
 
-@pytest.mark.parametrize("n,depths", [(1024, 0), (1025, 0), (4097, 0), (8192, 0), (8193, 0),
-                                      (20000, 0), (3000, 1), (3000, 40), (9000, 7), (17000, 3)])
+@pytest.mark.parametrize("n,depths", [(512, 0), (513, 0), (1025, 0), (2049, 0), (4096, 0),
+                                      (4097, 0), (20000, 0), (3000, 1), (3000, 40), (9000, 7), (17000, 3)])
 def test_long_lists_and_ties(P, orc, n, depths):
     """Every Gaussian covers all six tiles of a 48 x 32 image, so each bin's
-    list has n entries: up to the block's 8,192, one more, and three merged
+    list has n entries: up to the block's 4,096, one more, and five merged
     runs; with `depths` only that many distinct depths (ties by slot)."""
     cam = S.look_at((0.0, -8.0, 0.0), (0.0, 0.0, 0.0), 48, 32, 60.0)
     gf = S.random_gaussians(n, cam, n + depths, depth=(3.0, 6.0), scale=(1.5, 3.0), margin=0.0,
