@@ -30,6 +30,8 @@
 // continuous values are FP32.
 #include "octgs_internal.h"
 
+#include <type_traits>
+
 namespace octgs {
 
 namespace {
@@ -397,32 +399,75 @@ struct CompArgs {
 
 // One 16x16 tile per block of one wave (64 threads); each thread owns four
 // vertically adjacent pixels of one column, so the Gaussian's column terms
-// are shared four ways.  Batches of kFwdBatch list entries are staged in LDS
-// as three float4 per Gaussian.  Per entry the exponent of the first pixel
-// is evaluated directly and the next three by finite differences of the
-// quadratic in dy (exact in real arithmetic; in FP32 within a few ulps of
-// |p|):
+// are shared four ways.  Batches of kFwdBatch list entries are staged in LDS.
+// Per entry the exponent of the first pixel is evaluated directly and the next
+// three by finite differences of the quadratic in dy (exact in real
+// arithmetic; in FP32 within a few ulps of |p|):
 //   dx = x - mx; dy = y0 - my
 //   p0 = fma(C' dy, dy, fma(B' dx, dy, fma(A' dx, dx, log2 op)))
 //   d0 = p(dy + 1) - p(dy) = fma(C', 2 dy + 1, B' dx);  d(k+1) = d(k) + 2 C'
 //   p(k+1) = p(k) + d(k)
 //   a = min(alpha_max, exp2(p)) = min(alpha_max, op G')
-// The loop is branch-free (lanes that are done blend alpha 0), so the wave
-// only branches on wave-uniform conditions; the tile stops when all of its
-// pixels have.
-constexpr int kFwdThreads = 64;   // forward composite: one wave per tile, 4 pixels per thread
-constexpr int kFwdBatch = 128;    // list entries staged in LDS per batch
-constexpr int kPx = 4;
+// A pixel is done once T < t_min: from then on it blends nothing.  T of a done
+// pixel is kept aside and replaced by -0: w = a |T| is then +0, which leaves
+// the colour and T = -0 as they are, and as an integer -0 is no smaller than
+// t_min.  Entries go in groups of kGroup: the weights of all of them are
+// worked out as if no pixel got done in the group; as T only falls, one
+// integer minimum over the thread's pixels at the group's end and one compare
+// tell if that holds, and if not (or if alpha_max lets T go negative) the
+// group's T are walked again and the weights past t_min cleared.  So an entry
+// costs no select and no compare of its own, and the alphas of a group do not
+// wait for each other.  min(alpha_max, .) is left out for groups of entries
+// whose exponent cannot reach log2(alpha_max) in this tile (may_clamp).
+// Bound by vector issue (about 40 instructions per entry of four pixels a
+// lane; 54 with the selects).  3840 x 2160, 2.3M pairs: 215 -> 190 us; 1920 x
+// 1080, 0.86M: 97 -> 87; a training view of 1600 x 1066, 0.67M: 77 -> 66.
+// Groups of 2, 4, 8 and 16 take 100, 92, 87 and 93 us at 1920 x 1080.  Five
+// waves per SIMD (96 registers) suffice; six or eight spill.
+constexpr int kFwdThreads = 64;
+constexpr int kFwdBatch = 64;     // list entries staged in LDS per batch, one per lane
+constexpr int kPx = 4;            // pixels of a column
+constexpr int kGroup = 8;         // entries per check for done pixels
 
 template <bool LOG>
 struct CompLds {
-  float4 sA[kFwdBatch], sB[kFwdBatch], sC[kFwdBatch];
+  float4 sA[kFwdBatch], sB[kFwdBatch], sC[kFwdBatch];  // (mx, my, A', B') (C', log2 op, 2 C', -) (r, g, b, -)
   uint32_t s_slot[LOG ? kFwdBatch : 1];
   float s_w[LOG ? kFwdBatch : 1];
 };
 
-// The LDS lives in the kernel and is passed in, so the two AMIN
-// instantiations share one allocation.
+// The conditions of the earlier stages are final in the composite: one thread
+// adds them to the caller's status word.
+__device__ __forceinline__ void add_status(const CompArgs &a) {
+  if (a.status && blockIdx.x == 0 && threadIdx.x == 0) {
+    const uint32_t f = (a.ws.hdr->pair_overflow ? OCTGS_STATUS_PAIR_OVERFLOW : 0u) |
+                       (a.ws.hdr->sync_error ? OCTGS_STATUS_SYNC_ERROR : 0u);
+    if (f) atomicOr(a.status, f);
+  }
+}
+
+// T as an integer below this may have crossed t_min; 0 <= T <= 1 unless
+// alpha_max > 1.
+__device__ __forceinline__ uint32_t t_bits(const CompArgs &a) {
+  return !(a.alpha_max <= 1.0f) ? ~0u : (a.t_min > 0.0f ? __float_as_uint(a.t_min) : 0u);
+}
+
+// May the computed exponent of the entry exceed log2(alpha_max) at a pixel of
+// the tile whose first pixel centre is (X0, Y0)?  Exactly p <= log2 op, since
+// the quadratic is nowhere positive.  The conic's, the products' and the
+// differences' rounding errors add up to less than 64 x 2^-24 times the sum of
+// the terms' magnitudes over the tile (|dx|, |dy| reach at least 7.5, so the
+// terms of d are smaller than those of p); exp2 and log2 are within 2^-16.
+// Not-a-number and infinite terms count as "may".
+__device__ __forceinline__ bool may_clamp(float lamax, const float4 &A, const float4 &B, float X0,
+                                          float Y0) {
+  const float DX = fabsf(A.x - (X0 + 7.5f)) + 7.5f, DY = fabsf(A.y - (Y0 + 7.5f)) + 7.5f;
+  const float M = fabsf(A.z) * DX * DX + fabsf(A.w) * DX * DY + fabsf(B.x) * DY * DY + fabsf(B.y);
+  return !(B.y + 0x1p-18f * M + 0x1p-16f < lamax);
+}
+
+// The LDS lives in the kernel and is passed in, so the instantiations share
+// one allocation.
 template <bool LOG, bool AMIN, bool LAST>
 __device__ __forceinline__ void composite_tile(const CompArgs &a, CompLds<LOG> &lds) {
   float4 *sA = lds.sA, *sB = lds.sB, *sC = lds.sC;
@@ -434,128 +479,336 @@ __device__ __forceinline__ void composite_tile(const CompArgs &a, CompLds<LOG> &
   const int tx = tile % a.ws.tiles_x, ty = tile / a.ws.tiles_x;
   const int t = threadIdx.x;
   const int px = tx * kTile + (t % kTile), py0 = ty * kTile + kPx * (t / kTile);
-  bool in[kPx];
-#pragma unroll
-  for (int k = 0; k < kPx; ++k) in[k] = px < a.W && py0 + k < a.H;
   const float fx = (float)px + 0.5f, fy = (float)py0 + 0.5f;
   const uint32_t start = __builtin_amdgcn_readfirstlane(a.ws.ranges[2 * tile]);
   const uint32_t end = __builtin_amdgcn_readfirstlane(a.ws.ranges[2 * tile + 1]);
   const uint32_t *vals = a.ws.tval;
   const float4 *proj = a.ws.proj;
   const float amax = a.alpha_max, amin = a.alpha_min, tmin = a.t_min;
-  float T[kPx], cr[kPx], cg[kPx], cb[kPx];
+  const uint32_t tbits = t_bits(a);
+  const float lamax = log2f(amax);
+  float T[kPx], Tdone[kPx], cr[kPx], cg[kPx], cb[kPx];
   uint32_t last[kPx];
-  bool done[kPx];
+  uint32_t done = 0;  // bit k: pixel k
 #pragma unroll
   for (int k = 0; k < kPx; ++k) {
-    T[k] = in[k] ? 1.0f : 0.0f;
+    const bool in = px < a.W && py0 + k < a.H;
+    T[k] = in ? 1.0f : -0.0f;
+    done |= in ? 0u : 1u << k;
+    Tdone[k] = 0.0f;
     cr[k] = 0.0f; cg[k] = 0.0f; cb[k] = 0.0f;
     last[k] = end - start;
-    done[k] = !in[k];
   }
+  const uint32_t outside = done;
+  constexpr uint32_t kAll = (1u << kPx) - 1u;
   for (uint32_t b0 = start; b0 < end; b0 += kFwdBatch) {
     // one wave: the barrier only orders LDS reuse across batches
     __syncthreads();
-#pragma unroll
-    for (int q = 0; q < kFwdBatch / kFwdThreads; ++q) {
-      const int i = t + q * kFwdThreads;
-      const uint32_t e = min(b0 + i, end - 1u);
-      const uint32_t s = vals[e];
-      if (LOG) s_slot[i] = s;
-      sA[i] = proj[3 * (size_t)s];
-      sB[i] = proj[3 * (size_t)s + 1];
-      sC[i] = proj[3 * (size_t)s + 2];
+    uint64_t clamp;  // bit j: entry j may need min(alpha_max, .)
+    {
+      const uint32_t s = vals[min(b0 + t, end - 1u)];
+      if (LOG) s_slot[t] = s;
+      const float4 A = proj[3 * (size_t)s], B = proj[3 * (size_t)s + 1];
+      sA[t] = A;
+      sB[t] = make_float4(B.x, B.y, B.x + B.x, 0.0f);
+      sC[t] = make_float4(B.z, B.w, proj[3 * (size_t)s + 2].x, 0.0f);
+      clamp = ballot(may_clamp(lamax, A, B, (float)(tx * kTile) + 0.5f, (float)(ty * kTile) + 0.5f));
     }
     __syncthreads();
     const int nb = __builtin_amdgcn_readfirstlane((int)min((uint32_t)kFwdBatch, end - b0));
     const uint32_t base = b0 - start + 1u;
-    auto step = [&](int j) {
-      const float4 A = sA[j];
-      const float4 B = sB[j];
-      const float cbl = sC[j].x;
-      const float dx = fx - A.x;
-      const float adx = fma_(A.z * dx, dx, B.y);
-      const float bdx = A.w * dx;
-      const float dy = fy - A.y;
-      float p = fma_(B.x * dy, dy, fma_(bdx, dy, adx));
-      float d = fma_(B.x, fma_(2.0f, dy, 1.0f), bdx);
-      const float c2 = B.x + B.x;
-      const uint32_t li = base + (uint32_t)j;
-      float wsum = 0.0f;
+    // returns true once every pixel is done
+    auto step = [&](int j, auto ngroup, auto clamped) -> bool {
+      constexpr int G = decltype(ngroup)::value;
+      constexpr bool CLAMP = decltype(clamped)::value;
+      float w[G][kPx], T0[kPx];
 #pragma unroll
-      for (int k = 0; k < kPx; ++k) {
-        if (k > 0) {
-          p += d;
-          d += c2;
+      for (int k = 0; k < kPx; ++k) T0[k] = T[k];
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const float4 A = sA[j + g];
+        const float4 B = sB[j + g];
+        const float dx = fx - A.x;
+        const float adx = fma_(A.z * dx, dx, B.y);
+        const float bdx = A.w * dx;
+        const float dy = fy - A.y;
+        float p = fma_(B.x * dy, dy, fma_(bdx, dy, adx));
+        float d = fma_(B.x, fma_(2.0f, dy, 1.0f), bdx);
+#pragma unroll
+        for (int k = 0; k < kPx; ++k) {
+          if (k > 0) {
+            p += d;
+            d += B.z;
+          }
+          float al = __builtin_amdgcn_exp2f(p);
+          if (CLAMP) al = fminf(amax, al);
+          if (AMIN) al = al < amin ? 0.0f : al;
+          w[g][k] = al * fabsf(T[k]);
+          T[k] = T[k] - w[g][k];
         }
-        float al = fminf(amax, __builtin_amdgcn_exp2f(p));
-        if (AMIN) al = al < amin ? 0.0f : al;
-        al = done[k] ? 0.0f : al;
-        const float w = al * T[k];
-        cr[k] = fma_(w, B.z, cr[k]);
-        cg[k] = fma_(w, B.w, cg[k]);
-        cb[k] = fma_(w, cbl, cb[k]);
-        T[k] = T[k] - w;
-        // `last` follows every entry a live pixel blends and freezes once the
-        // pixel is done: the entry that took T below t_min, else the list
-        // length (a live pixel keeps the wave going to the end).  A done lane
-        // blends nothing more, so its T stays below t_min; an outside lane
-        // starts at T = 0.
-        if (LAST) last[k] = done[k] ? last[k] : li;
-        done[k] = T[k] < tmin;
-        if (LOG) wsum += w;
       }
-      if (LOG) {
-        const float ws = wave_sum_f(wsum);
-        if (__lane_id() == 0) s_w[j] = ws;
-      }
-    };
-    // groups of 16 entries, with a wave-uniform exit check between groups
-    for (int j0 = 0; j0 < nb; j0 += 16) {
-      if (!LOG && __all(done[0] && done[1] && done[2] && done[3])) break;
-      if (j0 + 16 <= nb) {
+      uint32_t low = ~0u;
 #pragma unroll
-        for (int k = 0; k < 16; ++k) step(j0 + k);
-      } else {
-        for (int j = j0; j < nb; ++j) step(j);
+      for (int k = 0; k < kPx; ++k) low = min(low, __float_as_uint(T[k]));
+      bool stop = false;
+      if (ballot(low < tbits) != 0ull) {
+        // `last` is the entry that took T below t_min, else the list length
+#pragma unroll
+        for (int k = 0; k < kPx; ++k) {
+          bool live = !(done & (1u << k));
+          float Tk = T0[k];
+#pragma unroll
+          for (int g = 0; g < G; ++g) {
+            w[g][k] = live ? w[g][k] : 0.0f;
+            Tk -= w[g][k];
+            const bool now = live && Tk < tmin;
+            if (LAST) last[k] = now ? base + (uint32_t)(j + g) : last[k];
+            live = live && !now;
+          }
+          Tdone[k] = live || (done & (1u << k)) ? Tdone[k] : Tk;
+          T[k] = live ? Tk : -0.0f;
+          done |= live ? 0u : 1u << k;
+        }
+        stop = __all(done == kAll);
       }
-    }
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const float4 C = sC[j + g];
+        float wsum = 0.0f;
+#pragma unroll
+        for (int k = 0; k < kPx; ++k) {
+          cr[k] = fma_(w[g][k], C.x, cr[k]);
+          cg[k] = fma_(w[g][k], C.y, cg[k]);
+          cb[k] = fma_(w[g][k], C.z, cb[k]);
+          if (LOG) wsum += w[g][k];
+        }
+        if (LOG) {
+          const float ws = wave_sum_f(wsum);
+          if (__lane_id() == 0) s_w[j + g] = ws;
+        }
+      }
+      return stop;
+    };
+    typedef std::integral_constant<int, kGroup> Group;
+    typedef std::integral_constant<int, 1> One;
+    int j = 0;
+    bool stop = false;
+    for (; j + kGroup <= nb && (LOG || !stop); j += kGroup)
+      stop = (uint32_t)(clamp >> j) & ((1u << kGroup) - 1u)
+                 ? step(j, Group(), std::true_type())
+                 : step(j, Group(), std::false_type());
+    for (; j < nb && (LOG || !stop); ++j) stop = step(j, One(), std::true_type());
     if (LOG) {
       __syncthreads();
-#pragma unroll
-      for (int q = 0; q < kFwdBatch / kFwdThreads; ++q) {
-        const int i = t + q * kFwdThreads;
-        if (i < nb && s_w[i] != 0.0f) atomicAdd(&a.gauss_w[s_slot[i]], s_w[i]);
-      }
+      if (t < nb && s_w[t] != 0.0f) atomicAdd(&a.gauss_w[s_slot[t]], s_w[t]);
     }
-    if (__all(done[0] && done[1] && done[2] && done[3])) break;
+    if (__all(done == kAll)) break;
   }
   const size_t plane = (size_t)a.W * a.H;
 #pragma unroll
   for (int k = 0; k < kPx; ++k) {
-    if (in[k]) {
+    if (!(outside & (1u << k))) {
       const size_t pix = (size_t)(py0 + k) * a.W + px;
-      a.rgb[pix] = fma_(T[k], a.bg[0], cr[k]);
-      a.rgb[plane + pix] = fma_(T[k], a.bg[1], cg[k]);
-      a.rgb[2 * plane + pix] = fma_(T[k], a.bg[2], cb[k]);
-      a.T_final[pix] = T[k];
+      const float Tk = done & (1u << k) ? Tdone[k] : T[k];
+      a.rgb[pix] = fma_(Tk, a.bg[0], cr[k]);
+      a.rgb[plane + pix] = fma_(Tk, a.bg[1], cg[k]);
+      a.rgb[2 * plane + pix] = fma_(Tk, a.bg[2], cb[k]);
+      a.T_final[pix] = Tk;
       if (LAST) a.last[pix] = last[k];
     }
   }
 }
 
-template <bool LOG>
-__global__ __launch_bounds__(kFwdThreads) void k_composite(CompArgs a) {
-  __shared__ CompLds<LOG> lds;
-  // the conditions of the earlier stages are final here: one thread adds
-  // them to the caller's status word
-  if (a.status && blockIdx.x == 0 && threadIdx.x == 0) {
-    const uint32_t f = (a.ws.hdr->pair_overflow ? OCTGS_STATUS_PAIR_OVERFLOW : 0u) |
-                       (a.ws.hdr->sync_error ? OCTGS_STATUS_SYNC_ERROR : 0u);
-    if (f) atomicOr(a.status, f);
+// Few tiles (kFewTiles): one wave per tile leaves most of the chip idle and the
+// longest list sets the time, 0.13 us per entry.  Here a block of eight waves
+// composites 64 pixels, the K-th (K = 0 .. 3) of every column of four: waves
+// 1 to 7 work out the alphas of a batch, a few entries each, into LDS, while
+// wave 0 blends the batch before it, which leaves five instructions per entry
+// in the chain; wave 7 also stages the batch after next.  The operations on a
+// pixel are those of composite_tile, in the same order.
+// A 128 x 128 view whose longest list has 606 entries: 81 -> 23 us.  It costs
+// 2.5 times the vector work of one wave per tile, so it stops paying where the
+// chip is full: whole passes of one view with one wave per tile / these blocks,
+// at 64 tiles 75 / 54 us, 256: 76 / 67, 475: 79 / 79 (94 / 88 with longer
+// lists), 768: 80 / 89, 1024: 80 / 101; four views in flight, at 64 tiles
+// 293 / 262, 192: 294 / 275, 300: 345 / 325.
+constexpr int kFewThreads = 512, kFewWaves = kFewThreads / kWave;
+constexpr int kFewTiles = 400;
+constexpr int kRing = 4;  // staged batches: blended last, being blended, next, after next
+
+struct FewLds {
+  float4 sA[kRing][kFwdBatch], sB[kRing][kFwdBatch], sC[kRing][kFwdBatch];
+  uint32_t s_slot[kRing][kFwdBatch];
+  float al[2][kFwdBatch][kWave];  // alphas of a batch, then its weights
+  uint32_t stop[2];
+};
+
+template <bool AMIN, int K>
+__device__ __forceinline__ void few_alphas(const CompArgs &a, FewLds &lds, uint32_t b, int w, int l,
+                                           int nb, float fx, float fy) {
+  for (int j = w - 1; j < kFwdBatch; j += kFewWaves - 1) {
+    const float4 A = lds.sA[b % kRing][j];
+    const float4 B = lds.sB[b % kRing][j];
+    const float dx = fx - A.x;
+    const float adx = fma_(A.z * dx, dx, B.y);
+    const float bdx = A.w * dx;
+    const float dy = fy - A.y;
+    float p = fma_(B.x * dy, dy, fma_(bdx, dy, adx));
+    float d = fma_(B.x, fma_(2.0f, dy, 1.0f), bdx);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      p += d;
+      d += B.z;
+    }
+    float al = fminf(a.alpha_max, __builtin_amdgcn_exp2f(p));
+    if (AMIN) al = al < a.alpha_min ? 0.0f : al;
+    lds.al[b & 1][j][l] = j < nb ? al : 0.0f;
   }
-  // a render that no backward follows may leave out the per-pixel entry
-  // count, one select per pixel and entry
+}
+
+template <bool LOG>
+__global__ __launch_bounds__(kFewThreads) void k_composite_few(CompArgs a) {
+  __shared__ FewLds lds;
+  add_status(a);
+  const int K = (int)(blockIdx.x % kPx);
+  const uint32_t block = blockIdx.x / kPx;
+  const int32_t tile = a.ordered ? (int32_t)a.ws.tile_order[block]
+                                 : tile_of_block(block, a.ws.tiles_x, a.ws.tiles_y);
+  if (tile < 0) return;
+  const int tx = tile % a.ws.tiles_x, ty = tile / a.ws.tiles_x;
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), l = __lane_id();
+  const int px = tx * kTile + (l % kTile), row0 = ty * kTile + kPx * (l / kTile), py = row0 + K;
+  const float fx = (float)px + 0.5f, fy = (float)row0 + 0.5f;
+  const uint32_t start = __builtin_amdgcn_readfirstlane(a.ws.ranges[2 * tile]);
+  const uint32_t end = __builtin_amdgcn_readfirstlane(a.ws.ranges[2 * tile + 1]);
+  const int len = (int)(end - start), nbatch = (len + kFwdBatch - 1) / kFwdBatch;
+  const float tmin = a.t_min;
+  const uint32_t tbits = t_bits(a);
+  const bool in = px < a.W && py < a.H;
+  float T = in ? 1.0f : -0.0f, Tdone = 0.0f, cr = 0.0f, cg = 0.0f, cb = 0.0f;
+  uint32_t last = (uint32_t)len;
+  bool done = !in;
+
+  // entry l of batch b, which exists; past the list's end a colour of 0
+  float4 A, B, C;
+  uint32_t s = 0;
+  auto load = [&](int b) {
+    const int e = b * kFwdBatch + l;
+    s = a.ws.tval[start + (uint32_t)min(e, len - 1)];
+    A = a.ws.proj[3 * (size_t)s];
+    B = a.ws.proj[3 * (size_t)s + 1];
+    C = make_float4(B.z, B.w, a.ws.proj[3 * (size_t)s + 2].x, 0.0f);
+    if (e >= len) C = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  };
+  auto put = [&](int b) {
+    lds.sA[b % kRing][l] = A;
+    lds.sB[b % kRing][l] = make_float4(B.x, B.y, B.x + B.x, 0.0f);
+    lds.sC[b % kRing][l] = C;
+    lds.s_slot[b % kRing][l] = s;
+  };
+  // sums of batch b's weights, by the waves that wrote its alphas
+  auto log_weights = [&](int b) {
+    const int nb = min(kFwdBatch, len - b * kFwdBatch);
+    for (int j = w - 1; j < nb; j += kFewWaves - 1) {
+      const float ws = wave_sum_f(lds.al[b & 1][j][l]);
+      if (l == 0 && ws != 0.0f) atomicAdd(&a.gauss_w[lds.s_slot[b % kRing][j]], ws);
+    }
+  };
+  if (w == 0 && nbatch > 0) {
+    load(0);
+    put(0);
+  }
+  __syncthreads();
+  int b = -1;
+  for (; b < nbatch; ++b) {
+    const bool ahead = w == kFewWaves - 1 && b + 2 < nbatch;
+    if (ahead) load(b + 2);
+    if (w == 0) {
+      if (b >= 0) {
+        const int nb = min(kFwdBatch, len - b * kFwdBatch);
+        const float4 *sC = lds.sC[b % kRing];
+        float (*al)[kWave] = lds.al[b & 1];
+        for (int j = 0; j < nb; j += kGroup) {
+          float wt[kGroup], T0 = T;
+          float4 c[kGroup];
+#pragma unroll
+          for (int g = 0; g < kGroup; ++g) {
+            wt[g] = al[j + g][l];
+            c[g] = sC[j + g];
+          }
+#pragma unroll
+          for (int g = 0; g < kGroup; ++g) {
+            wt[g] = wt[g] * fabsf(T);
+            T -= wt[g];
+          }
+          if (ballot(__float_as_uint(T) < tbits) != 0ull) {
+            bool live = !done;
+            float Tk = T0;
+#pragma unroll
+            for (int g = 0; g < kGroup; ++g) {
+              wt[g] = live ? wt[g] : 0.0f;
+              Tk -= wt[g];
+              const bool now = live && Tk < tmin;
+              last = now ? (uint32_t)(b * kFwdBatch + j + g + 1) : last;
+              live = live && !now;
+            }
+            Tdone = live || done ? Tdone : Tk;
+            T = live ? Tk : -0.0f;
+            done = !live;
+          }
+#pragma unroll
+          for (int g = 0; g < kGroup; ++g) {
+            cr = fma_(wt[g], c[g].x, cr);
+            cg = fma_(wt[g], c[g].y, cg);
+            cb = fma_(wt[g], c[g].z, cb);
+            if (LOG) al[j + g][l] = wt[g];
+          }
+        }
+        const bool all = __all(done);  // over the whole wave
+        if (l == 0) lds.stop[b & 1] = all ? 1u : 0u;
+      }
+    } else {
+      if (LOG && b > 0) log_weights(b - 1);
+      if (b + 1 < nbatch) {
+        const int nb = min(kFwdBatch, len - (b + 1) * kFwdBatch);
+        const bool amin = a.alpha_min > 0.0f;
+#define OCTGS_FEW_ALPHAS(KK)                                                \
+  case KK:                                                                  \
+    if (amin)                                                               \
+      few_alphas<true, KK>(a, lds, (uint32_t)(b + 1), w, l, nb, fx, fy);    \
+    else                                                                    \
+      few_alphas<false, KK>(a, lds, (uint32_t)(b + 1), w, l, nb, fx, fy);   \
+    break;
+        switch (K) {
+          OCTGS_FEW_ALPHAS(0)
+          OCTGS_FEW_ALPHAS(1)
+          OCTGS_FEW_ALPHAS(2)
+          OCTGS_FEW_ALPHAS(3)
+        }
+#undef OCTGS_FEW_ALPHAS
+      }
+    }
+    if (ahead) put(b + 2);
+    lds_barrier();
+    // (a word is written again two barriers later)
+    if (b >= 0 && lds.stop[b & 1]) break;
+  }
+  if (LOG && nbatch > 0 && w > 0) log_weights(min(b, nbatch - 1));
+  if (w > 0 || !in) return;
+  const size_t plane = (size_t)a.W * a.H, pix = (size_t)py * a.W + px;
+  const float Tk = done ? Tdone : T;
+  a.rgb[pix] = fma_(Tk, a.bg[0], cr);
+  a.rgb[plane + pix] = fma_(Tk, a.bg[1], cg);
+  a.rgb[2 * plane + pix] = fma_(Tk, a.bg[2], cb);
+  a.T_final[pix] = Tk;
+  if (a.last) a.last[pix] = last;
+}
+
+template <bool LOG>
+__global__ __launch_bounds__(kFwdThreads, LOG ? 1 : 5) void k_composite(CompArgs a) {
+  __shared__ CompLds<LOG> lds;
+  add_status(a);
+  // a render that no backward follows may leave out the per-pixel entry count
   if (a.alpha_min > 0.0f) {
     if (a.last)
       composite_tile<LOG, true, true>(a, lds);
@@ -736,12 +989,18 @@ int octgs_rasterize_fwd(const octgs_gaussians *g, const octgs_camera *cam,
   ca.gauss_w = gauss_w;
   ca.status = g->status;
   mark(8);
-  if (gauss_w)
-    hipLaunchKernelGGL(k_composite<true>, dim3(tile_grid_blocks(ws.tiles_x, ws.tiles_y)),
-                       dim3(kFwdThreads), 0, s, ca);
-  else
-    hipLaunchKernelGGL(k_composite<false>, dim3(tile_grid_blocks(ws.tiles_x, ws.tiles_y)),
-                       dim3(kFwdThreads), 0, s, ca);
+  const uint32_t blocks = tile_grid_blocks(ws.tiles_x, ws.tiles_y);
+  if ((int64_t)ws.tiles_x * ws.tiles_y <= kFewTiles) {
+    if (gauss_w)
+      hipLaunchKernelGGL(k_composite_few<true>, dim3(kPx * blocks), dim3(kFewThreads), 0, s, ca);
+    else
+      hipLaunchKernelGGL(k_composite_few<false>, dim3(kPx * blocks), dim3(kFewThreads), 0, s, ca);
+  } else {
+    if (gauss_w)
+      hipLaunchKernelGGL(k_composite<true>, dim3(blocks), dim3(kFwdThreads), 0, s, ca);
+    else
+      hipLaunchKernelGGL(k_composite<false>, dim3(blocks), dim3(kFwdThreads), 0, s, ca);
+  }
   mark(9);
   return hipGetLastError() == hipSuccess ? OCTGS_OK : OCTGS_EHIP;
 }
