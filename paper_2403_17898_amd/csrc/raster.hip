@@ -879,8 +879,6 @@ RasterWs raster_layout(void *base, int64_t gcap, int64_t pcap, int32_t W, int32_
   ws.rect = (ulonglong2 *)take((size_t)g * 16);
   ws.pair_base = (uint32_t *)take((size_t)g * 4);
   ws.group_off = (uint16_t *)take((size_t)ws.nblk_g * ws.group_pitch * 2);
-  ws.group = (uint4 *)take((size_t)ws.nblk_g * kGroupCap * 16);
-  ws.large = (uint4 *)take((size_t)ws.nblk_g * kSlots * 16);
   ws.bin_range = (uint2 *)take((size_t)nbins * 8);
   for (int i = 0; i < 2; ++i) ws.bin_slot[i] = (uint32_t *)take((size_t)pc * 4);
   for (int i = 0; i < 2; ++i) ws.bin_mask[i] = (uint32_t *)take((size_t)pc * 4);
@@ -891,10 +889,18 @@ RasterWs raster_layout(void *base, int64_t gcap, int64_t pcap, int32_t W, int32_
   ws.tval = (uint32_t *)take((size_t)pc * 4);
   ws.ranges = (uint32_t *)take((size_t)ntiles * 8);
   ws.tile_order = (uint32_t *)take((size_t)tile_grid_blocks(ws.tiles_x, ws.tiles_y) * 4);
+  // the groups are read by the bin sort only, before anything writes the
+  // backward's arrays (the tile lists clear rows of gpair): one place for both
+  const size_t shared = off;
+  ws.group = (uint4 *)take((size_t)ws.nblk_g * kGroupCap * 16);
+  ws.large = (uint4 *)take((size_t)ws.nblk_g * kSlots * 16);
+  const size_t fwd_end = off;
+  off = shared;
   ws.dproj = (float *)take((size_t)g * 9 * 4);
   ws.gpair = (float *)take((size_t)pc * kPairRow * 4);
   ws.chunk_part = (float *)take((size_t)((pc + 63) / 64) * 18 * 4);
   ws.chunk_info = (uint32_t *)take((size_t)((pc + 63) / 64) * 4);
+  off = std::max(off, fwd_end);
   ws.bytes = off;
   return ws;
 }
