@@ -452,20 +452,6 @@ __device__ __forceinline__ uint32_t t_bits(const CompArgs &a) {
   return !(a.alpha_max <= 1.0f) ? ~0u : (a.t_min > 0.0f ? __float_as_uint(a.t_min) : 0u);
 }
 
-// May the computed exponent of the entry exceed log2(alpha_max) at a pixel of
-// the tile whose first pixel centre is (X0, Y0)?  Exactly p <= log2 op, since
-// the quadratic is nowhere positive.  The conic's, the products' and the
-// differences' rounding errors add up to less than 64 x 2^-24 times the sum of
-// the terms' magnitudes over the tile (|dx|, |dy| reach at least 7.5, so the
-// terms of d are smaller than those of p); exp2 and log2 are within 2^-16.
-// Not-a-number and infinite terms count as "may".
-__device__ __forceinline__ bool may_clamp(float lamax, const float4 &A, const float4 &B, float X0,
-                                          float Y0) {
-  const float DX = fabsf(A.x - (X0 + 7.5f)) + 7.5f, DY = fabsf(A.y - (Y0 + 7.5f)) + 7.5f;
-  const float M = fabsf(A.z) * DX * DX + fabsf(A.w) * DX * DY + fabsf(B.x) * DY * DY + fabsf(B.y);
-  return !(B.y + 0x1p-18f * M + 0x1p-16f < lamax);
-}
-
 // The LDS lives in the kernel and is passed in, so the instantiations share
 // one allocation.
 template <bool LOG, bool AMIN, bool LAST>

@@ -18,6 +18,8 @@
 // quantities (rotation, 3D covariance, Jacobian, 2D covariance) in FP32.
 #include "octgs_internal.h"
 
+#include <type_traits>
+
 namespace octgs {
 
 namespace {
@@ -32,41 +34,83 @@ struct BwdArgs {
   const uint32_t *last;
 };
 
-// Sum of 8 values over the 64 lanes of a wave, by halving exchanges: a
-// permlane32 swap, a permlane16 swap and a DPP row rotation leave each lane
-// one partial sum of value 4 b5 + 2 b4 + b3 (b = lane bits), and three DPP
-// steps finish it within 8 lanes.  Lane 8 q returns the total of value q.
-__device__ __forceinline__ float wave_sum8(const float (&v)[8], int &q) {
-  const int l = __lane_id();
-  float a[4], b[2];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    uint32_t x = __float_as_uint(v[i]), y = __float_as_uint(v[4 + i]);
-    swap32(x, y);
-    a[i] = __uint_as_float(x) + __uint_as_float(y);
+// What one entry's pixels of a lane add to its gradient, with dq = dL/da a0
+// (0 where alpha is clamped): D = sum dq, Sy = sum dq dy, Q = sum dq dy^2, the
+// colour weights, and the lane's dx (one column, so the sums with dx follow).
+struct EntrySums {
+  float D, Sy, Q, wr, wg, wb, dx;
+};
+
+__device__ __forceinline__ float half32(float x, float y) {  // lanes 0..31: sum of x, 32..63: of y
+  uint32_t u = __float_as_uint(x), v = __float_as_uint(y);
+  swap32(u, v);
+  return __uint_as_float(u) + __uint_as_float(v);
+}
+__device__ __forceinline__ float half16(float x, float y) {  // even rows of 16 lanes: x, odd: y
+  uint32_t u = __float_as_uint(x), v = __float_as_uint(y);
+  swap16(u, v);
+  return __uint_as_float(u) + __uint_as_float(v);
+}
+template <int CTRL>
+__device__ __forceinline__ float half_dpp(float x, float y, bool second) {
+  return (second ? y : x) + __uint_as_float(dpp_u<CTRL>(__float_as_uint(second ? x : y)));
+}
+
+// Sums of two entries over the wave, by halving exchanges: first over the four
+// lanes of a column, where D, Sy and Q need no dx yet (12 values, to a value
+// per row of 16 lanes in three registers), then over the 16 columns (7
+// registers with the products by dx).  42 instructions for 18 sums; summing
+// each entry's nine values over the wave took 62.  Lane `l` returns the sum
+// described by pair_sum_of(l).
+__device__ __forceinline__ float pair_sums(const EntrySums &a, const EntrySums &b, int l) {
+  const float r0 = half16(half32(a.D, a.Sy), half32(a.Q, a.wr));
+  const float r1 = half16(half32(b.D, b.Sy), half32(b.Q, b.wr));
+  const float r2 = half16(half32(a.wg, b.wg), half32(a.wb, b.wb));
+  const float ax = r0 * a.dx, axx = ax * a.dx, bx = r1 * b.dx, bxx = bx * b.dx;
+  const bool h3 = (l >> 3) & 1, h2 = (l >> 2) & 1, h1 = (l >> 1) & 1;
+  const float s0 = half_dpp<kDppRor8>(r0, ax, h3), s1 = half_dpp<kDppRor8>(axx, r2, h3);
+  const float s2 = half_dpp<kDppRor8>(r1, bx, h3);
+  const float s3 = bxx + __uint_as_float(dpp_u<kDppRor8>(__float_as_uint(bxx)));
+  const float t0 = half_dpp<kDppHalfMirror>(s0, s1, h2), t1 = half_dpp<kDppHalfMirror>(s2, s3, h2);
+  const float u = half_dpp<kDppXor2>(t0, t1, h1);
+  return u + __uint_as_float(dpp_u<kDppXor1>(__float_as_uint(u)));
+}
+
+// Which sum lane l gets from pair_sums: 2 v + e for value v (D, D dx, D dx^2,
+// Sy, Sy dx, Q, wr, wg, wb) of entry e (0: a, 1: b), or -1.
+__device__ __forceinline__ int pair_sum_of(int l) {
+  if (l & 1) return -1;
+  const int row = l >> 4;  // 0: D, 1: Q, 2: Sy, 3: wr; of r2: wg a, wb a, wg b, wb b
+  const int h3 = (l >> 3) & 1, h2 = (l >> 2) & 1, e = (l >> 1) & 1;
+  int v;
+  if (h2 == 0 && h3 == 0) {
+    v = row == 0 ? 0 : (row == 1 ? 5 : (row == 2 ? 3 : 6));
+  } else if (h2 == 0) {
+    v = row == 0 ? 1 : (row == 2 ? 4 : -1);
+  } else if (h3 == 0 || e == 1) {
+    v = row == 0 && h3 == 0 ? 2 : -1;
+  } else {
+    return 2 * (7 + (row & 1)) + (row >> 1);
   }
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    uint32_t x = __float_as_uint(a[i]), y = __float_as_uint(a[2 + i]);
-    swap16(x, y);
-    b[i] = __uint_as_float(x) + __uint_as_float(y);
-  }
-  const bool h3 = (l >> 3) & 1;
-  float c = (h3 ? b[1] : b[0]) + __uint_as_float(dpp_u<kDppRor8>(__float_as_uint(h3 ? b[0] : b[1])));
-  c += __uint_as_float(dpp_u<kDppXor1>(__float_as_uint(c)));
-  c += __uint_as_float(dpp_u<kDppXor2>(__float_as_uint(c)));
-  c += __uint_as_float(dpp_u<kDppHalfMirror>(__float_as_uint(c)));
-  q = 4 * ((l >> 5) & 1) + 2 * ((l >> 4) & 1) + (int)h3;
-  return c;
+  return v < 0 ? -1 : 2 * v + e;
 }
 
 // Reverse replay of one tile by one wave (64 threads), four vertically
 // adjacent pixels per thread, replaying the forward's per-pixel exponent
 // sequence operation for operation, so every a_i is bit-identical to the
 // forward's and T_i = T_{i+1} / (1 - a_i) retraces its transmittances.
+// Bound by vector issue.  Entries before the first one that some pixel stopped
+// at (most of a list) need no per-pixel test, and those whose alphas cannot
+// reach alpha_max no clamp: 88 instructions per entry and 21 for its share of
+// the sums over the wave, where testing, clamping and summing each entry alone
+// took 165 together.  A 1600 x 1066 view, 0.67M pairs: 208 -> 170 us (at 85
+// registers; held to 80 and 72: 174 and 181).
 constexpr int kBwdThreads = 64;
 constexpr int kBwdBatch = 64;
 constexpr int kBPx = 4;
+// How an entry is replayed: every pixel counts it and its alphas cannot reach
+// alpha_max (may_clamp); every pixel counts it; or per pixel.
+constexpr int kBwdFree = 0, kBwdClamp = 1, kBwdCheck = 2;
 
 struct BwdLds {
   float4 sA[kBwdBatch], sB[kBwdBatch], sC[kBwdBatch];
@@ -129,7 +173,7 @@ __device__ __forceinline__ void composite_bwd_tile(const BwdArgs &a, BwdLds &lds
   // instead of the colour), entries used
   float T[kBPx], dr[kBPx], dg[kBPx], db[kBPx], S[kBPx];
   uint32_t last[kBPx];
-  uint32_t mx = 0;
+  uint32_t mx = 0, mn = 0xffffffffu;
 #pragma unroll
   for (int k = 0; k < kBPx; ++k) {
     T[k] = 1.0f; dr[k] = 0.0f; dg[k] = 0.0f; db[k] = 0.0f; last[k] = 0;
@@ -143,39 +187,52 @@ __device__ __forceinline__ void composite_bwd_tile(const BwdArgs &a, BwdLds &lds
     }
     S[k] = T[k] * fma_(a.bg[0], dr[k], fma_(a.bg[1], dg[k], a.bg[2] * db[k]));
     mx = max(mx, last[k]);
+    mn = min(mn, last[k]);  // 0 where a pixel lies outside the image
   }
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, o, kWave));
+  for (int o = 32; o > 0; o >>= 1) {
+    mx = max(mx, (uint32_t)__shfl_xor((int)mx, o, kWave));
+    mn = min(mn, (uint32_t)__shfl_xor((int)mn, o, kWave));
+  }
+  mx = (uint32_t)__builtin_amdgcn_readfirstlane((int)mx);
+  mn = (uint32_t)__builtin_amdgcn_readfirstlane((int)mn);
   const uint32_t n_used = min(mx, end - start);
-  const float amax = a.alpha_max, amin = a.alpha_min;
+  const float amax = a.alpha_max, amin = a.alpha_min, lamax = log2f(amax);
+  const int sum_of = pair_sum_of(l);
+  // where the lane's sum goes, from the later entry's index on
+  const int sum_at = (sum_of >> 1) * kBwdBatch - (sum_of & 1);
   zero_pairs(a.ws, nblk, (uint32_t)tx, (uint32_t)ty, start + n_used, end);
   if (n_used == 0) return;
   for (int32_t b0 = (int32_t)((n_used - 1) / kBwdBatch) * kBwdBatch; b0 >= 0; b0 -= kBwdBatch) {
     const int nb = (int)min((uint32_t)kBwdBatch, n_used - (uint32_t)b0);
     __syncthreads();  // one wave: orders the reuse of the batch buffers
-#pragma unroll
-    for (int q = 0; q < kBwdBatch / kBwdThreads; ++q) {
-      const int i = t + q * kBwdThreads;
-      const uint32_t e = start + (uint32_t)b0 + (uint32_t)min(i, nb - 1);
+    uint64_t clamp;  // bit i: entry i may need min(alpha_max, .)
+    {
+      const uint32_t e = start + (uint32_t)b0 + (uint32_t)min(t, nb - 1);
       const uint32_t s = vals[e];
-      s_pair[i] = pair_number(a.ws, s, nblk, (uint32_t)tx, (uint32_t)ty);
-      lds.s_slot[i] = s;
-      sA[i] = proj[3 * (size_t)s];
-      const float4 bv = proj[3 * (size_t)s + 1];
-      sB[i] = bv;
+      s_pair[t] = pair_number(a.ws, s, nblk, (uint32_t)tx, (uint32_t)ty);
+      lds.s_slot[t] = s;
+      const float4 av = proj[3 * (size_t)s], bv = proj[3 * (size_t)s + 1];
       float4 cv = proj[3 * (size_t)s + 2];
+      sA[t] = av;
+      sB[t] = bv;
       cv.y = __builtin_amdgcn_exp2f(-bv.y);  // 1 / opacity, for dL/dop = dL/da a / op
-      sC[i] = cv;
-#pragma unroll
-      for (int g = 0; g < 9; ++g) sG[g][i] = 0.0f;
+      sC[t] = cv;
+      clamp = ballot(may_clamp(lamax, av, bv, (float)(tx * kTile) + 0.5f, (float)(ty * kTile) + 0.5f));
     }
     __syncthreads();
-    for (int j = nb - 1; j >= 0; --j) {
-      const uint32_t li = (uint32_t)b0 + (uint32_t)j;  // index in the tile list
+    // one entry: its alphas by the forward's sequence, so each a0 (= op G') is
+    // bit-identical to it, then the reverse blending step of each pixel:
+    //   r = a / (1 - a), w = T_i a_i = r T, u = T cdot - S,
+    //   dL/da = u / (1 - a), dq = u r, S += w cdot, T_i = T / (1 - a)
+    // (T, S: behind the entry; cdot = dL/dC . c).  Over the thread's pixels
+    // k = 0..3 (dy = dy0 + k) E = sum k dq, F = sum k^2 dq, so sum dq dy =
+    // dy0 D + E and sum dq dy^2 = dy0^2 D + 2 dy0 E + F.
+    auto entry = [&](int j, auto mode) -> EntrySums {
+      constexpr int MODE = decltype(mode)::value;
       const float4 A = sA[j];
       const float4 B = sB[j];
-      const float4 Cc = sC[j];
-      // the forward's sequence, so each a0 (= op G') is bit-identical to it
+      const float cblue = sC[j].x;
       const float dx = fx - A.x;
       const float adx = fma_(A.z * dx, dx, B.y);
       const float bdx = A.w * dx;
@@ -183,13 +240,11 @@ __device__ __forceinline__ void composite_bwd_tile(const BwdArgs &a, BwdLds &lds
       float p = fma_(B.x * dy, dy, fma_(bdx, dy, adx));
       float d = fma_(B.x, fma_(2.0f, dy, 1.0f), bdx);
       const float c2 = B.x + B.x;
-      // raw per-lane sums, turned into gradients once per (tile, Gaussian):
-      // dq = dL/da a0 (0 where alpha is clamped); over the thread's pixels
-      // k = 0..3 (dy = dy0 + k), D = sum dq, E = sum k dq, F = sum k^2 dq,
-      // so sum dq dy = dy0 D + E and sum dq dy^2 = dy0^2 D + 2 dy0 E + F;
-      // colour weights
-      float D = 0.0f, E = 0.0f, F = 0.0f, wr = 0.0f, wg = 0.0f, wb = 0.0f;
-      bool any = false;
+      const uint32_t li = (uint32_t)b0 + (uint32_t)j;  // index in the tile list
+      float dq[kBPx];
+      EntrySums o;
+      o.dx = dx;
+      if (MODE == kBwdCheck) o.wr = o.wg = o.wb = 0.0f;
 #pragma unroll
       for (int k = 0; k < kBPx; ++k) {
         if (k > 0) {
@@ -197,39 +252,60 @@ __device__ __forceinline__ void composite_bwd_tile(const BwdArgs &a, BwdLds &lds
           d += c2;
         }
         const float a0 = __builtin_amdgcn_exp2f(p);
-        const float al = fminf(amax, a0);
-        bool valid = li < last[k];
-        if (AMIN) valid = valid && !(al < amin);
+        const float al = MODE == kBwdFree ? a0 : fminf(amax, a0);
+        dq[k] = 0.0f;
+        bool valid = true;
+        if (MODE == kBwdCheck) {
+          valid = li < last[k];
+          if (AMIN) valid = valid && !(al < amin);
+        }
         if (valid) {
-          any = true;
           const float inv1 = __builtin_amdgcn_rcpf(1.0f - al);
-          const float Ti = T[k] * inv1;
-          const float w = al * Ti;
-          wr = fma_(w, dr[k], wr);
-          wg = fma_(w, dg[k], wg);
-          wb = fma_(w, db[k], wb);
-          const float cdot = fma_(B.z, dr[k], fma_(B.w, dg[k], Cc.x * db[k]));
-          const float dLda = Ti * cdot - S[k] * inv1;
-          S[k] = fma_(w, cdot, S[k]);
-          T[k] = Ti;
-          const float dq = a0 <= amax ? dLda * a0 : 0.0f;
-          D += dq;
-          if (k > 0) {
-            E = fma_((float)k, dq, E);
-            F = fma_((float)(k * k), dq, F);
+          const float r = al * inv1;
+          const float w = r * T[k];
+          const float cdot = fma_(B.z, dr[k], fma_(B.w, dg[k], cblue * db[k]));
+          const float u = fma_(T[k], cdot, -S[k]);
+          if (MODE == kBwdCheck || k > 0) {
+            o.wr = fma_(w, dr[k], o.wr);
+            o.wg = fma_(w, dg[k], o.wg);
+            o.wb = fma_(w, db[k], o.wb);
+          } else {
+            o.wr = w * dr[k];
+            o.wg = w * dg[k];
+            o.wb = w * db[k];
           }
+          S[k] = fma_(w, cdot, S[k]);
+          T[k] = T[k] * inv1;
+          dq[k] = u * r;
+          if (MODE != kBwdFree) dq[k] = a0 <= amax ? dq[k] : 0.0f;
         }
       }
-      if (ballot(any) != 0ull) {
-        int q;
-        const float Sy = fma_(dy, D, E);
-        const float Qyy = fma_(dy, fma_(dy, D, 2.0f * E), F);
-        const float v8[8] = {D, D * dx, D * dx * dx, Sy, Sy * dx, Qyy, wr, wg};
-        const float s8 = wave_sum8(v8, q);
-        const float s9 = wave_sum_f(wb);
-        if ((l & 7) == 0) sG[q][j] = s8;
-        if (l == 0) sG[8][j] = s9;
+      const float q23 = dq[2] + dq[3], q123 = dq[1] + q23;
+      const float E = q123 + (q23 + dq[3]);
+      const float F = fma_(4.0f, dq[3], fma_(2.0f, q23, E));
+      o.D = dq[0] + q123;
+      o.Sy = fma_(dy, o.D, E);
+      o.Q = fma_(dy, fma_(dy, o.D, E + E), F);
+      return o;
+    };
+    // two entries a step, the later one first; where nb is odd the first step's
+    // later one lies past the list and no pixel counts it
+    for (int j = (nb - 1) | 1; j > 0; j -= 2) {
+      EntrySums hi, lo;
+      if (!AMIN && (uint32_t)(b0 + j) < mn) {
+        if ((clamp >> (j - 1)) & 3u) {
+          hi = entry(j, std::integral_constant<int, kBwdClamp>());
+          lo = entry(j - 1, std::integral_constant<int, kBwdClamp>());
+        } else {
+          hi = entry(j, std::integral_constant<int, kBwdFree>());
+          lo = entry(j - 1, std::integral_constant<int, kBwdFree>());
+        }
+      } else {
+        hi = entry(j, std::integral_constant<int, kBwdCheck>());
+        lo = entry(j - 1, std::integral_constant<int, kBwdCheck>());
       }
+      const float sum = pair_sums(hi, lo, l);
+      if (sum_of >= 0) (&sG[0][0])[sum_at + j] = sum;
     }
     __syncthreads();
     // raw sums -> dL/d(mx, my, ca, cb, cc, op, r, g, b).  With dpw = ln2 dq
@@ -237,9 +313,8 @@ __device__ __forceinline__ void composite_bwd_tile(const BwdArgs &a, BwdLds &lds
     //   dmx = -(2 A' Sx + B' Sy) ln2, dmy = -(B' Sx + 2 C' Sy) ln2,
     //   d(ca, cb, cc) = ln2 (-log2e / 2 Qxx, -log2e Qxy, -log2e / 2 Qyy),
     //   dop = D / op
-#pragma unroll
-    for (int q = 0; q < kBwdBatch / kBwdThreads; ++q) {
-      const int i = t + q * kBwdThreads;
+    {
+      const int i = t;
       if (i < nb) {
         const float4 A = sA[i], B = sB[i], Cc = sC[i];
         const float D = sG[0][i], Sx = sG[1][i], Qxx = sG[2][i], Sy = sG[3][i];

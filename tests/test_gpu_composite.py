@@ -58,3 +58,36 @@ def test_lists_and_stops(P, orc, W, n, opacity, kw):
         if log:
             np.testing.assert_allclose(_np(vb.gauss_w).astype(np.float64), ref["weights"],
                                        rtol=2e-4, atol=2e-4 * np.abs(ref["weights"]).max())
+
+
+@pytest.mark.parametrize("W,n,opacity,kw", [
+    (320, 1, (0.9, 1.0), {}), (320, 2, (0.1, 0.5), {}), (320, 63, (0.01, 0.05), {}),
+    (320, 64, (0.01, 0.05), {}), (320, 65, (0.02, 0.2), {}), (320, 129, (0.01, 0.2), {}),
+    (333, 66, (0.02, 0.2), {}), (320, 40, (0.9, 1.0), {}), (333, 31, (0.3, 1.0), {}),
+    (320, 50, (0.05, 1.0), {"alpha_min": 1.0 / 255.0}),
+])
+def test_backward_entry_modes(P, orc, W, n, opacity, kw):
+    """Gradients where every pixel counts an entry or only some do, with and
+    without alphas near the clamp, for odd and even list lengths around the
+    64-entry batches, on whole and partial tiles: 1e-3 normwise per attribute
+    group."""
+    H = 320
+    cam = S.look_at((0.0, -8.0, 0.0), (0.0, 0.0, 0.0), W, H, 60.0)
+    gf = S.random_gaussians(n, cam, 17 * n + W, depth=(4.0, 9.0), scale=(0.4, 3.0), margin=0.0,
+                            opacity=opacity)
+    say("composite backward", W, H, n, opacity, kw)
+    prm_o = orc.params_array(**kw)
+    ref = orc.rasterize(gf, cam, prm_o)
+    dimg = np.random.default_rng(n).standard_normal((3, H, W)).astype(np.float32)
+    dproj = orc.composite_backward(ref["pj"], ref["bs"], cam, prm_o, dimg.astype(np.float64))
+    want = orc.project_backward(gf.astype(np.float64), ref["pj"], cam, prm_o, dproj)
+    vb = P.ViewBuffers(n, 1, W, H, max(1, ref["bs"]["n_rect_pairs"]), gauss_capacity=n)
+    vb.gauss.copy_(torch.as_tensor(gf).cuda())
+    vb.gauss_count.fill_(n)
+    prm = P.raster_params(train=True, **kw)
+    vb.rasterize(P.make_camera(cam), prm)
+    vb.rasterize_bwd(P.make_camera(cam), prm, torch.as_tensor(dimg).cuda())
+    torch.cuda.synchronize()
+    got = _np(vb.dgauss).astype(np.float64)
+    for a, b in ((0, 3), (3, 6), (6, 10), (10, 11), (11, 14)):
+        assert np.linalg.norm(got[a:b] - want[a:b]) <= 1e-3 * np.linalg.norm(want[a:b]), (a, b)
