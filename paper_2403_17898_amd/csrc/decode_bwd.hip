@@ -26,6 +26,16 @@
 // atomics, the same result on every run.  The anchor count lives on the
 // device.
 //
+// Bound by latency between the block's barriers: the products alone take 6 of
+// the 14 us a pair of tiles takes (64 wide, k = 10), the rest is LDS round
+// trips, the activations and index arithmetic.  So tile indices are wave-
+// uniform and, the width being a template argument, free of divisions; a wave
+// owns whole column tiles and reads their operand once for all row tiles; the
+// activations' inputs and the next tile's anchors are read a phase or a tile
+// ahead; barriers wait for LDS only.  13,000 anchors: 62.5 -> 44.7 us (two
+// pairs per block, 1.6 on average; weights and first inputs take 6 us, handing
+// the second group's sums over and writing the block's row 4).
+//
 // MFMA 16x16x4 operand layouts (lane l, group g = l / 16, c = l % 16):
 //   A[m][k]: row m = c, k = g;  B[k][n]: column n = c, k = g;
 //   D[m][n]: column n = c, rows m = 4 g + i, i = 0..3.
@@ -52,8 +62,9 @@ constexpr int kXS = kInP + 4;          // LDS row pitches (floats)
 constexpr int kHS = 3 * kMaxW + 4;
 constexpr int kYS = kMaxOutP + 4;
 constexpr int kW1P = kMaxW + 4;        // W1 row pitch: conflict-free column reads for dX
-constexpr int kMaxT1 = 9;              // dW1 output tiles per wave (3 x 12 / 4)
-constexpr int kMaxT2 = 11;             // dW2 output tiles per wave (4 x 11 / 4)
+// A wave owns every fourth column tile of a product, three at most (hidden: 12,
+// outputs: 11), with all row tiles of dW1 (3, inputs) and dW2 (NHW, hidden).
+constexpr int kCols = 3;
 constexpr int kDecBwdGrid = 256;       // persistent blocks (one per CU: ~159 KB of LDS each)
 constexpr int kDecGroups = 2;          // wave groups per block, one tile each
 // A listed anchor's gradient row: position, feature, k offsets, offset
@@ -93,13 +104,12 @@ struct DecBwdTile {
   float dX[kRB][kInP];
   float Dn[kRB][4];              // distance and unit direction per anchor
   float dp[kRB][3];              // position gradient through the decoded means
-  uint32_t aidx[kRB];
 };
 
-// the second group's weight-gradient sums, handed to the first at the end
-// (in the tile buffers, which are free by then): per lane kMaxT1 + kMaxT2
-// accumulator tiles of 4 floats and the two bias sums
-constexpr int kXchSlots = 4 * (kMaxT1 + kMaxT2) + 2;
+// the second group's weight-gradient sums, handed to the first at the end (in
+// the whole of the LDS, which is free by then): per lane the accumulator tiles
+// of 4 floats and the two bias sums
+constexpr int kXchSlots = 4 * kCols * (3 + 4) + 2;
 
 struct DecBwdLds {
   float W1s[3 * kIn * kW1P];     // W1 heads, rows of kW1P
@@ -108,8 +118,8 @@ struct DecBwdLds {
   float b2s[kMaxOutP];           // padded output layout
   DecBwdTile tl[kDecGroups];
 };
-static_assert(sizeof(DecBwdTile) * kDecGroups >= sizeof(float) * kXchSlots * kBlock,
-              "the hand-over of the second group's sums fits in the tile buffers");
+static_assert(sizeof(DecBwdLds) >= sizeof(float) * kXchSlots * kBlock,
+              "the hand-over of the second group's sums fits");
 static_assert(sizeof(DecBwdLds) <= 160 * 1024, "LDS of one CU");
 
 __device__ __forceinline__ const float *pick3(const float *const p[3], int h) {
@@ -154,17 +164,28 @@ struct Ld4 {
   }
 };
 
+// NHW: column tiles of 16 per hidden layer (the width is 16 NHW).
+template <int NHW>
 __global__ __launch_bounds__(kDecBwdThreads) void k_dec_bwd(DecBwdArgs a) {
-  __shared__ DecBwdLds sh;
+  __shared__ __align__(16) DecBwdLds sh;
   // tb: thread of the block (weight staging); t, w: thread and wave within
   // the group, which owns tile buffers s
   const int tb = threadIdx.x, grp = tb / kBlock, t = tb % kBlock;
-  const int w = t / kWave, l = __lane_id(), g = l / 16, lc = l % 16;
+  const int w = __builtin_amdgcn_readfirstlane(t / kWave);
+  const int l = __lane_id(), g = l / 16, lc = l % 16;
   DecBwdTile &s = sh.tl[grp];
-  const int k = a.k, W = a.W;
-  const int nhw = W / 16, n1t = 3 * nhw;
+  const int k = a.k;
+  constexpr int W = 16 * NHW, nhw = NHW, n1t = 3 * NHW;
   const int n2t = a.t[0] + a.t[1] + a.t[2];
   const uint32_t M = min(*a.count, (uint32_t)a.cap_anchors);
+
+  // the anchor of this thread's row (16 threads each) in the coming tile, read
+  // ahead of what it is needed for
+  auto row_anchor = [&](uint64_t pair) -> uint32_t {
+    const uint64_t r = (pair * kDecGroups + grp) * kRB + t / 16;
+    return r < M ? a.idx[r] : 0u;
+  };
+  uint32_t j_next = row_anchor(blockIdx.x);
 
   // ---- weights and biases into LDS, every load in flight first ----
   {
@@ -209,11 +230,14 @@ __global__ __launch_bounds__(kDecBwdThreads) void k_dec_bwd(DecBwdArgs a) {
   }
   __syncthreads();
 
-  f4 acc1[kMaxT1], acc2[kMaxT2];
+  f4 acc1[kCols][3], acc2[kCols][NHW];  // [column tile w + 4 q][row tile]
 #pragma unroll
-  for (int q = 0; q < kMaxT1; ++q) acc1[q] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+  for (int q = 0; q < kCols; ++q) {
 #pragma unroll
-  for (int q = 0; q < kMaxT2; ++q) acc2[q] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int rt = 0; rt < 3; ++rt) acc1[q][rt] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int rt = 0; rt < NHW; ++rt) acc2[q][rt] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+  }
   float db1r = 0.0f, db2r = 0.0f;  // thread t owns hidden column t / padded output column t
 
   // pairs of tiles, one per group; a group past the last anchor runs the
@@ -221,17 +245,31 @@ __global__ __launch_bounds__(kDecBwdThreads) void k_dec_bwd(DecBwdArgs a) {
   for (uint32_t pair = blockIdx.x; (uint64_t)pair * kDecGroups * kRB < M; pair += gridDim.x) {
     const uint32_t r0 = (pair * kDecGroups + grp) * kRB;
     const int rows = r0 < M ? (int)min((uint32_t)kRB, M - r0) : 0;
-    // ---- inputs: 16 threads per anchor ----
+    // ---- inputs: 16 threads per anchor; lane i of a row is Gaussian i in the
+    // activations below, whose inputs are read here, long before their use ----
+    const int r = t / 16, i = t % 16;
+    const bool act = r < rows && i < k;
+    const uint32_t j = j_next;
+    j_next = row_anchor((uint64_t)pair + gridDim.x);
+    float dgv[kGaussFields], o[3], lv[3], bs[3];
     {
-      const int r = t / 16, part = t % 16;
+      const size_t jj = r < rows ? j : 0u;  // a row past the list reads anchor 0's, unused
+      const int ii = act ? i : 0;
+      const size_t sl = r < rows ? (size_t)(r0 + r) * k + ii : 0;
+#pragma unroll
+      for (int f = 0; f < kGaussFields; ++f) dgv[f] = a.dgauss[f * a.dstride + sl];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        o[c] = a.offsets[(jj * k + ii) * 3 + c];
+        lv[c] = a.oscale[3 * jj + c];
+        bs[c] = a.bscale[3 * jj + c];
+      }
       if (r < rows) {
-        const uint32_t j = a.idx[r0 + r];
-        if (part < 8) {
-          const float4 v = *(const float4 *)(a.feat + (size_t)j * 32 + part * 4);
-          s.X[r][part * 4 + 0] = v.x; s.X[r][part * 4 + 1] = v.y;
-          s.X[r][part * 4 + 2] = v.z; s.X[r][part * 4 + 3] = v.w;
-        } else if (part == 8) {
-          s.aidx[r] = j;
+        if (i < 8) {
+          const float4 v = *(const float4 *)(a.feat + (size_t)j * 32 + i * 4);
+          s.X[r][i * 4 + 0] = v.x; s.X[r][i * 4 + 1] = v.y;
+          s.X[r][i * 4 + 2] = v.z; s.X[r][i * 4 + 3] = v.w;
+        } else if (i == 8) {
           const float d0 = a.pos[3 * (size_t)j] - a.C[0], d1 = a.pos[3 * (size_t)j + 1] - a.C[1];
           const float d2 = a.pos[3 * (size_t)j + 2] - a.C[2];
           const float dist = sqrtf(fma_(d0, d0, fma_(d1, d1, d2 * d2)));
@@ -239,15 +277,15 @@ __global__ __launch_bounds__(kDecBwdThreads) void k_dec_bwd(DecBwdArgs a) {
           s.X[r][32] = dist * a.inv_dmax;
           s.X[r][33] = d0 * inv; s.X[r][34] = d1 * inv; s.X[r][35] = d2 * inv;
           s.Dn[r][0] = dist; s.Dn[r][1] = d0 * inv; s.Dn[r][2] = d1 * inv; s.Dn[r][3] = d2 * inv;
-        } else if (part < 12) {
-          const int c0 = kIn + 4 * (part - 9);
+        } else if (i < 12) {
+          const int c0 = kIn + 4 * (i - 9);
           s.X[r][c0] = 0.0f; s.X[r][c0 + 1] = 0.0f; s.X[r][c0 + 2] = 0.0f; s.X[r][c0 + 3] = 0.0f;
         }
       } else {
-        for (int c = part; c < kInP; c += 16) s.X[r][c] = 0.0f;
+        for (int c = i; c < kInP; c += 16) s.X[r][c] = 0.0f;
       }
     }
-    __syncthreads();
+    lds_barrier();
     // ---- Hp = X W1 + b1 ----
     // The wave's three column tiles share the A operand; each chunk of k-steps
     // loads all of its operands before its products, so the matrix pipe does
@@ -289,7 +327,7 @@ __global__ __launch_bounds__(kDecBwdThreads) void k_dec_bwd(DecBwdArgs a) {
         }
       }
     }
-    __syncthreads();
+    lds_barrier();
     // ---- Y = relu(Hp) W2 + b2 (padded output columns stay 0) ----
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
@@ -319,22 +357,16 @@ __global__ __launch_bounds__(kDecBwdThreads) void k_dec_bwd(DecBwdArgs a) {
         for (int i = 0; i < 4; ++i) s.Yd[4 * g + i][c * 16 + lc] = cv ? acc[i] + sh.b2s[c * 16 + lc] : 0.0f;
       }
     }
-    __syncthreads();
+    lds_barrier();
     // ---- activation derivatives: row r = anchor, lane i = Gaussian ----
     {
-      const int r = t / 16, i = t % 16;
       if (r < rows) {
-        const uint32_t j = s.aidx[r];
-        const bool act = i < k;
         const int ii = act ? i : 0;
         float *yr = s.Yd[r];
-        const size_t sl = (size_t)(r0 + r) * k + ii;
-        const float *lv = a.oscale + 3 * (size_t)j;
-        const float *bs = a.bscale + 3 * (size_t)j;
-        const float *o = a.offsets + ((size_t)j * k + ii) * 3;
-        float dgv[kGaussFields];
+        if (!act) {
 #pragma unroll
-        for (int f = 0; f < kGaussFields; ++f) dgv[f] = act ? a.dgauss[f * a.dstride + sl] : 0.0f;
+          for (int f = 0; f < kGaussFields; ++f) dgv[f] = 0.0f;
+        }
         float dp[3], dl[3], dbs[3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
@@ -394,7 +426,7 @@ __global__ __launch_bounds__(kDecBwdThreads) void k_dec_bwd(DecBwdArgs a) {
         for (int c = i; c < 16 * n2t; c += 16) s.Yd[r][c] = 0.0f;
       }
     }
-    __syncthreads();
+    lds_barrier();
     // ---- dHp = (dY W2^T) * [Hp > 0]; dW2 += relu(Hp)^T dY; db2 ----
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
@@ -429,91 +461,89 @@ __global__ __launch_bounds__(kDecBwdThreads) void k_dec_bwd(DecBwdArgs a) {
         }
       }
     }
-    // two output tiles at a time, their 16 operands loaded first (a tile
-    // past the last reads tile 0's and is skipped)
+    // a column tile's gradients are read once for its row tiles
 #pragma unroll
-    for (int q0 = 0; q0 < kMaxT2; q0 += 2) {
-      float av[2][kRB / 4], bv[2][kRB / 4];
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int T = w + 4 * (q0 + u);
-        const int Tc = T < nhw * n2t ? T : 0;
-        const int rt = Tc / n2t, c = Tc - rt * n2t;
+    for (int q = 0; q < kCols; ++q) {
+      const int c = w + 4 * q;
+      if (c < n2t) {
         int col0;
         const int h = out_head(a, c, col0);
+        float av[NHW][kRB / 4], bv[kRB / 4];
 #pragma unroll
         for (int ks = 0; ks < kRB / 4; ++ks) {
           const int row = ks * 4 + g;
-          av[u][ks] = fmaxf(s.Hp[row][h * W + rt * 16 + lc], 0.0f);
-          bv[u][ks] = s.Yd[row][c * 16 + lc];
-        }
-      }
+          bv[ks] = s.Yd[row][c * 16 + lc];
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int q = q0 + u;
-        if (q < kMaxT2 && w + 4 * q < nhw * n2t) {
-#pragma unroll
-          for (int ks = 0; ks < kRB / 4; ++ks) acc2[q] = mfma(av[u][ks], bv[u][ks], acc2[q]);
+          for (int rt = 0; rt < NHW; ++rt) av[rt][ks] = s.Hp[row][h * W + rt * 16 + lc];
         }
+#pragma unroll
+        for (int ks = 0; ks < kRB / 4; ++ks)
+#pragma unroll
+          for (int rt = 0; rt < NHW; ++rt)
+            acc2[q][rt] = mfma(fmaxf(av[rt][ks], 0.0f), bv[ks], acc2[q][rt]);
+        __builtin_amdgcn_sched_group_barrier(0x100, 4 * (NHW + 1), 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 4 * NHW, 0);
       }
-      __builtin_amdgcn_sched_group_barrier(0x100, 16, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
     }
     if (t < 16 * n2t)
       for (int r = 0; r < kRB; ++r) db2r += s.Yd[r][t];
-    __syncthreads();
+    lds_barrier();
     // ---- dX = dHp W1^T; dW1 += X^T dHp; db1 ----
     if (w < 3) {
       const int n = w * 16 + lc;
       const bool nv = n < kIn;
       f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-      // chunks of eight k-steps (3 W / 4 is a multiple of 12), operands first
+      // chunks of four k-steps of each head (W / 4 is a multiple of 4),
+      // operands first; a sum per head, so three chains run side by side
       const int nn = nv ? n : 0;
-      for (int k0 = 0; k0 < 3 * W / 4; k0 += 4) {
-        float av[4], bv[4];
+      f4 hs[3];
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-          const int kq = (k0 + kk) * 4 + g, h = kq / W, kh = kq - h * W;
-          av[kk] = s.dH[lc][kq];
-          bv[kk] = sh.W1s[(h * kIn + nn) * kW1P + kh];
-        }
+      for (int h = 0; h < 3; ++h) hs[h] = f4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) acc = mfma(av[kk], nv ? bv[kk] : 0.0f, acc);
-        __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+      for (int k0 = 0; k0 < W / 4; k0 += 4) {
+        float av[3][4], bv[3][4];
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+          for (int h = 0; h < 3; ++h) {
+            const int kh = (k0 + kk) * 4 + g;
+            av[h][kk] = s.dH[lc][h * W + kh];
+            bv[h][kk] = sh.W1s[(h * kIn + nn) * kW1P + kh];
+          }
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+          for (int h = 0; h < 3; ++h) hs[h] = mfma(av[h][kk], nv ? bv[h][kk] : 0.0f, hs[h]);
+        __builtin_amdgcn_sched_group_barrier(0x100, 24, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 12, 0);
       }
+      acc = (hs[0] + hs[1]) + hs[2];
 #pragma unroll
       for (int i = 0; i < 4; ++i) s.dX[4 * g + i][n] = acc[i];
     }
+    {
+      float av[3][kRB / 4];
 #pragma unroll
-    for (int q0 = 0; q0 < kMaxT1; q0 += 2) {
-      float av[2][kRB / 4], bv[2][kRB / 4];
+      for (int rt = 0; rt < 3; ++rt)
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int T = w + 4 * (q0 + u);
-        const int Tc = T < 3 * n1t ? T : 0;
-        const int rt = Tc / n1t, ct = Tc - rt * n1t;
+        for (int ks = 0; ks < kRB / 4; ++ks) av[rt][ks] = s.X[ks * 4 + g][rt * 16 + lc];
 #pragma unroll
-        for (int ks = 0; ks < kRB / 4; ++ks) {
-          const int row = ks * 4 + g;
-          av[u][ks] = s.X[row][rt * 16 + lc];
-          bv[u][ks] = s.dH[row][ct * 16 + lc];
+      for (int q = 0; q < kCols; ++q) {
+        const int ct = w + 4 * q;
+        if (ct < n1t) {
+          float bv[kRB / 4];
+#pragma unroll
+          for (int ks = 0; ks < kRB / 4; ++ks) bv[ks] = s.dH[ks * 4 + g][ct * 16 + lc];
+#pragma unroll
+          for (int ks = 0; ks < kRB / 4; ++ks)
+#pragma unroll
+            for (int rt = 0; rt < 3; ++rt) acc1[q][rt] = mfma(av[rt][ks], bv[ks], acc1[q][rt]);
         }
       }
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int q = q0 + u;
-        if (q < kMaxT1 && w + 4 * q < 3 * n1t) {
-#pragma unroll
-          for (int ks = 0; ks < kRB / 4; ++ks) acc1[q] = mfma(av[u][ks], bv[u][ks], acc1[q]);
-        }
-      }
-      __builtin_amdgcn_sched_group_barrier(0x100, 16, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
     }
     if (t < 3 * W)
       for (int r = 0; r < kRB; ++r) db1r += s.dH[r][t];
-    __syncthreads();
+    lds_barrier();
     // ---- features and position: 32 lanes per anchor ----
     for (int r = t / 32; r < rows; r += kBlock / 32) {
       const int f = t % 32;
@@ -531,62 +561,60 @@ __global__ __launch_bounds__(kDecBwdThreads) void k_dec_bwd(DecBwdArgs a) {
         row[kRowPos + 2] = s.dp[r][2] + fma_(u2, sd, (dx[35] - u2 * dot) * id);
       }
     }
-    __syncthreads();
+    lds_barrier();
   }
 
   // ---- the second group's sums into the first's (group order), then this
   // block's weight-gradient sums, one row of the workspace ----
-  float *xch = reinterpret_cast<float *>(&sh.tl[0]);
-  __syncthreads();  // every group is done with its tile buffers
+  float *xch = reinterpret_cast<float *>(&sh);
+  f4 *xch4 = reinterpret_cast<f4 *>(&sh);
+  __syncthreads();  // every group is done with the LDS
   if (grp == 1) {
 #pragma unroll
-    for (int q = 0; q < kMaxT1; ++q)
+    for (int q = 0; q < kCols; ++q) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) xch[(4 * q + i) * kBlock + t] = acc1[q][i];
+      for (int rt = 0; rt < 3; ++rt) xch4[(3 * q + rt) * kBlock + t] = acc1[q][rt];
 #pragma unroll
-    for (int q = 0; q < kMaxT2; ++q)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) xch[(4 * (kMaxT1 + q) + i) * kBlock + t] = acc2[q][i];
+      for (int rt = 0; rt < NHW; ++rt) xch4[(3 * kCols + NHW * q + rt) * kBlock + t] = acc2[q][rt];
+    }
     xch[(kXchSlots - 2) * kBlock + t] = db1r;
     xch[(kXchSlots - 1) * kBlock + t] = db2r;
   }
   __syncthreads();
   if (grp == 1) return;
 #pragma unroll
-  for (int q = 0; q < kMaxT1; ++q)
+  for (int q = 0; q < kCols; ++q) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) acc1[q][i] += xch[(4 * q + i) * kBlock + t];
+    for (int rt = 0; rt < 3; ++rt) acc1[q][rt] += xch4[(3 * q + rt) * kBlock + t];
 #pragma unroll
-  for (int q = 0; q < kMaxT2; ++q)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) acc2[q][i] += xch[(4 * (kMaxT1 + q) + i) * kBlock + t];
+    for (int rt = 0; rt < NHW; ++rt) acc2[q][rt] += xch4[(3 * kCols + NHW * q + rt) * kBlock + t];
+  }
   db1r += xch[(kXchSlots - 2) * kBlock + t];
   db2r += xch[(kXchSlots - 1) * kBlock + t];
   float *pp = a.part + (size_t)blockIdx.x * a.P;
 #pragma unroll
-  for (int q = 0; q < kMaxT1; ++q) {
-    const int T = w + 4 * q;
-    if (T < 3 * n1t) {
-      const int rt = T / n1t, ct = T - rt * n1t;
-      const int col = ct * 16 + lc, h = col / W, hc = col - h * W;
+  for (int q = 0; q < kCols; ++q) {
+    const int ct = w + 4 * q;
+    if (ct < n1t) {
+      const int col = ct * 16 + lc, h = ct / nhw, hc = col - h * W;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int in = rt * 16 + 4 * g + i;
-        if (in < kIn) pp[(h * kIn + in) * W + hc] = acc1[q][i];
-      }
+      for (int rt = 0; rt < 3; ++rt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int in = rt * 16 + 4 * g + i;
+          if (in < kIn) pp[(h * kIn + in) * W + hc] = acc1[q][rt][i];
+        }
     }
-  }
-#pragma unroll
-  for (int q = 0; q < kMaxT2; ++q) {
-    const int T = w + 4 * q;
-    if (T < nhw * n2t) {
-      const int rt = T / n2t, c = T - rt * n2t;
+    if (ct < n2t) {
       int col0;
-      const int h = out_head(a, c, col0);
+      const int h = out_head(a, ct, col0);
       const int col = col0 + lc, ncol = sel3(a.outs, h);
       if (col < ncol) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) pp[a.p_w2 + sel3(a.wo, h) + (rt * 16 + 4 * g + i) * ncol + col] = acc2[q][i];
+        for (int rt = 0; rt < NHW; ++rt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            pp[a.p_w2 + sel3(a.wo, h) + (rt * 16 + 4 * g + i) * ncol + col] = acc2[q][rt][i];
       }
     }
   }
@@ -766,7 +794,13 @@ int octgs_decode_bwd_rows(const octgs_anchors *an, const octgs_mlp *mlp, const o
   a.part = (float *)ws;
   a.rows = (float *)((char *)ws + rows_offset(mcap, k, W));
   a.rstride = row_len(k);
-  hipLaunchKernelGGL(k_dec_bwd, dim3(grid_for(mcap)), dim3(kDecBwdThreads), 0, (hipStream_t)stream, a);
+  const dim3 grid(grid_for(mcap)), block(kDecBwdThreads);
+  switch (W / 16) {
+    case 1: hipLaunchKernelGGL(k_dec_bwd<1>, grid, block, 0, (hipStream_t)stream, a); break;
+    case 2: hipLaunchKernelGGL(k_dec_bwd<2>, grid, block, 0, (hipStream_t)stream, a); break;
+    case 3: hipLaunchKernelGGL(k_dec_bwd<3>, grid, block, 0, (hipStream_t)stream, a); break;
+    default: hipLaunchKernelGGL(k_dec_bwd<4>, grid, block, 0, (hipStream_t)stream, a); break;
+  }
   return hipGetLastError() == hipSuccess ? OCTGS_OK : OCTGS_EHIP;
 }
 
