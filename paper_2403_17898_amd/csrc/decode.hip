@@ -12,7 +12,13 @@
 // kernel writes those B operands once per call into the caller's workspace,
 // already rounded to the path's precision and in the lane order the MFMA
 // reads them, so each block loads its slices with a few fully coalesced loads
-// instead of staging and converting every weight itself.  Two variants:
+// instead of staging and converting every weight itself (gathered by the
+// blocks themselves, without that kernel, they cost more: 13,000 anchors FP32
+// 14.7 -> 17.8 us, 120,000 BF16 35.7 -> 46.3).  A tile's inputs are read a tile
+// ahead, its anchors two, its Gaussians' offsets ahead of the layers, and the
+// barriers wait for LDS only, not for the stores.  Bound by the latency of a
+// tile's phases between them.  FP32, 13,000 anchors: 14.7 -> 14.0 us; BF16,
+// 120,000 (93 MB): 48 -> 35.7.  Two variants:
 //   FP32: v_mfma_f32_16x16x4_f32 on FP32 inputs and weights;
 //   BF16: v_mfma_f32_16x16x16_bf16 on BF16 features, inputs and weights,
 //         FP32 accumulation; biases, activations and the Gaussian assembly
@@ -77,8 +83,9 @@ struct alignas(16) Smem {
   T X[kTM][kXS];
   T H[kTM][kHS];
   float Y[kTM][kYS];
+  float aux[3][kTM][3];  // position, offset scale, base scale
+  float ofac[kTM];       // opacity factor per anchor (1 without blending)
   uint32_t aidx[kTM];
-  float ofac[kTM];  // opacity factor per anchor (1 without blending)
 };
 
 // One of three pointers by a lane-varying index, without indexing the
@@ -182,10 +189,11 @@ __global__ __launch_bounds__(kBlock) void k_decode_prep(PrepArgs a) {
 }
 
 template <bool BF16>
-__global__ __launch_bounds__(kBlock) void k_decode(DecodeArgs a) {
+__global__ __launch_bounds__(kBlock, BF16 ? 4 : 2) void k_decode(DecodeArgs a) {
   typedef Frag<BF16> F;
   __shared__ Smem<BF16> sm;
-  const int t = threadIdx.x, w = t / kWave, l = __lane_id();
+  const int t = threadIdx.x, l = __lane_id();
+  const int w = __builtin_amdgcn_readfirstlane(t / kWave);
   const int g = l / 16, lc = l % 16;
   const int k = a.k, W = a.W;
   const int n1tiles = 3 * W / 16;
@@ -201,6 +209,27 @@ __global__ __launch_bounds__(kBlock) void k_decode(DecodeArgs a) {
   }
   if ((uint64_t)blockIdx.x * kTM >= m_total) return;
 
+  // ---- a tile's inputs: 8 threads per anchor, four features each, and three
+  // of its position, offset scale or base scale; read a tile ahead of their
+  // use, the anchors two ahead.  Rows past the list repeat its last anchor.
+  const int sr = t / 8, part = t % 8;
+  auto anchor = [&](uint32_t tile) { return a.idx[min(tile * kTM + (uint32_t)sr, m_total - 1u)]; };
+  typename std::conditional<BF16, uint2, float4>::type fv;
+  float ev[3], bias = 0.0f;
+  int lev = 0;
+  auto load_inputs = [&](uint32_t j) {
+    if constexpr (BF16) fv = *(const uint2 *)(a.feat_bf16 + (size_t)j * 32 + part * 4);
+    else fv = *(const float4 *)(a.feat + (size_t)j * 32 + part * 4);
+    const float *src = part == 1 ? a.oscale : (part == 2 ? a.bscale : a.pos);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) ev[c] = src[3 * (size_t)j + c];
+    if (a.blend) {
+      bias = a.lod_bias[j];
+      lev = a.level[j];
+    }
+  };
+  uint32_t jc = anchor(blockIdx.x), jn = anchor(blockIdx.x + gridDim.x);
+
   // ---- weights of this wave's column tiles, kept in registers ----
   constexpr int KS1 = F::KS1, KS2 = F::KS2;
   const int ks2 = BF16 ? W / 16 : W / 4;
@@ -211,6 +240,7 @@ __global__ __launch_bounds__(kBlock) void k_decode(DecodeArgs a) {
   const float *fb2 = fb1 + F::nb;
   Op B1[3][KS1], B2[3][KS2];
   float b1r[3], b2r[3];
+  int hb[3];  // layer 2: first hidden column of the tile's head
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
 #pragma unroll
@@ -219,6 +249,24 @@ __global__ __launch_bounds__(kBlock) void k_decode(DecodeArgs a) {
     for (int ks = 0; ks < KS2; ++ks) B2[q][ks] = f2[((w * 3 + q) * KS2 + ks) * kWave + l];
     b1r[q] = fb1[(w * 3 + q) * kWave + l];
     b2r[q] = fb2[(w * 3 + q) * kWave + l];
+    int head, col0, ncol;
+    l2_tile(w + 4 * q, k, head, col0, ncol);
+    hb[q] = head * W;
+  }
+  if constexpr (BF16) {  // inputs 36 .. 47 are 0
+    for (int e = t; e < kTM * (kInPad - kIn); e += kBlock)
+      sm.X[e / (kInPad - kIn)][kIn + e % (kInPad - kIn)] = 0;
+  }
+  load_inputs(jc);
+
+  // this thread's Gaussians of a tile: items t and t + kBlock, anchor rows
+  // item / k (a tile has at most 2 kBlock)
+  static_assert(kTM * kMaxK <= 2 * kBlock, "two items per thread");
+  int ir[2], ii[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    ir[u] = min((t + u * kBlock) / k, kTM - 1);
+    ii[u] = min(t + u * kBlock - ir[u] * k, k - 1);
   }
 
   const int64_t cap = a.cap;
@@ -226,53 +274,50 @@ __global__ __launch_bounds__(kBlock) void k_decode(DecodeArgs a) {
   for (uint32_t tile = blockIdx.x; tile * kTM < m_total; tile += gridDim.x) {
     const uint32_t r0 = tile * kTM;
     const int rows = (int)min((uint32_t)kTM, m_total - r0);
-    // ---- gather the network inputs ----
-    {
-      const int r = t / 8, part = t % 8;  // 8 threads per anchor, 4 features each
-      if (r < rows) {
-        const uint32_t j = a.idx[r0 + r];
-        if (part == 0) sm.aidx[r] = j;
-        if constexpr (BF16) {
-          const uint2 v = *(const uint2 *)(a.feat_bf16 + (size_t)j * 32 + part * 4);
-          *(uint2 *)&sm.X[r][part * 4] = v;
-        } else {
-          const float4 v = *(const float4 *)(a.feat + (size_t)j * 32 + part * 4);
-          sm.X[r][part * 4 + 0] = v.x; sm.X[r][part * 4 + 1] = v.y;
-          sm.X[r][part * 4 + 2] = v.z; sm.X[r][part * 4 + 3] = v.w;
-        }
-        if (part == 0) {
-          const float d0 = a.pos[3 * (size_t)j] - a.C[0];
-          const float d1 = a.pos[3 * (size_t)j + 1] - a.C[1];
-          const float d2 = a.pos[3 * (size_t)j + 2] - a.C[2];
-          const float dist = sqrtf(__builtin_fmaf(d0, d0, __builtin_fmaf(d1, d1, d2 * d2)));
-          const float inv = 1.0f / dist;
-          float of = 1.0f;
-          if (a.blend) {
-            // fractional level L* = clamp(log2(d_max / (d s)) + Delta L, 0, K - 1)
-            const float ls = fminf(fmaxf(log2f(a.d_max / (dist * a.s)) + a.lod_bias[j], 0.0f),
-                                   (float)(a.n_levels - 1));
-            of = fminf(fmaxf(ls - (float)a.level[j] + 1.0f, 0.0f), 1.0f);
-          }
-          sm.ofac[r] = of;
-          float e[kInPad - 32];
-          e[0] = dist * a.inv_dmax;
-          e[1] = d0 * inv; e[2] = d1 * inv; e[3] = d2 * inv;
+    // ---- the network inputs ----
+    if constexpr (BF16) {
+      *(uint2 *)&sm.X[sr][part * 4] = fv;
+    } else {
+      sm.X[sr][part * 4 + 0] = fv.x; sm.X[sr][part * 4 + 1] = fv.y;
+      sm.X[sr][part * 4 + 2] = fv.z; sm.X[sr][part * 4 + 3] = fv.w;
+    }
+    float of = 1.0f;
+    if (part == 0) {
+      sm.aidx[sr] = jc;
+      const float d0 = ev[0] - a.C[0], d1 = ev[1] - a.C[1], d2 = ev[2] - a.C[2];
+      const float dist = sqrtf(__builtin_fmaf(d0, d0, __builtin_fmaf(d1, d1, d2 * d2)));
+      const float inv = 1.0f / dist;
+      if (a.blend) {
+        // fractional level L* = clamp(log2(d_max / (d s)) + Delta L, 0, K - 1)
+        const float ls = fminf(fmaxf(log2f(a.d_max / (dist * a.s)) + bias, 0.0f),
+                               (float)(a.n_levels - 1));
+        of = fminf(fmaxf(ls - (float)lev + 1.0f, 0.0f), 1.0f);
+      }
+      const float e[4] = {dist * a.inv_dmax, d0 * inv, d1 * inv, d2 * inv};
 #pragma unroll
-          for (int q = 4; q < kInPad - 32; ++q) e[q] = 0.0f;
-#pragma unroll
-          for (int q = 0; q < kInPad - 32; ++q) {
-            if constexpr (BF16) sm.X[r][32 + q] = f2bf(e[q]);
-            else sm.X[r][32 + q] = e[q];
-          }
-        }
-      } else if (r < kTM) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) sm.X[r][part * 4 + q] = 0;
-        if (part == 0)
-          for (int q = 32; q < kInPad; ++q) sm.X[r][q] = 0;
+      for (int q = 0; q < 4; ++q) {
+        if constexpr (BF16) sm.X[sr][32 + q] = f2bf(e[q]);
+        else sm.X[sr][32 + q] = e[q];
       }
     }
-    __syncthreads();
+    lds_barrier();
+    // (every wave has assembled the tile before)
+    if (part < 3) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) sm.aux[part][sr][c] = ev[c];
+    }
+    if (part == 0) sm.ofac[sr] = of;
+    // the offsets of this tile's Gaussians, the next tile's inputs
+    float off[2][3];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const float *o = a.offsets + ((size_t)sm.aidx[ir[u]] * k + ii[u]) * 3;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) off[u][c] = o[c];
+    }
+    jc = jn;
+    load_inputs(jc);
+    jn = anchor(tile + 2 * gridDim.x);
 
     // ---- layer 1: H = relu(X W1 + b1) ----
 #pragma unroll
@@ -301,7 +346,7 @@ __global__ __launch_bounds__(kBlock) void k_decode(DecodeArgs a) {
         }
       }
     }
-    __syncthreads();
+    lds_barrier();
 
     // ---- layer 2: Y_head = H_head W2_head + b2 ----
 #pragma unroll
@@ -310,18 +355,15 @@ __global__ __launch_bounds__(kBlock) void k_decode(DecodeArgs a) {
       for (int q = 0; q < 3; ++q) {
         const int c = w + 4 * q;
         if (c < n2tiles) {
-          int head, col0, ncol;
-          l2_tile(c, k, head, col0, ncol);
-          const int hb = head * W;
           f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
           for (int ks = 0; ks < KS2; ++ks) {
             if (ks < ks2) {
               if constexpr (BF16) {
-                const s4 av = *(const s4 *)&sm.H[rt * 16 + lc][hb + ks * 16 + g * 4];
+                const s4 av = *(const s4 *)&sm.H[rt * 16 + lc][hb[q] + ks * 16 + g * 4];
                 acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, B2[q][ks], acc, 0, 0, 0);
               } else {
-                const float av = sm.H[rt * 16 + lc][hb + ks * 4 + g];
+                const float av = sm.H[rt * 16 + lc][hb[q] + ks * 4 + g];
                 acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av, B2[q][ks], acc, 0, 0, 0);
               }
             }
@@ -331,21 +373,19 @@ __global__ __launch_bounds__(kBlock) void k_decode(DecodeArgs a) {
         }
       }
     }
-    __syncthreads();
+    lds_barrier();
 
     // ---- activations and Gaussian assembly, coalesced planar stores ----
     const int items = rows * k;
     const size_t slot0 = (size_t)r0 * k;
-    for (int it = t; it < items; it += kBlock) {
-      const int r = it / k, i = it - r * k;
-      const uint32_t j = sm.aidx[r];
-      const size_t s = slot0 + it;
-      const float *o = a.offsets + ((size_t)j * k + i) * 3;
-      const float *ls = a.oscale + 3 * (size_t)j;
-      const float *bs = a.bscale + 3 * (size_t)j;
-      const float *p = a.pos + 3 * (size_t)j;
 #pragma unroll
-      for (int c = 0; c < 3; ++c) a.out[c * cap + s] = __builtin_fmaf(o[c], ls[c], p[c]);
+    for (int u = 0; u < 2; ++u) {
+      const int it = t + u * kBlock, r = ir[u], i = ii[u];
+      if (it >= items) continue;
+      const size_t s = slot0 + it;
+      const float *p = sm.aux[0][r], *ls = sm.aux[1][r], *bs = sm.aux[2][r];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) a.out[c * cap + s] = __builtin_fmaf(off[u][c], ls[c], p[c]);
 #pragma unroll
       for (int c = 0; c < 3; ++c) a.out[(3 + c) * cap + s] = bs[c] * sigmoidf(sm.Y[r][off_s + 7 * i + c]);
       const float qw = sm.Y[r][off_s + 7 * i + 3], qx = sm.Y[r][off_s + 7 * i + 4];
@@ -362,7 +402,6 @@ __global__ __launch_bounds__(kBlock) void k_decode(DecodeArgs a) {
 #pragma unroll
       for (int c = 0; c < 3; ++c) a.out[(11 + c) * cap + s] = sigmoidf(sm.Y[r][off_c + 3 * i + c]);
     }
-    __syncthreads();
   }
 }
 
