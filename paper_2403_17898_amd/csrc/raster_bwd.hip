@@ -108,9 +108,9 @@ __device__ __forceinline__ int pair_sum_of(int l) {
 constexpr int kBwdThreads = 64;
 constexpr int kBwdBatch = 64;
 constexpr int kBPx = 4;
-// How an entry is replayed: every pixel counts it and its alphas cannot reach
-// alpha_max (may_clamp); every pixel counts it; or per pixel.
-constexpr int kBwdFree = 0, kBwdClamp = 1, kBwdCheck = 2;
+// How an entry is replayed: its alphas may reach alpha_max (may_clamp); some
+// pixel may not count it.
+constexpr int kBwdClamp = 1, kBwdCheck = 2;
 
 struct BwdLds {
   float4 sA[kBwdBatch], sB[kBwdBatch], sC[kBwdBatch];
@@ -244,7 +244,7 @@ __device__ __forceinline__ void composite_bwd_tile(const BwdArgs &a, BwdLds &lds
       float dq[kBPx];
       EntrySums o;
       o.dx = dx;
-      if (MODE == kBwdCheck) o.wr = o.wg = o.wb = 0.0f;
+      if (MODE & kBwdCheck) o.wr = o.wg = o.wb = 0.0f;
 #pragma unroll
       for (int k = 0; k < kBPx; ++k) {
         if (k > 0) {
@@ -252,10 +252,10 @@ __device__ __forceinline__ void composite_bwd_tile(const BwdArgs &a, BwdLds &lds
           d += c2;
         }
         const float a0 = __builtin_amdgcn_exp2f(p);
-        const float al = MODE == kBwdFree ? a0 : fminf(amax, a0);
+        const float al = MODE & kBwdClamp ? fminf(amax, a0) : a0;
         dq[k] = 0.0f;
         bool valid = true;
-        if (MODE == kBwdCheck) {
+        if (MODE & kBwdCheck) {
           valid = li < last[k];
           if (AMIN) valid = valid && !(al < amin);
         }
@@ -265,7 +265,7 @@ __device__ __forceinline__ void composite_bwd_tile(const BwdArgs &a, BwdLds &lds
           const float w = r * T[k];
           const float cdot = fma_(B.z, dr[k], fma_(B.w, dg[k], cblue * db[k]));
           const float u = fma_(T[k], cdot, -S[k]);
-          if (MODE == kBwdCheck || k > 0) {
+          if ((MODE & kBwdCheck) || k > 0) {
             o.wr = fma_(w, dr[k], o.wr);
             o.wg = fma_(w, dg[k], o.wg);
             o.wb = fma_(w, db[k], o.wb);
@@ -277,7 +277,7 @@ __device__ __forceinline__ void composite_bwd_tile(const BwdArgs &a, BwdLds &lds
           S[k] = fma_(w, cdot, S[k]);
           T[k] = T[k] * inv1;
           dq[k] = u * r;
-          if (MODE != kBwdFree) dq[k] = a0 <= amax ? dq[k] : 0.0f;
+          if (MODE & kBwdClamp) dq[k] = a0 <= amax ? dq[k] : 0.0f;
         }
       }
       const float q23 = dq[2] + dq[3], q123 = dq[1] + q23;
@@ -292,17 +292,17 @@ __device__ __forceinline__ void composite_bwd_tile(const BwdArgs &a, BwdLds &lds
     // later one lies past the list and no pixel counts it
     for (int j = (nb - 1) | 1; j > 0; j -= 2) {
       EntrySums hi, lo;
+      auto both = [&](auto mode) {
+        hi = entry(j, mode);
+        lo = entry(j - 1, mode);
+      };
+      const bool clamped = ((clamp >> (j - 1)) & 3u) != 0u;
       if (!AMIN && (uint32_t)(b0 + j) < mn) {
-        if ((clamp >> (j - 1)) & 3u) {
-          hi = entry(j, std::integral_constant<int, kBwdClamp>());
-          lo = entry(j - 1, std::integral_constant<int, kBwdClamp>());
-        } else {
-          hi = entry(j, std::integral_constant<int, kBwdFree>());
-          lo = entry(j - 1, std::integral_constant<int, kBwdFree>());
-        }
+        if (clamped) both(std::integral_constant<int, kBwdClamp>());
+        else both(std::integral_constant<int, 0>());
       } else {
-        hi = entry(j, std::integral_constant<int, kBwdCheck>());
-        lo = entry(j - 1, std::integral_constant<int, kBwdCheck>());
+        if (clamped) both(std::integral_constant<int, kBwdCheck | kBwdClamp>());
+        else both(std::integral_constant<int, kBwdCheck>());
       }
       const float sum = pair_sums(hi, lo, l);
       if (sum_of >= 0) (&sG[0][0])[sum_at + j] = sum;
