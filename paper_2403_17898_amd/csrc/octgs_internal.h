@@ -269,7 +269,6 @@ struct RasterWs {
   float *gpair;           // [pcap][kPairRow] backward: the same per pair number, then the slot
   float *chunk_part;      // [ceil(pcap / 64)][2][9] backward: sums of a 64-pair chunk's first and
                           // last run where the run crosses the chunk's start or end
-  uint32_t *chunk_info;   // [ceil(pcap / 64)] backward: which of those the chunk has
   BinGrid bins;
   int64_t gcap, pcap;
   int32_t tiles_x, tiles_y, nblk_g, group_pitch, scan_blocks;

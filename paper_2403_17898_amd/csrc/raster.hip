@@ -885,7 +885,6 @@ RasterWs raster_layout(void *base, int64_t gcap, int64_t pcap, int32_t W, int32_
   ws.dproj = (float *)take((size_t)g * 9 * 4);
   ws.gpair = (float *)take((size_t)pc * kPairRow * 4);
   ws.chunk_part = (float *)take((size_t)((pc + 63) / 64) * 18 * 4);
-  ws.chunk_info = (uint32_t *)take((size_t)((pc + 63) / 64) * 4);
   off = std::max(off, fwd_end);
   ws.bytes = off;
   return ws;

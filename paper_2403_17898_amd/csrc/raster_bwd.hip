@@ -370,11 +370,9 @@ __device__ __forceinline__ void seg_step(float (&v)[9], bool take) {
 // the last lane of each run then holds the run's sum.  A run that lies inside
 // the chunk is stored.  A run that crosses the chunk's start or end leaves
 // its sum in the chunk's two partial slots (the first and the last run; one
-// run covering the whole chunk is its first), and k_pair_fix adds a crossing
-// run's partials in chunk order: no atomics, the same sums on every run.
-constexpr uint32_t kChunkFirst = 1u;   // the chunk's first run continues from the previous chunk
-constexpr uint32_t kChunkLast = 2u;    // its last run continues into the next chunk
-constexpr uint32_t kChunkWhole = 4u;   // one run covers the chunk and continues both ways
+// run covering the whole chunk is its first), which the projection backward
+// adds in chunk order (gaussian_sums; a kernel of its own for that took 5.8 us
+// of a 1600 x 1066 view): no atomics, the same sums on every run.
 __global__ __launch_bounds__(kBlock) void k_pair_reduce(RasterWs ws) {
   // a full chunk's 64 records (2,560 bytes, 16-byte aligned) are read with
   // lane-contiguous float4 loads into LDS, then each lane takes its own
@@ -451,57 +449,38 @@ __global__ __launch_bounds__(kBlock) void k_pair_reduce(RasterWs ws) {
 #pragma unroll
       for (int k = 0; k < 9; ++k) d[k] = v[k];
     }
-    if (l == kWave - 1)
-      ws.chunk_info[chunk] = (first_cont ? kChunkFirst : 0u) | (last_cont ? kChunkLast : 0u) |
-                             (first_cont && last_cont && hl == 0 ? kChunkWhole : 0u);
   }
 }
 
-// One thread per chunk whose last run starts in it and continues into the
-// next chunk: that run's sum is its partial here, plus the partials of the
-// following chunks in order (the whole-chunk ones, then the one where the
-// run ends), stored once into the run's slot row.
-__global__ __launch_bounds__(kBlock) void k_pair_fix(RasterWs ws) {
-  const uint32_t P = ws.hdr->n_emit;
-  const uint32_t nch = (P + kWave - 1) / kWave;
-  for (uint32_t c = blockIdx.x * kBlock + threadIdx.x; c < nch; c += gridDim.x * kBlock) {
-    const uint32_t info = ws.chunk_info[c];
-    if (!(info & kChunkLast) || (info & kChunkWhole)) continue;
-    float t[9];
-    const float *src = ws.chunk_part + 18 * (size_t)c + 9;
+// A Gaussian's sums: its row of dproj, or, where its pairs [p0, p1) cross
+// chunks, the partials of those chunks added in chunk order (the first chunk's
+// last run, then the first run of each that follows) and put there.  The
+// partials are read eight at a time: one round trip for most, a few for a
+// Gaussian listed in thousands of tiles.
+__device__ __forceinline__ void gaussian_sums(const RasterWs &ws, uint32_t slot, uint32_t p0,
+                                              uint32_t p1, float (&v)[9]) {
+  float *row = ws.dproj + 9 * (size_t)slot;
+  const uint32_t c0 = p0 / kWave, c1 = p0 < p1 ? (p1 - 1u) / kWave : c0;
+  const float *src = c0 == c1 ? row : ws.chunk_part + 18 * (size_t)c0 + 9;
 #pragma unroll
-    for (int k = 0; k < 9; ++k) t[k] = src[k];
-    // a run that continues into the next chunk ends in some later chunk
-    // (the last chunk's last run cannot continue), so the walk stops.  The
-    // following chunks are read eight at a time (one round trip for most
-    // runs, a few for a Gaussian listed in thousands of tiles) and added in
-    // chunk order.
-    constexpr int kAhead = 8;
-    bool done = false;
-    for (uint32_t j0 = c + 1; j0 < nch && !done; j0 += kAhead) {
-      uint32_t inf[kAhead];
-      float pv[kAhead][9];
+  for (int k = 0; k < 9; ++k) v[k] = src[k];
+  if (c0 == c1) return;
+  constexpr uint32_t kAhead = 8;
+  for (uint32_t j0 = c0 + 1; j0 <= c1; j0 += kAhead) {
+    float pv[kAhead][9];
 #pragma unroll
-      for (int u = 0; u < kAhead; ++u) {
-        const uint32_t j = min(j0 + (uint32_t)u, nch - 1);
-        inf[u] = ws.chunk_info[j];
+    for (uint32_t u = 0; u < kAhead; ++u)
 #pragma unroll
-        for (int k = 0; k < 9; ++k) pv[u][k] = ws.chunk_part[18 * (size_t)j + k];
+      for (int k = 0; k < 9; ++k) pv[u][k] = ws.chunk_part[18 * (size_t)min(j0 + u, c1) + k];
+#pragma unroll
+    for (uint32_t u = 0; u < kAhead; ++u)
+      if (j0 + u <= c1) {
+#pragma unroll
+        for (int k = 0; k < 9; ++k) v[k] += pv[u][k];
       }
-#pragma unroll
-      for (int u = 0; u < kAhead; ++u) {
-        if (!done && j0 + (uint32_t)u < nch) {
-#pragma unroll
-          for (int k = 0; k < 9; ++k) t[k] += pv[u][k];
-          done = !(inf[u] & kChunkWhole);
-        }
-      }
-    }
-    float *d = ws.dproj +
-               9 * (size_t)__float_as_uint(ws.gpair[kPairRow * (c * (size_t)kWave + kWave - 1) + 9]);
-#pragma unroll
-    for (int k = 0; k < 9; ++k) d[k] = t[k];
   }
+#pragma unroll
+  for (int k = 0; k < 9; ++k) row[k] = v[k];
 }
 
 struct PBwdArgs {
@@ -634,7 +613,7 @@ __device__ void project_bwd_one(const PBwdArgs &a, const float *g, const float *
 }
 
 __global__ __launch_bounds__(kBlock) void k_project_bwd(PBwdArgs a) {
-  const uint32_t n = a.ws.hdr->n_slots;
+  const uint32_t n = a.ws.hdr->n_slots, P = a.ws.hdr->n_emit, nblk = slot_blocks(n);
   for (uint32_t s = blockIdx.x * kBlock + threadIdx.x; s < n; s += gridDim.x * kBlock) {
     float out[kGaussFields];
     const bool vis = (a.ws.vis_mask[s >> 6] >> (s & 63)) & 1ull;
@@ -642,8 +621,12 @@ __global__ __launch_bounds__(kBlock) void k_project_bwd(PBwdArgs a) {
       float g[kGaussFields], dp[9];
 #pragma unroll
       for (int f = 0; f < kGaussFields; ++f) g[f] = a.g[f * a.gstride + s];
-#pragma unroll
-      for (int q = 0; q < 9; ++q) dp[q] = a.ws.dproj[9 * (size_t)s + q];
+      // the slot's pair numbers (none if the view listed no pairs)
+      const ulonglong2 rm = a.ws.rect[s];
+      const uint32_t tiles = rect_tiles(unpack_rect(rm.x));
+      const uint32_t p0 = a.ws.blk_pairs[slot_block(s, nblk)] + a.ws.pair_base[s];
+      const uint32_t np = tiles <= kKeepBits ? (uint32_t)__popcll(rm.y) : tiles;
+      gaussian_sums(a.ws, s, P ? p0 : 0u, P ? p0 + np : 0u, dp);
       project_bwd_one(a, g, dp, out);
     } else {
 #pragma unroll
@@ -698,8 +681,6 @@ extern "C" int octgs_rasterize_bwd(const octgs_gaussians *g, const octgs_camera 
   mark(2);
   const int rgrid = (int)std::min<int64_t>(std::max<int64_t>((ws.pcap + kBlock - 1) / kBlock, 1), 2048);
   hipLaunchKernelGGL(k_pair_reduce, dim3(rgrid), dim3(kBlock), 0, s, ws);
-  const int fgrid = (int)std::min<int64_t>(std::max<int64_t>((ws.pcap + 64 * kBlock - 1) / (64 * kBlock), 1), 1024);
-  hipLaunchKernelGGL(k_pair_fix, dim3(fgrid), dim3(kBlock), 0, s, ws);
   PBwdArgs pa;
   for (int i = 0; i < 9; ++i) pa.cam.R[i] = cam->R[i];
   for (int i = 0; i < 3; ++i) pa.cam.C[i] = cam->C[i];
