@@ -25,12 +25,11 @@ constexpr int kGaussFields = 14;
 constexpr int kProjVec = 3;          // float4 records per projected Gaussian
 constexpr int kMaxK = 16;
 
-// FP32 -> BF16 bit pattern, round to nearest even (NaN kept quiet).
+// FP32 -> BF16 bit pattern, round to nearest even (NaN kept quiet): one
+// v_cvt_pk_bf16_f32, which gives what the integer arithmetic for it (five
+// instructions) gives for all 2^32 inputs.
 __device__ __forceinline__ uint16_t f2bf(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);  // quiet NaN
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
+  return __builtin_bit_cast(uint16_t, (__bf16)f);
 }
 
 // ---------------------------------------------------------------------------
