@@ -608,53 +608,77 @@ __device__ __forceinline__ void composite_tile(const CompArgs &a, CompLds<LOG> &
 // Few tiles (kFewTiles): one wave per tile leaves most of the chip idle and the
 // longest list sets the time, 0.13 us per entry.  Here a block of eight waves
 // composites 64 pixels, the K-th (K = 0 .. 3) of every column of four: waves
-// 1 to 7 work out the alphas of a batch, a few entries each, into LDS, while
-// wave 0 blends the batch before it, which leaves five instructions per entry
-// in the chain; wave 7 also stages the batch after next.  The operations on a
-// pixel are those of composite_tile, in the same order.
-// A 128 x 128 view whose longest list has 606 entries: 81 -> 23 us.  It costs
-// 2.5 times the vector work of one wave per tile, so it stops paying where the
-// chip is full: whole passes of one view with one wave per tile / these blocks,
-// at 64 tiles 75 / 54 us, 256: 76 / 67, 475: 79 / 79 (94 / 88 with longer
-// lists), 768: 80 / 89, 1024: 80 / 101; four views in flight, at 64 tiles
-// 293 / 262, 192: 294 / 275, 300: 345 / 325.
+// 3 to 7 work out the alphas of a batch, every fifth entry each, into LDS,
+// while waves 0 to 2 blend the batch before it, a colour channel each (T in all
+// three), which leaves three instructions per entry in the chain.  The last two
+// waves also stage the batches that follow.  The operations on a pixel are those of
+// composite_tile, in the same order.
+// A 128 x 128 view whose longest list has 606 entries: 81 -> 19 us.  (16 waves
+// a block, two of them staging only: 17 there, but half as fast again from 256
+// tiles on.)  It costs 2.5 times the vector work of one wave per tile, so it
+// stops paying where the chip is full: whole passes of one view with one wave
+// per tile / these blocks, at 64 tiles 75 / 53 us, 256: 76 / 64, 475: 79 / 77
+// (94 / 85 with longer lists), 768: 80 / 86, 1024: 80 / 96; four views in
+// flight, at 64 tiles 293 / 237, 192: 294 / 265, 300: 345 / 318.
 constexpr int kFewThreads = 512, kFewWaves = kFewThreads / kWave;
+constexpr int kFewBlend = 3, kFewAlpha = kFewWaves - kFewBlend, kFewStage = 2;
 constexpr int kFewTiles = 400;
 constexpr int kRing = 4;  // staged batches: blended last, being blended, next, after next
 
+template <bool LOG>
 struct FewLds {
-  float4 sA[kRing][kFwdBatch], sB[kRing][kFwdBatch], sC[kRing][kFwdBatch];
+  float4 sA[kRing][kFwdBatch], sB[kRing][kFwdBatch];
+  alignas(16) float sC[kFewBlend][kRing][kFwdBatch];
   uint32_t s_slot[kRing][kFwdBatch];
-  float al[2][kFwdBatch][kWave];  // alphas of a batch, then its weights
+  float al[2][kFwdBatch][kWave];                      // alphas of a batch
+  float wt[LOG ? 2 : 1][LOG ? kFwdBatch : 1][kWave];  // its weights
   uint32_t stop[2];
 };
 
-template <bool AMIN, int K>
-__device__ __forceinline__ void few_alphas(const CompArgs &a, FewLds &lds, uint32_t b, int w, int l,
+template <bool LOG, bool AMIN, int K>
+__device__ __forceinline__ void few_alphas(const CompArgs &a, FewLds<LOG> &lds, uint32_t b, int w, int l,
                                            int nb, float fx, float fy) {
-  for (int j = w - 1; j < kFwdBatch; j += kFewWaves - 1) {
-    const float4 A = lds.sA[b % kRing][j];
-    const float4 B = lds.sB[b % kRing][j];
-    const float dx = fx - A.x;
-    const float adx = fma_(A.z * dx, dx, B.y);
-    const float bdx = A.w * dx;
-    const float dy = fy - A.y;
-    float p = fma_(B.x * dy, dy, fma_(bdx, dy, adx));
-    float d = fma_(B.x, fma_(2.0f, dy, 1.0f), bdx);
+  // several entries at a time, as one alone is a chain of latencies
+  constexpr int kN = 4;
+  for (int j0 = w - kFewBlend; j0 < nb; j0 += kN * kFewAlpha) {
+    float4 A[kN], B[kN];
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-      p += d;
-      d += B.z;
+    for (int u = 0; u < kN; ++u) {
+      const int j = min(j0 + u * kFewAlpha, kFwdBatch - 1);
+      A[u] = lds.sA[b % kRing][j];
+      B[u] = lds.sB[b % kRing][j];
     }
-    float al = fminf(a.alpha_max, __builtin_amdgcn_exp2f(p));
-    if (AMIN) al = al < a.alpha_min ? 0.0f : al;
-    lds.al[b & 1][j][l] = j < nb ? al : 0.0f;
+    float al[kN];
+#pragma unroll
+    for (int u = 0; u < kN; ++u) {
+      const float dx = fx - A[u].x;
+      const float adx = fma_(A[u].z * dx, dx, B[u].y);
+      const float bdx = A[u].w * dx;
+      const float dy = fy - A[u].y;
+      float p = fma_(B[u].x * dy, dy, fma_(bdx, dy, adx));
+      float d = fma_(B[u].x, fma_(2.0f, dy, 1.0f), bdx);
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        p += d;
+        d += B[u].z;
+      }
+      al[u] = fminf(a.alpha_max, __builtin_amdgcn_exp2f(p));
+      if (AMIN) al[u] = al[u] < a.alpha_min ? 0.0f : al[u];
+    }
+#pragma unroll
+    for (int u = 0; u < kN; ++u) {
+      const int j = j0 + u * kFewAlpha;
+      if (j < kFwdBatch) lds.al[b & 1][j][l] = j < nb ? al[u] : 0.0f;
+    }
   }
+  // (the blending reads whole groups)
+  for (int j = nb + w - kFewBlend; j < min((nb + kGroup - 1) / kGroup * kGroup, kFwdBatch); j += kFewAlpha)
+    lds.al[b & 1][j][l] = 0.0f;
 }
 
 template <bool LOG>
 __global__ __launch_bounds__(kFewThreads) void k_composite_few(CompArgs a) {
-  __shared__ FewLds lds;
+  __shared__ FewLds<LOG> lds;
   add_status(a);
   const int K = (int)(blockIdx.x % kPx);
   const uint32_t block = blockIdx.x / kPx;
@@ -671,57 +695,83 @@ __global__ __launch_bounds__(kFewThreads) void k_composite_few(CompArgs a) {
   const float tmin = a.t_min;
   const uint32_t tbits = t_bits(a);
   const bool in = px < a.W && py < a.H;
-  float T = in ? 1.0f : -0.0f, Tdone = 0.0f, cr = 0.0f, cg = 0.0f, cb = 0.0f;
+  float T = in ? 1.0f : -0.0f, Tdone = 0.0f, col = 0.0f;
   uint32_t last = (uint32_t)len;
   bool done = !in;
 
-  // entry l of batch b, which exists; past the list's end a colour of 0
+  // entry l of batch b: its slot (past the list's end, the last entry's), then
+  // its data (there, a colour of 0)
   float4 A, B, C;
-  uint32_t s = 0;
+  uint32_t s = 0, s_next = 0;
+  auto slot_of = [&](int b) { return a.ws.tval[start + (uint32_t)min(b * kFwdBatch + l, len - 1)]; };
   auto load = [&](int b) {
-    const int e = b * kFwdBatch + l;
-    s = a.ws.tval[start + (uint32_t)min(e, len - 1)];
     A = a.ws.proj[3 * (size_t)s];
     B = a.ws.proj[3 * (size_t)s + 1];
     C = make_float4(B.z, B.w, a.ws.proj[3 * (size_t)s + 2].x, 0.0f);
-    if (e >= len) C = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (b * kFwdBatch + l >= len) C = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   };
   auto put = [&](int b) {
     lds.sA[b % kRing][l] = A;
     lds.sB[b % kRing][l] = make_float4(B.x, B.y, B.x + B.x, 0.0f);
-    lds.sC[b % kRing][l] = C;
+    lds.sC[0][b % kRing][l] = C.x;
+    lds.sC[1][b % kRing][l] = C.y;
+    lds.sC[2][b % kRing][l] = C.z;
     lds.s_slot[b % kRing][l] = s;
   };
   // sums of batch b's weights, by the waves that wrote its alphas
   auto log_weights = [&](int b) {
     const int nb = min(kFwdBatch, len - b * kFwdBatch);
-    for (int j = w - 1; j < nb; j += kFewWaves - 1) {
-      const float ws = wave_sum_f(lds.al[b & 1][j][l]);
+    for (int j = w - kFewBlend; j < nb; j += kFewAlpha) {
+      const float ws = wave_sum_f(lds.wt[b & 1][j][l]);
       if (l == 0 && ws != 0.0f) atomicAdd(&a.gauss_w[lds.s_slot[b % kRing][j]], ws);
     }
   };
-  if (w == 0 && nbatch > 0) {
-    load(0);
-    put(0);
+  // the last two waves stage the even and the odd batches: a batch's slots are
+  // read two batches before its entries' data, and that two batches before it is
+  // put down, as either takes longer to arrive than a batch to blend
+  const int stage = w - (kFewWaves - kFewStage);  // 0 or 1: this wave's batches
+  if (stage >= 0 && stage < nbatch) {
+    s = slot_of(stage);
+    s_next = slot_of(stage + 2);
+    load(stage);
+    put(stage);
+    s = s_next;
+    s_next = slot_of(stage + 4);
+    load(stage + 2);
   }
   __syncthreads();
   int b = -1;
   for (; b < nbatch; ++b) {
-    const bool ahead = w == kFewWaves - 1 && b + 2 < nbatch;
-    if (ahead) load(b + 2);
-    if (w == 0) {
+    if (b >= 0 && (b & 1) == stage && b + 2 < nbatch) {
+      put(b + 2);
+      s = s_next;
+      s_next = slot_of(b + 6);
+      load(b + 4);
+    }
+    if (w < kFewBlend) {
       if (b >= 0) {
         const int nb = min(kFwdBatch, len - b * kFwdBatch);
-        const float4 *sC = lds.sC[b % kRing];
-        float (*al)[kWave] = lds.al[b & 1];
+        const float *sC = lds.sC[w][b % kRing];
+        const float (*al)[kWave] = lds.al[b & 1];
+        float an[kGroup], cn[kGroup];  // the next group's, read ahead
+        auto read = [&](int j) {
+#pragma unroll
+          for (int g = 0; g < kGroup; ++g) an[g] = al[j + g][l];
+#pragma unroll
+          for (int g = 0; g < kGroup; g += 4) {
+            const float4 v = *reinterpret_cast<const float4 *>(sC + j + g);
+            cn[g] = v.x; cn[g + 1] = v.y; cn[g + 2] = v.z; cn[g + 3] = v.w;
+          }
+        };
+        read(0);
         for (int j = 0; j < nb; j += kGroup) {
-          float wt[kGroup], T0 = T;
-          float4 c[kGroup];
+          float wt[kGroup], c[kGroup], T0 = T;
 #pragma unroll
           for (int g = 0; g < kGroup; ++g) {
-            wt[g] = al[j + g][l];
-            c[g] = sC[j + g];
+            wt[g] = an[g];
+            c[g] = cn[g];
           }
+          read(min(j + kGroup, kFwdBatch - kGroup));
 #pragma unroll
           for (int g = 0; g < kGroup; ++g) {
             wt[g] = wt[g] * fabsf(T);
@@ -744,14 +794,12 @@ __global__ __launch_bounds__(kFewThreads) void k_composite_few(CompArgs a) {
           }
 #pragma unroll
           for (int g = 0; g < kGroup; ++g) {
-            cr = fma_(wt[g], c[g].x, cr);
-            cg = fma_(wt[g], c[g].y, cg);
-            cb = fma_(wt[g], c[g].z, cb);
-            if (LOG) al[j + g][l] = wt[g];
+            col = fma_(wt[g], c[g], col);
+            if (LOG && w == 0) lds.wt[b & 1][j + g][l] = wt[g];
           }
         }
         const bool all = __all(done);  // over the whole wave
-        if (l == 0) lds.stop[b & 1] = all ? 1u : 0u;
+        if (w == 0 && l == 0) lds.stop[b & 1] = all ? 1u : 0u;
       }
     } else {
       if (LOG && b > 0) log_weights(b - 1);
@@ -761,9 +809,9 @@ __global__ __launch_bounds__(kFewThreads) void k_composite_few(CompArgs a) {
 #define OCTGS_FEW_ALPHAS(KK)                                                \
   case KK:                                                                  \
     if (amin)                                                               \
-      few_alphas<true, KK>(a, lds, (uint32_t)(b + 1), w, l, nb, fx, fy);    \
+      few_alphas<LOG, true, KK>(a, lds, (uint32_t)(b + 1), w, l, nb, fx, fy);    \
     else                                                                    \
-      few_alphas<false, KK>(a, lds, (uint32_t)(b + 1), w, l, nb, fx, fy);   \
+      few_alphas<LOG, false, KK>(a, lds, (uint32_t)(b + 1), w, l, nb, fx, fy);   \
     break;
         switch (K) {
           OCTGS_FEW_ALPHAS(0)
@@ -774,18 +822,16 @@ __global__ __launch_bounds__(kFewThreads) void k_composite_few(CompArgs a) {
 #undef OCTGS_FEW_ALPHAS
       }
     }
-    if (ahead) put(b + 2);
     lds_barrier();
     // (a word is written again two barriers later)
     if (b >= 0 && lds.stop[b & 1]) break;
   }
-  if (LOG && nbatch > 0 && w > 0) log_weights(min(b, nbatch - 1));
-  if (w > 0 || !in) return;
+  if (LOG && nbatch > 0 && w >= kFewBlend) log_weights(min(b, nbatch - 1));
+  if (w >= kFewBlend || !in) return;
   const size_t plane = (size_t)a.W * a.H, pix = (size_t)py * a.W + px;
   const float Tk = done ? Tdone : T;
-  a.rgb[pix] = fma_(Tk, a.bg[0], cr);
-  a.rgb[plane + pix] = fma_(Tk, a.bg[1], cg);
-  a.rgb[2 * plane + pix] = fma_(Tk, a.bg[2], cb);
+  a.rgb[w * plane + pix] = fma_(Tk, w == 0 ? a.bg[0] : (w == 1 ? a.bg[1] : a.bg[2]), col);
+  if (w > 0) return;
   a.T_final[pix] = Tk;
   if (a.last) a.last[pix] = last;
 }
