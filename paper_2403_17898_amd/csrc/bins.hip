@@ -566,7 +566,7 @@ __global__ __launch_bounds__(kScanThreads) void k_tile_scan(RasterWs ws, int tra
     uint2 *out = reinterpret_cast<uint2 *>(ws.ranges) + t0;
 #pragma unroll
     for (int q = 0; q < kScanTiles; ++q) {
-      if (t0 + q < ntiles) out[q] = make_uint2(run, run + c[q]);
+      if (t0 + q < ntiles) out[q] = c[q] ? make_uint2(run, run + c[q]) : make_uint2(0u, 0u);
       run += c[q];
     }
     if (b == (uint32_t)ws.scan_blocks - 1 && t == 0) {

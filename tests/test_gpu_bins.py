@@ -94,6 +94,16 @@ def test_bin_shapes(P, orc, W, H, n, scale):
         assert (tiles <= 64).sum() > 100 and (tiles > 64).sum() > 20
 
 
+@pytest.mark.parametrize("n", [1, 64, 513, 3000])
+@pytest.mark.parametrize("neg", [0.0, 0.03, 0.5, 0.97, 1.0])
+def test_slots_without_opacity(P, orc, n, neg):
+    """Blocks in which none, few, half, most or all slots have no opacity (the
+    others are moved together)."""
+    cam = S.look_at((3.0, -20.0, 4.0), (0.0, 0.0, 0.0), 333, 200, 60.0)
+    gf = S.random_gaussians(n, cam, 7 * n, scale=(0.05, 1.5), neg_opacity_frac=neg)
+    _check(P, orc, cam, gf, f"opacity fraction {neg}")
+
+
 @pytest.mark.parametrize("n,depths", [(512, 0), (513, 0), (1025, 0), (2049, 0), (4096, 0),
                                       (4097, 0), (20000, 0), (3000, 1), (3000, 40), (9000, 7), (17000, 3)])
 def test_long_lists_and_ties(P, orc, n, depths):
