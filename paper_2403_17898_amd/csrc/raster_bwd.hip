@@ -103,7 +103,7 @@ __device__ __forceinline__ int pair_sum_of(int l) {
 // at (most of a list) need no per-pixel test, and those whose alphas cannot
 // reach alpha_max no clamp: 88 instructions per entry and 21 for its share of
 // the sums over the wave, where testing, clamping and summing each entry alone
-// took 165 together.  A 1600 x 1066 view, 0.67M pairs: 208 -> 170 us (at 85
+// took 165 together.  A 1600 x 1066 view, 0.67M pairs: 208 -> 167 us (at 91
 // registers; held to 80 and 72: 174 and 181).
 constexpr int kBwdThreads = 64;
 constexpr int kBwdBatch = 64;
@@ -650,7 +650,7 @@ extern "C" int octgs_rasterize_bwd(const octgs_gaussians *g, const octgs_camera 
                                    size_t ws_bytes, void *const *stage_events,
                                    octgs_stream stream) {
   if (!g || !cam || !p || !T_final || !last || !dL_drgb || !d_gauss || !wsp) return OCTGS_EINVAL;
-  // the pair indices of the forward's tile sort are kept only in training mode
+  // the pairs' numbers are worked out only in training mode
   if (!(p->flags & OCTGS_RASTER_TRAIN)) return OCTGS_EINVAL;
   if (!g->data || !g->count || g->capacity < 0 || g->capacity >= (int64_t(1) << 31))
     return OCTGS_EINVAL;

@@ -3,7 +3,7 @@ the views in flight on separate streams (the multi-view loss of Sec. V).
 
 Each view renders, computes its loss and runs the rasterizer backward and
 the decode backward's compute half on its own stream and buffer set, so the
-views' latency-bound kernels (scans, sorts, emission, the MLP backward)
+views' latency-bound kernels (binning, scans, the MLP backward)
 overlap.  The steps that read-modify-write arrays shared by all views, the
 decode backward's apply half into the scene gradients and the
 densification statistics, run in view order, chained by events, so the
