@@ -592,12 +592,28 @@ __global__ __launch_bounds__(kScanThreads) void k_tile_scan(RasterWs ws, int tra
     if (t == 0) ws.hdr->n_emit = ws.hdr->pair_overflow ? 0u : run;
     return;
   }
+  // long lists: their entries, kScanThreads at a time, are dealt over the blocks
+  __shared__ uint2 range[kScanThreads];
+  __shared__ uint32_t chunk0[kScanThreads];
   const uint32_t nover = ws.hdr->n_over;
   const uint32_t mb = blockIdx.x - (uint32_t)ws.scan_blocks - 1u;
   const uint32_t *key = ws.tkey, *slot = ws.bin_slot[0];
-  for (uint32_t q = 0; q < nover; ++q) {
-    const uint2 rg = ws.bin_range[ws.over_bin[q]];
-    for (uint32_t i = mb * kScanThreads + t; i < rg.y; i += kMergeBlocks * kScanThreads) {
+  for (uint32_t q0 = 0; q0 < nover; q0 += kScanThreads) {
+    const bool on = q0 + t < nover;
+    const uint2 rt = on ? ws.bin_range[ws.over_bin[q0 + t]] : make_uint2(0u, 0u);
+    uint32_t chunks;
+    const uint32_t c0 = block_scan<kScanThreads>((rt.y + kScanThreads - 1) / kScanThreads, tmp, &chunks);
+    range[t] = rt;
+    chunk0[t] = c0;
+    __syncthreads();
+    for (uint32_t u = mb; u < chunks; u += kMergeBlocks) {
+      uint32_t q = 0;  // the list of chunk u: the last that starts at or before it
+#pragma unroll
+      for (int st = kScanThreads / 2; st > 0; st >>= 1)
+        if (q0 + q + st < nover && chunk0[q + st] <= u) q += st;
+      const uint2 rg = range[q];
+      const uint32_t i = (u - chunk0[q]) * kScanThreads + t;
+      if (i >= rg.y) continue;
       const uint32_t own = i / kBinCap;
       const uint32_t k = key[rg.x + i], s = slot[rg.x + i];
       uint32_t rank = i - own * kBinCap;
@@ -607,6 +623,7 @@ __global__ __launch_bounds__(kScanThreads) void k_tile_scan(RasterWs ws, int tra
       ws.bin_slot[1][rg.x + rank] = s;
       ws.bin_mask[1][rg.x + rank] = ws.bin_mask[0][rg.x + i];
     }
+    __syncthreads();  // before the next lists take their place
   }
 }
 
