@@ -384,12 +384,12 @@ OCTGS_API size_t octgs_photometric_workspace_bytes(int64_t n_images, int32_t hei
  *   *loss += w_l1 mean|img - target| + w_ssim (1 - mean SSIM(img, target)),
  * and dimg (overwritten) = its gradient with respect to img.  img, target,
  * dimg: device, n_images planes of [height][width] FP32 (views x 3 colour
- * channels, each plane an image of its own).  SSIM is the standard form of
- * Wang et al. (2004): 11 x 11 Gaussian window with sigma 1.5, C1 = 0.01^2,
- * C2 = 0.03^2 (data range 1), windowed statistics over a zero-padded
- * same-size correlation, averaged over every pixel of every plane.  With
- * w_ssim = 0 the call is the L1 term alone and needs no workspace.  ws:
- * device, >= octgs_photometric_workspace_bytes.
+ * channels, each plane an image of its own); dimg may be img or target itself.
+ * SSIM is the standard form of Wang et al. (2004): 11 x 11 Gaussian window
+ * with sigma 1.5, C1 = 0.01^2, C2 = 0.03^2 (data range 1), windowed statistics
+ * over a zero-padded same-size correlation, averaged over every pixel of every
+ * plane.  With w_ssim = 0 the call is the L1 term alone and needs no
+ * workspace.  ws: device, >= octgs_photometric_workspace_bytes.
  * n_images <= 65535. */
 OCTGS_API int octgs_photometric_loss_grad(const float *img, const float *target,
                                           int64_t n_images, int32_t height, int32_t width,

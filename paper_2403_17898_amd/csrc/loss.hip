@@ -264,6 +264,12 @@ int64_t tile_blocks(int64_t n_images, int32_t height, int32_t width) {
 // 69 / 52, 3 x 1066 x 1600 115 / 72.
 constexpr int64_t kTileElements = 1600000;
 
+// Do the two ranges of n floats share memory?
+bool overlap(const float *a, const float *b, int64_t n) {
+  const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b, bytes = (uintptr_t)n * sizeof(float);
+  return x < y ? y - x < bytes : x - y < bytes;
+}
+
 // Stage `nmaps` planes of the (kRH x kRW) region around the block's tile
 // (zeros outside the image).
 template <int NM>
@@ -446,11 +452,10 @@ __global__ __launch_bounds__(kBlock) void k_loss_finish(const float *__restrict_
     *loss = (float)((double)*loss + (double)base + ((red[0] + red[1]) + (red[2] + red[3])));
 }
 
-// L1 only (w_ssim = 0): elementwise, four independent elements per step.
-__global__ __launch_bounds__(kBlock) void k_l1_only(const float *__restrict__ x,
-                                                    const float *__restrict__ y, int64_t n,
-                                                    float scale, float *__restrict__ dimg,
-                                                    float *__restrict__ loss) {
+// L1 only (w_ssim = 0): elementwise, four independent elements per step; dimg
+// may be x or y.
+__global__ __launch_bounds__(kBlock) void k_l1_only(const float *x, const float *y, int64_t n,
+                                                    float scale, float *dimg, float *loss) {
   __shared__ float red[4];
   float acc = 0.0f;
   const int64_t stride = (int64_t)gridDim.x * kBlock;
@@ -534,7 +539,10 @@ int octgs_photometric_loss_grad(const float *img, const float *target, int64_t n
   if (ws_bytes < octgs_photometric_workspace_bytes(n_images, height, width)) return OCTGS_ENOSPC;
   SsimArgs a;
   a.x = img; a.y = target;
-  const bool tiled = n <= kTileElements;
+  // A strip reads rows of its neighbours as halo while those write theirs, so a
+  // gradient that is written over an image takes the tiled passes: the second
+  // reads the images only where it writes.
+  const bool tiled = n <= kTileElements || overlap(dimg, img, n) || overlap(dimg, target, n);
   a.m0 = (float *)ws; a.m1 = a.m0 + n; a.m2 = a.m1 + n;
   a.part = tiled ? a.m2 + n : (float *)ws;
   a.dimg = dimg; a.loss = loss;

@@ -86,6 +86,27 @@ def test_photometric_strip_edges(P, LO, hw):
         assert np.abs(g - rg).max() <= 1e-3 * np.abs(rg).max()
 
 
+@pytest.mark.parametrize("planes,hw", [(3, (97, 131)), (3, (720, 1280)), (2, (1301, 1417))])
+@pytest.mark.parametrize("over", ["img", "target"])
+def test_photometric_in_place(P, LO, planes, hw, over):
+    """The gradient written over the image or the target: the same as beside
+    them, below and above the size that is done in tiles.  Bars of the parity
+    test."""
+    img, tgt = _images((planes,) + hw, 17 * hw[0] + hw[1])
+    for w_ssim in (0.2, 0.0):
+        say("photometric in place", planes, hw, over, w_ssim)
+        x, y = torch.as_tensor(img).cuda(), torch.as_tensor(tgt).cuda()
+        d = x if over == "img" else y
+        loss = torch.zeros(1, dtype=torch.float32, device="cuda")
+        P.photometric_loss_grad(x, y, d, loss, 0.8, w_ssim)
+        torch.cuda.synchronize()
+        g = d.cpu().numpy().astype(np.float64)
+        rl, rg = LO.photometric_loss_grad(img, tgt, 0.8, w_ssim)
+        assert abs(float(loss.item()) - rl) <= 2e-6
+        assert np.linalg.norm(g - rg) <= 1e-4 * np.linalg.norm(rg)
+        assert np.abs(g - rg).max() <= 1e-3 * np.abs(rg).max()
+
+
 def test_l1_only_and_identity(P, LO):
     img, tgt = _images((2, 3, 40, 70), 5)
     loss, g = _run(P, img, tgt, 1.0, 0.0)
