@@ -14,7 +14,7 @@
 // with A1 = 2 mu_x mu_y + C1, A2 = 2 s_xy + C2, B1 = mu_x^2 + mu_y^2 + C1,
 // B2 = s_xx + s_yy + C2, so dS/dx = w * m0 + 2 x (w * m1) + y (w * m2).
 //
-// Large images: one kernel does both correlations.  A block of 256 threads walks down a
+// Large images (tiles_cheaper): one kernel does both correlations.  A block of 256 threads walks down a
 // strip of kOutW = 236 output columns (236 + 2 x 10 image columns, one per
 // thread), two image rows per step:
 //   - the rows' (m, d, m^2, d^2) with m = (x + y) / 2 and d = x - y go to LDS
@@ -259,10 +259,28 @@ int64_t tile_blocks(int64_t n_images, int32_t height, int32_t width) {
   return (int64_t)((width + kSW - 1) / kSW) * ((height + kSH - 1) / kSH) * n_images;
 }
 
-// Largest call done in tiles.  Measured (us, tiles / strips): 3 x 51 x 88 15 / 24,
-// 3 x 480 x 640 35 / 48, 3 x 540 x 960 (1.56M) 42 / 43, 3 x 720 x 1280 (2.76M)
-// 69 / 52, 3 x 1066 x 1600 115 / 72.
+// Tiles or strips, whichever has less to do for the planes at hand: a strip is
+// 256 columns wide however narrow its plane, so what counts is the padded work,
+// not the pixels.  Either form costs what its fullest compute unit runs, a
+// strip 0.87 us per step of two rows and a tile (both passes) 5.5 us, and the
+// tiles 4 us more around that (a second launch, three maps).  Calls of up to
+// 1.6M elements stay in tiles: there the strips' steps, one after the other, are
+// no less than the tiles even where they fill the chip.  Measured (us, tiles /
+// strips):
+//   3 x 51 x 88 15 / 24, 3 x 480 x 640 35 / 48, 3 x 540 x 960 (1.56M) 42 / 43;
+//   wide planes: 3 x 720 x 1280 73 / 52, 3 x 1066 x 1600 122 / 72, 3 x 600 x
+//     4000 167 / 124, 2 x 900 x 1000 52 / 42, 6 x 500 x 600 55 / 42;
+//   narrow ones: 400 x 64 x 64 51 / 89, 1,600 x 32 x 32 78 / 286, 7,000 x 16 x 16
+//     148 / 486, 16 x 1000 x 128 56 / 78, 3 x 20000 x 64 92 / 137, 24 x 300 x 240
+//     55 / 78 (two strips of 236 columns), 12 x 400 x 480 65 / 78;
+//   alike: 12 x 400 x 472 64 / 64, 48 x 200 x 200 66 / 64, 3 x 2000 x 300 55 / 51.
 constexpr int64_t kTileElements = 1600000;
+
+bool tiles_cheaper(int64_t n_images, int32_t height, int32_t width) {
+  const int64_t cus = 256, steps = strip_rows(n_images, height, width) / 2 + kTaps;
+  const int64_t strips = (ssim_blocks(n_images, height, width) + cus - 1) / cus * steps;
+  return tile_blocks(n_images, height, width) * (5.5 / cus) + 4.0 <= strips * 0.87;
+}
 
 // Do the two ranges of n floats share memory?
 bool overlap(const float *a, const float *b, int64_t n) {
@@ -541,8 +559,10 @@ int octgs_photometric_loss_grad(const float *img, const float *target, int64_t n
   a.x = img; a.y = target;
   // A strip reads rows of its neighbours as halo while those write theirs, so a
   // gradient that is written over an image takes the tiled passes: the second
-  // reads the images only where it writes.
-  const bool tiled = n <= kTileElements || overlap(dimg, img, n) || overlap(dimg, target, n);
+  // reads the images only where it writes.  (Planes too high for a grid of tiles
+  // are left to the strips.)
+  const bool tiled = n <= kTileElements || overlap(dimg, img, n) || overlap(dimg, target, n) ||
+                     ((height + kSH - 1) / kSH <= 65535 && tiles_cheaper(n_images, height, width));
   a.m0 = (float *)ws; a.m1 = a.m0 + n; a.m2 = a.m1 + n;
   a.part = tiled ? a.m2 + n : (float *)ws;
   a.dimg = dimg; a.loss = loss;

@@ -86,6 +86,48 @@ def test_photometric_strip_edges(P, LO, hw):
         assert np.abs(g - rg).max() <= 1e-3 * np.abs(rg).max()
 
 
+@pytest.mark.parametrize("planes,hw", [(3, (720, 1180)), (3, (719, 1181)), (3, (731, 1179)),
+                                       (1600, (32, 32)), (3, (9000, 65))])
+def test_photometric_wide_and_narrow(P, LO, planes, hw):
+    """Calls past 1.6M elements: planes of five strips of 236 columns, one
+    column more and less (strips), and narrow ones (tiles).  Bars of the parity
+    test."""
+    img, tgt = _images((planes,) + hw, hw[0] + hw[1])
+    say("photometric wide and narrow", planes, hw)
+    loss, g = _run(P, img, tgt, 0.8, 0.2)
+    rl, rg = LO.photometric_loss_grad(img, tgt, 0.8, 0.2)
+    assert abs(loss - rl) <= 2e-6
+    assert np.linalg.norm(g - rg) <= 1e-4 * np.linalg.norm(rg)
+    assert np.abs(g - rg).max() <= 1e-3 * np.abs(rg).max()
+
+
+@pytest.mark.parametrize("planes,hw", [(1600, (32, 32)), (7000, (16, 16)), (60, (1000, 40))])
+def test_photometric_narrow_time(P, planes, hw):
+    """Many narrow planes in one call take no longer than in two calls of half
+    of them (which are done in tiles); 236-column strips took 1.35 to 3.6 times
+    as long."""
+    x, y = torch.rand((planes,) + hw, device="cuda"), torch.rand((planes,) + hw, device="cuda")
+    d, loss = torch.empty_like(x), torch.zeros(1, device="cuda")
+    ws = P.photometric_loss_grad(x, y, d, loss)
+
+    def best(parts):
+        us = []
+        for _ in range(12):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for i in parts:
+                P.photometric_loss_grad(x[i], y[i], d[i], loss, ws=ws)
+            b.record()
+            b.synchronize()
+            us.append(1e3 * a.elapsed_time(b))
+        return min(us)
+
+    h = planes // 2
+    whole, halves = best([slice(None)]), best([slice(0, h), slice(h, None)])
+    say(f"photometric narrow {planes} x {hw}: {whole:.0f} us, in halves {halves:.0f}")
+    assert whole <= 1.25 * halves
+
+
 @pytest.mark.parametrize("planes,hw", [(3, (97, 131)), (3, (720, 1280)), (2, (1301, 1417))])
 @pytest.mark.parametrize("over", ["img", "target"])
 def test_photometric_in_place(P, LO, planes, hw, over):
