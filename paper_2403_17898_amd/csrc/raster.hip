@@ -448,6 +448,12 @@ __device__ __forceinline__ void add_status(const CompArgs &a) {
   }
 }
 
+// May a pixel blend on with T < 0?  There w = a |T| has the wrong sign, and is
+// put right one entry at a time (t_bits has every entry looked at).
+__host__ __device__ __forceinline__ bool negative_t(const CompArgs &a) {
+  return !(a.alpha_max <= 1.0f) && a.t_min < 0.0f;
+}
+
 // T as an integer below this may have crossed t_min; 0 <= T <= 1 unless
 // alpha_max > 1.
 __device__ __forceinline__ uint32_t t_bits(const CompArgs &a) {
@@ -547,6 +553,7 @@ __device__ __forceinline__ void composite_tile(const CompArgs &a, CompLds<LOG> &
           float Tk = T0[k];
 #pragma unroll
           for (int g = 0; g < G; ++g) {
+            if (G == 1) w[g][k] = Tk < 0.0f ? -w[g][k] : w[g][k];
             w[g][k] = live ? w[g][k] : 0.0f;
             Tk -= w[g][k];
             const bool now = live && Tk < tmin;
@@ -581,7 +588,8 @@ __device__ __forceinline__ void composite_tile(const CompArgs &a, CompLds<LOG> &
     typedef std::integral_constant<int, 1> One;
     int j = 0;
     bool stop = false;
-    for (; j + kGroup <= nb && (LOG || !stop); j += kGroup)
+    const int ng = negative_t(a) ? 0 : nb;  // entries that may go in groups
+    for (; j + kGroup <= ng && (LOG || !stop); j += kGroup)
       stop = (uint32_t)(clamp >> j) & ((1u << kGroup) - 1u)
                  ? step(j, Group(), std::true_type())
                  : step(j, Group(), std::false_type());
@@ -678,7 +686,7 @@ __device__ __forceinline__ void few_alphas(const CompArgs &a, FewLds<LOG> &lds, 
     lds.al[b & 1][j][l] = 0.0f;
 }
 
-template <bool LOG>
+template <bool LOG, bool NEG>
 __global__ __launch_bounds__(kFewThreads) void k_composite_few(CompArgs a) {
   __shared__ FewLds<LOG> lds;
   add_status(a);
@@ -784,6 +792,7 @@ __global__ __launch_bounds__(kFewThreads) void k_composite_few(CompArgs a) {
             float Tk = T0;
 #pragma unroll
             for (int g = 0; g < kGroup; ++g) {
+              if (NEG) wt[g] = al[j + g][l] * Tk;  // negative_t
               wt[g] = live ? wt[g] : 0.0f;
               Tk -= wt[g];
               const bool now = live && Tk < tmin;
@@ -1033,10 +1042,9 @@ int octgs_rasterize_fwd(const octgs_gaussians *g, const octgs_camera *cam,
   mark(8);
   const uint32_t blocks = tile_grid_blocks(ws.tiles_x, ws.tiles_y);
   if ((int64_t)ws.tiles_x * ws.tiles_y <= kFewTiles) {
-    if (gauss_w)
-      hipLaunchKernelGGL(k_composite_few<true>, dim3(kPx * blocks), dim3(kFewThreads), 0, s, ca);
-    else
-      hipLaunchKernelGGL(k_composite_few<false>, dim3(kPx * blocks), dim3(kFewThreads), 0, s, ca);
+    const auto few = negative_t(ca) ? (gauss_w ? k_composite_few<true, true> : k_composite_few<false, true>)
+                                    : (gauss_w ? k_composite_few<true, false> : k_composite_few<false, false>);
+    hipLaunchKernelGGL(few, dim3(kPx * blocks), dim3(kFewThreads), 0, s, ca);
   } else {
     if (gauss_w)
       hipLaunchKernelGGL(k_composite<true>, dim3(blocks), dim3(kFwdThreads), 0, s, ca);

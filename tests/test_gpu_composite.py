@@ -91,3 +91,33 @@ def test_backward_entry_modes(P, orc, W, n, opacity, kw):
     got = _np(vb.dgauss).astype(np.float64)
     for a, b in ((0, 3), (3, 6), (6, 10), (10, 11), (11, 14)):
         assert np.linalg.norm(got[a:b] - want[a:b]) <= 1e-3 * np.linalg.norm(want[a:b]), (a, b)
+
+
+@pytest.mark.parametrize("W", [320, 336])
+@pytest.mark.parametrize("n,opacity,t_min", [(9, (0.9, 1.4), -0.05), (40, (0.6, 1.4), -0.2),
+                                             (130, (0.3, 1.4), -10.0)])
+def test_negative_transmittance(P, orc, W, n, opacity, t_min):
+    """alpha_max > 1 with t_min < 0: pixels blend on with T < 0.  Bars of the
+    first test."""
+    H = 320
+    kw = {"alpha_max": 1.5, "t_min": t_min}
+    cam = S.look_at((0.0, -8.0, 0.0), (0.0, 0.0, 0.0), W, H, 60.0)
+    gf = S.random_gaussians(n, cam, 31 * n + W, depth=(4.0, 9.0), scale=(0.4, 3.0), margin=0.0,
+                            opacity=opacity)
+    say("composite T < 0", W, H, n, opacity, t_min)
+    ref = orc.rasterize(gf, cam, orc.params_array(**kw), weights=True)
+    assert (ref["T"] < 0).any()
+    for log in (False, True):
+        vb = P.ViewBuffers(n, 1, W, H, max(1, ref["bs"]["n_rect_pairs"]), gauss_capacity=n,
+                           log_weights=log)
+        vb.gauss.copy_(torch.as_tensor(gf).cuda())
+        vb.gauss_count.fill_(n)
+        vb.rasterize(P.make_camera(cam), P.raster_params(train=True, **kw))
+        torch.cuda.synchronize()
+        same = _np(vb.last) == ref["last"]
+        assert same.mean() >= 0.999
+        assert np.abs(_np(vb.rgb) - ref["img"])[:, same].max() <= 1e-4
+        assert np.abs(_np(vb.T) - ref["T"])[same].max() <= 1e-4
+        if log:
+            np.testing.assert_allclose(_np(vb.gauss_w).astype(np.float64), ref["weights"],
+                                       rtol=2e-4, atol=2e-4 * np.abs(ref["weights"]).max())
