@@ -416,16 +416,22 @@ struct CompArgs {
 // t_min.  Entries go in groups of kGroup: the weights of all of them are
 // worked out as if no pixel got done in the group; as T only falls, one
 // integer minimum over the thread's pixels at the group's end and one compare
-// tell if that holds, and if not (or if alpha_max lets T go negative) the
-// group's T are walked again and the weights past t_min cleared.  So an entry
-// costs no select and no compare of its own, and the alphas of a group do not
-// wait for each other.  min(alpha_max, .) is left out for groups of entries
-// whose exponent cannot reach log2(alpha_max) in this tile (may_clamp).
+// tell if that holds, and if not the pixels of which some lane got done are
+// walked again: as T falls on, the entries that leave it below t_min are the
+// group's last ones, so each compare stands for itself and no chain of them
+// forms.  So an entry costs no select and no compare of its own, and the alphas
+// of a group do not wait for each other.  min(alpha_max, .) is left out for
+// groups of entries whose exponent cannot reach log2(alpha_max) in this tile
+// (may_clamp).  Where alphas may lie outside [0, 1] (t_falls) entries go one at a
+// time, with a select and a compare each (step_any).
 // Bound by vector issue (about 40 instructions per entry of four pixels a
-// lane; 54 with the selects).  3840 x 2160, 2.3M pairs: 215 -> 190 us; 1920 x
-// 1080, 0.86M: 97 -> 87; a training view of 1600 x 1066, 0.67M: 77 -> 66.
-// Groups of 2, 4, 8 and 16 take 100, 92, 87 and 93 us at 1920 x 1080.  Five
-// waves per SIMD (96 registers) suffice; six or eight spill.
+// lane; 54 with the selects).  3840 x 2160, 2.3M pairs: 215 -> 187 us; 1920 x
+// 1080, 0.86M: 97 -> 85; a training view of 1600 x 1066, 0.67M: 77 -> 64.  Lists
+// of about 1,000 entries in 725 tiles, in most groups of which some pixel gets
+// done (300k Gaussians within 400 x 400 px): 244 with a select per entry, 283
+// where the walk kept a chain of done flags for all four pixels, 242 now.
+// Groups of 2, 4, 8 and 16 take 100, 92, 87 and 93 us at 1920 x 1080.  Four
+// waves per SIMD (117 registers): held to five the walk's values spill.
 constexpr int kFwdThreads = 64;
 constexpr int kFwdBatch = 64;     // list entries staged in LDS per batch, one per lane
 constexpr int kPx = 4;            // pixels of a column
@@ -448,16 +454,14 @@ __device__ __forceinline__ void add_status(const CompArgs &a) {
   }
 }
 
-// May a pixel blend on with T < 0?  There w = a |T| has the wrong sign, and is
-// put right one entry at a time (t_bits has every entry looked at).
-__host__ __device__ __forceinline__ bool negative_t(const CompArgs &a) {
-  return !(a.alpha_max <= 1.0f) && a.t_min < 0.0f;
+// T only falls and stays in [0, 1], as alphas lie in [0, 1].
+__host__ __device__ __forceinline__ bool t_falls(const CompArgs &a) {
+  return a.alpha_max >= 0.0f && a.alpha_max <= 1.0f;
 }
 
-// T as an integer below this may have crossed t_min; 0 <= T <= 1 unless
-// alpha_max > 1.
+// Where t_falls: T as an integer below this has crossed t_min.
 __device__ __forceinline__ uint32_t t_bits(const CompArgs &a) {
-  return !(a.alpha_max <= 1.0f) ? ~0u : (a.t_min > 0.0f ? __float_as_uint(a.t_min) : 0u);
+  return a.t_min > 0.0f ? __float_as_uint(a.t_min) : 0u;
 }
 
 // The LDS lives in the kernel and is passed in, so the instantiations share
@@ -480,6 +484,7 @@ __device__ __forceinline__ void composite_tile(const CompArgs &a, CompLds<LOG> &
   const float4 *proj = a.ws.proj;
   const float amax = a.alpha_max, amin = a.alpha_min, tmin = a.t_min;
   const uint32_t tbits = t_bits(a);
+  const bool falling = t_falls(a);
   const float lamax = log2f(amax);
   float T[kPx], Tdone[kPx], cr[kPx], cg[kPx], cb[kPx];
   uint32_t last[kPx];
@@ -546,23 +551,27 @@ __device__ __forceinline__ void composite_tile(const CompArgs &a, CompLds<LOG> &
       for (int k = 0; k < kPx; ++k) low = min(low, __float_as_uint(T[k]));
       bool stop = false;
       if (ballot(low < tbits) != 0ull) {
-        // `last` is the entry that took T below t_min, else the list length
+        // as T only falls, the entries that a pixel counts are those before the
+        // first that leaves it below t_min, and that one; `last` is that
+        // entry, else the list length
 #pragma unroll
         for (int k = 0; k < kPx; ++k) {
-          bool live = !(done & (1u << k));
-          float Tk = T0[k];
+          if (ballot(__float_as_uint(T[k]) < tbits) == 0ull) continue;
+          float Tg = T0[k], Te = T0[k];  // as if no pixel got done; left at
+          bool under = false;            // false where done (T0 = -0, w = 0)
+          uint32_t left = 0;
 #pragma unroll
           for (int g = 0; g < G; ++g) {
-            if (G == 1) w[g][k] = Tk < 0.0f ? -w[g][k] : w[g][k];
-            w[g][k] = live ? w[g][k] : 0.0f;
-            Tk -= w[g][k];
-            const bool now = live && Tk < tmin;
-            if (LAST) last[k] = now ? base + (uint32_t)(j + g) : last[k];
-            live = live && !now;
+            Tg -= w[g][k];
+            Te = under ? Te : Tg;
+            w[g][k] = under ? 0.0f : w[g][k];
+            under = __float_as_uint(Tg) < tbits;
+            if (LAST) left += under ? 1u : 0u;
           }
-          Tdone[k] = live || (done & (1u << k)) ? Tdone[k] : Tk;
-          T[k] = live ? Tk : -0.0f;
-          done |= live ? 0u : 1u << k;
+          if (LAST) last[k] = under ? base + (uint32_t)(j + G) - left : last[k];
+          Tdone[k] = under ? Te : Tdone[k];
+          T[k] = under ? -0.0f : T[k];
+          done |= under ? 1u << k : 0u;
         }
         stop = __all(done == kAll);
       }
@@ -584,12 +593,50 @@ __device__ __forceinline__ void composite_tile(const CompArgs &a, CompLds<LOG> &
       }
       return stop;
     };
+    // one entry, any alpha_max and t_min: T may be negative and rise again
+    auto step_any = [&](int j) -> bool {
+      const float4 A = sA[j], B = sB[j], C = sC[j];
+      const float dx = fx - A.x;
+      const float adx = fma_(A.z * dx, dx, B.y);
+      const float bdx = A.w * dx;
+      const float dy = fy - A.y;
+      float p = fma_(B.x * dy, dy, fma_(bdx, dy, adx));
+      float d = fma_(B.x, fma_(2.0f, dy, 1.0f), bdx);
+      float wsum = 0.0f;
+#pragma unroll
+      for (int k = 0; k < kPx; ++k) {
+        if (k > 0) {
+          p += d;
+          d += B.z;
+        }
+        float al = fminf(amax, __builtin_amdgcn_exp2f(p));
+        if (AMIN) al = al < amin ? 0.0f : al;
+        const bool live = !(done & (1u << k));
+        const float w = live ? al * T[k] : 0.0f;
+        T[k] -= w;
+        cr[k] = fma_(w, C.x, cr[k]);
+        cg[k] = fma_(w, C.y, cg[k]);
+        cb[k] = fma_(w, C.z, cb[k]);
+        if (LOG) wsum += w;
+        if (live && T[k] < tmin) {
+          if (LAST) last[k] = base + (uint32_t)j;
+          Tdone[k] = T[k];
+          done |= 1u << k;
+        }
+      }
+      if (LOG) {
+        const float ws = wave_sum_f(wsum);
+        if (__lane_id() == 0) s_w[j] = ws;
+      }
+      return __all(done == kAll);
+    };
     typedef std::integral_constant<int, kGroup> Group;
     typedef std::integral_constant<int, 1> One;
     int j = 0;
     bool stop = false;
-    const int ng = negative_t(a) ? 0 : nb;  // entries that may go in groups
-    for (; j + kGroup <= ng && (LOG || !stop); j += kGroup)
+    if (!falling)
+      for (; j < nb && (LOG || !stop); ++j) stop = step_any(j);
+    for (; j + kGroup <= nb && (LOG || !stop); j += kGroup)
       stop = (uint32_t)(clamp >> j) & ((1u << kGroup) - 1u)
                  ? step(j, Group(), std::true_type())
                  : step(j, Group(), std::false_type());
@@ -686,7 +733,9 @@ __device__ __forceinline__ void few_alphas(const CompArgs &a, FewLds<LOG> &lds, 
     lds.al[b & 1][j][l] = 0.0f;
 }
 
-template <bool LOG, bool NEG>
+// ANY: for alphas outside [0, 1] (t_falls), where T may be negative and rise
+// again; the blending waves then go entry by entry.
+template <bool LOG, bool ANY>
 __global__ __launch_bounds__(kFewThreads) void k_composite_few(CompArgs a) {
   __shared__ FewLds<LOG> lds;
   add_status(a);
@@ -787,12 +836,12 @@ __global__ __launch_bounds__(kFewThreads) void k_composite_few(CompArgs a) {
             wt[g] = wt[g] * fabsf(T);
             T -= wt[g];
           }
-          if (ballot(__float_as_uint(T) < tbits) != 0ull) {
+          if (ANY || ballot(__float_as_uint(T) < tbits) != 0ull) {
             bool live = !done;
             float Tk = T0;
 #pragma unroll
             for (int g = 0; g < kGroup; ++g) {
-              if (NEG) wt[g] = al[j + g][l] * Tk;  // negative_t
+              if (ANY) wt[g] = al[j + g][l] * Tk;
               wt[g] = live ? wt[g] : 0.0f;
               Tk -= wt[g];
               const bool now = live && Tk < tmin;
@@ -848,7 +897,7 @@ __global__ __launch_bounds__(kFewThreads) void k_composite_few(CompArgs a) {
 }
 
 template <bool LOG>
-__global__ __launch_bounds__(kFwdThreads, LOG ? 1 : 5) void k_composite(CompArgs a) {
+__global__ __launch_bounds__(kFwdThreads, LOG ? 1 : 4) void k_composite(CompArgs a) {
   __shared__ CompLds<LOG> lds;
   add_status(a);
   // a render that no backward follows may leave out the per-pixel entry count
@@ -1042,8 +1091,8 @@ int octgs_rasterize_fwd(const octgs_gaussians *g, const octgs_camera *cam,
   mark(8);
   const uint32_t blocks = tile_grid_blocks(ws.tiles_x, ws.tiles_y);
   if ((int64_t)ws.tiles_x * ws.tiles_y <= kFewTiles) {
-    const auto few = negative_t(ca) ? (gauss_w ? k_composite_few<true, true> : k_composite_few<false, true>)
-                                    : (gauss_w ? k_composite_few<true, false> : k_composite_few<false, false>);
+    const auto few = t_falls(ca) ? (gauss_w ? k_composite_few<true, false> : k_composite_few<false, false>)
+                                 : (gauss_w ? k_composite_few<true, true> : k_composite_few<false, true>);
     hipLaunchKernelGGL(few, dim3(kPx * blocks), dim3(kFewThreads), 0, s, ca);
   } else {
     if (gauss_w)

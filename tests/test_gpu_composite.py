@@ -121,3 +121,31 @@ def test_negative_transmittance(P, orc, W, n, opacity, t_min):
         if log:
             np.testing.assert_allclose(_np(vb.gauss_w).astype(np.float64), ref["weights"],
                                        rtol=2e-4, atol=2e-4 * np.abs(ref["weights"]).max())
+
+
+def test_scattered_stops(P, orc):
+    """Lists of several hundred small Gaussians each, so that pixels get done one
+    here, one there: in most groups of entries, several of a lane in one group.
+    Every entry count equal but for the pixels whose stop decision is within
+    rounding; other bars of the first test."""
+    W, H, n = 480, 352, 120000
+    cam = S.look_at((0.0, -8.0, 0.0), (0.0, 0.0, 0.0), W, H, 60.0)
+    gf = S.random_gaussians(n, cam, 11, depth=(4.0, 9.0), scale=(0.01, 0.06), margin=0.0,
+                            opacity=(0.05, 1.0))
+    say("composite scattered stops")
+    ref = orc.rasterize(gf, cam, orc.params_array())
+    stops = ref["last"][:H, :W].astype(np.int64)
+    length = (ref["bs"]["ranges"][:, 1].astype(np.int64) - ref["bs"]["ranges"][:, 0]).reshape(H // 16, W // 16)
+    done = stops < np.kron(length, np.ones((16, 16), np.int64))
+    tile = stops[160:176, 160:176][done[160:176, 160:176]]
+    assert len(set(((tile - 1) // 8).tolist())) >= 20  # groups of one tile in which a pixel stops
+    for order in (False, True):
+        vb = P.ViewBuffers(n, 1, W, H, ref["bs"]["n_rect_pairs"], gauss_capacity=n)
+        vb.gauss.copy_(torch.as_tensor(gf).cuda())
+        vb.gauss_count.fill_(n)
+        vb.rasterize(P.make_camera(cam), P.raster_params(tile_order=order))
+        torch.cuda.synchronize()
+        same = _np(vb.last) == ref["last"]
+        assert same.mean() >= 0.999
+        assert np.abs(_np(vb.rgb) - ref["img"])[:, same].max() <= 1e-4
+        assert np.abs(_np(vb.T) - ref["T"])[same].max() <= 1e-4
