@@ -5,17 +5,22 @@
 // grouped by screen bin.  Here:
 //   k_bin_sort    one block per bin collects the bin's entries, sorts them by
 //                 (depth bits, slot) in LDS, works out which of the bin's
-//                 tiles each is listed in and counts the tiles' entries;
-//   k_tile_scan   exclusive scan of the counts in tile order: each tile's
-//                 range (and, in training, the blocks' pair numbers); its
-//                 other blocks merge the sorted runs of bins whose list is
-//                 longer than one block sorts at once;
+//                 tiles each is listed in and counts the tiles' entries; a bin
+//                 with more entries than one block sorts at once is put on a
+//                 list instead;
+//   k_tile_scan   first, by all its blocks together, those long bins: their
+//                 entries to memory, then, a slice of the depths per block,
+//                 sorted and counted; then the exclusive scan of the counts in
+//                 tile order: each tile's range (and, in training, the blocks'
+//                 pair numbers);
 //   k_tile_lists  one block per bin writes its tiles' lists in depth order:
 //                 a wave takes a tile and compacts the bin's ordered entries
-//                 by ballots, so all writes are in place and in order.
-// No sort pass over pairs, no look-back chain over hundreds of partitions:
-// the only waits on other blocks are the tile scan's (one block per 8,192
-// tiles), bounded and on blocks that already run.
+//                 by ballots, so all writes are in place and in order; a long
+//                 bin is done slice by slice.
+// No sort pass over pairs, no look-back chain over hundreds of partitions: the
+// waits on other blocks are the tile scan's (one block per 8,192 tiles) and,
+// where there are long bins, those for units of work that running blocks have
+// taken.  All are bounded.
 #include "octgs_internal.h"
 
 namespace octgs {
@@ -55,7 +60,7 @@ struct BinSmem {
   uint32_t tmp[kNW], ltmp[kNW];
   uint32_t tcnt[32];
   unsigned long long cand;
-  uint32_t vis, m, diff, flag, base, unknown;
+  uint32_t vis, m, run, diff, flag, base, unknown, unit;
 };
 
 // Index of the last of pre[0..kRound) that is <= i (pre[0] = 0, nondecreasing).
@@ -67,35 +72,36 @@ __device__ __forceinline__ uint32_t owner_of(const uint32_t *pre, uint32_t i) {
   return lo;
 }
 
-// All entries of a bin, in no particular order, handed to put(position, depth
-// key, slot, tiles); returns their number.  local: the bin's index in its band.  On
-// the first call (TOTALS) also the view's candidate and survivor counts into
-// sm.cand and sm.vis.  Everything that one slot block says about the bin is
-// loaded at once, then all entries and large survivors: two dependent round
-// trips for up to 2,048 blocks.
-template <bool TOTALS, typename Put>
-__device__ __forceinline__ uint32_t collect(const RasterWs &ws, BinSmem &sm, int local, uint32_t bx,
-                                            uint32_t by, uint32_t nblk, bool mine, Put put) {
+// All entries of a bin from slot blocks [b0, b1), in no particular order, handed
+// to put(position, depth key, slot, tiles).  local: the bin's index in its band.
+// Positions come from take(n): the first of n, asked for by one thread.  COUNT:
+// positions count from 0 in sm.m, which ends as the number of entries; once they
+// are more than kBinCap only that number is of use, and the grouped ones are not
+// read; also the view's candidate and survivor counts into sm.cand and sm.vis.
+// Everything that one slot block says about the bin is loaded at once, then all
+// entries and large survivors: two dependent round trips for up to 2,048 blocks.
+template <bool COUNT, typename Take, typename Put>
+__device__ __forceinline__ void collect(const RasterWs &ws, BinSmem &sm, int local, uint32_t bx,
+                                        uint32_t by, uint32_t b0, uint32_t b1, bool mine, Take take,
+                                        Put put) {
   const int t = threadIdx.x, w = t / kWave, l = __lane_id();
-  if (t == 0) {
+  if (COUNT && t == 0) {
     sm.m = 0u;
-    if (TOTALS) {
-      sm.cand = 0ull;
-      sm.vis = 0u;
-    }
+    sm.cand = 0ull;
+    sm.vis = 0u;
   }
   uint64_t cand = 0;
   uint32_t vis = 0;
-  for (uint32_t r0 = 0; r0 < nblk; r0 += kRound) {
+  for (uint32_t r0 = b0; r0 < b1; r0 += kRound) {
     uint32_t first[kSeg], c[kSeg], lc[kSeg], sc = 0, sl = 0;
 #pragma unroll
     for (int j = 0; j < kSeg; ++j) {
       const uint32_t b = r0 + (uint32_t)(kSeg * t + j);
-      const bool on = b < nblk;
-      const uint32_t bc = on ? b : nblk - 1u;  // unconditional loads, all in flight together
+      const bool on = b < b1;
+      const uint32_t bc = on ? b : b1 - 1u;  // unconditional loads, all in flight together
       const uint16_t *row = ws.group_off + (size_t)bc * ws.group_pitch + local;
       const uint32_t e0 = row[0], e1 = row[1], lg = ws.blk_large[bc];
-      if (TOTALS) {
+      if (COUNT) {
         const uint32_t cv = ws.blk_cand[bc], vv = ws.blk_vis[bc];
         cand += on ? cv : 0u;
         vis += on ? vv : 0u;
@@ -123,7 +129,7 @@ __device__ __forceinline__ uint32_t collect(const RasterWs &ws, BinSmem &sm, int
       ts += sm.tmp[v];
       tl += sm.ltmp[v];
     }
-    const uint32_t run = sm.m;
+    if (t == 0) sm.run = take(ts);
 #pragma unroll
     for (int j = 0; j < kSeg; ++j) {
       sm.pre[kSeg * t + j] = es;
@@ -133,9 +139,9 @@ __device__ __forceinline__ uint32_t collect(const RasterWs &ws, BinSmem &sm, int
       el += lc[j];
     }
     __syncthreads();
-    if (t == 0) sm.m = run + ts;
-    __syncthreads();
-    for (uint32_t i0 = w * kWave; i0 < ts + tl; i0 += kNT) {
+    const uint32_t run = sm.run;
+    const uint32_t n0 = COUNT && run + ts > (uint32_t)kBinCap ? ts : 0u;
+    for (uint32_t i0 = n0 + w * kWave; i0 < ts + tl; i0 += kNT) {
       const uint32_t i = i0 + l;
       const bool small = i < ts, large = !small && i < ts + tl;
       bool hit = false;
@@ -153,21 +159,20 @@ __device__ __forceinline__ uint32_t collect(const RasterWs &ws, BinSmem &sm, int
       const uint64_t hm = ballot(hit);
       if (hm == 0ull) continue;
       uint32_t p = 0;
-      if (l == 0) p = atomicAdd(&sm.m, (uint32_t)__popcll(hm));
+      if (l == 0) p = take((uint32_t)__popcll(hm));
       p = (uint32_t)__builtin_amdgcn_readfirstlane((int)p);
       if (hit) put(p + (uint32_t)__popcll(hm & lanemask_lt()), e.z, e.w, kTilesUnknown);
     }
     __syncthreads();
   }
-  if (TOTALS) {
+  if (COUNT) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) cand += __shfl_xor(cand, o, kWave);
     vis = wave_sum(vis);
     if (l == 0 && cand) atomicAdd(&sm.cand, (unsigned long long)cand);
     if (l == 0 && vis) atomicAdd(&sm.vis, vis);
+    __syncthreads();
   }
-  __syncthreads();
-  return sm.m;
 }
 
 // Puts the positions of the m collected entries into (key, slot) order in
@@ -184,9 +189,8 @@ constexpr uint32_t kRun = 16;
 constexpr int kPosBits = 12;
 static_assert(kBinCap <= 1 << kPosBits, "positions and run heads share a word");
 
-// gkeys (nullable) receives the sorted keys.
 template <int I>
-__device__ __forceinline__ void sort_entries(BinSmem &sm, uint32_t m, uint32_t *gkeys) {
+__device__ __forceinline__ void sort_entries(BinSmem &sm, uint32_t m) {
   const int t = threadIdx.x, w = t / kWave, l = __lane_id();
   const uint64_t lt = lanemask_lt();
   const uint32_t e0 = (uint32_t)(w * I * kWave + l);
@@ -302,8 +306,6 @@ __device__ __forceinline__ void sort_entries(BinSmem &sm, uint32_t m, uint32_t *
       lds_barrier();
     }
     if (phase == 0) {
-      if (gkeys)
-        for (uint32_t i = t; i < m; i += kNT) gkeys[i] = sm.kk[i];
       for (uint32_t i = t; i + 1 < m; i += kNT) {
         const uint32_t k = sm.kk[i];
         if (sm.kk[i + 1] != k || (i > 0 && sm.kk[i - 1] == k)) continue;
@@ -327,12 +329,12 @@ __device__ __forceinline__ void sort_entries(BinSmem &sm, uint32_t m, uint32_t *
   }
 }
 
-__device__ __forceinline__ void sort_any(BinSmem &sm, uint32_t m, uint32_t *gkeys) {
+__device__ __forceinline__ void sort_any(BinSmem &sm, uint32_t m) {
   static_assert(kBinItems == 8, "item counts of the sort");
-  if (m <= kNT) sort_entries<1>(sm, m, gkeys);
-  else if (m <= 2 * kNT) sort_entries<2>(sm, m, gkeys);
-  else if (m <= 4 * kNT) sort_entries<4>(sm, m, gkeys);
-  else sort_entries<8>(sm, m, gkeys);
+  if (m <= kNT) sort_entries<1>(sm, m);
+  else if (m <= 2 * kNT) sort_entries<2>(sm, m);
+  else if (m <= 4 * kNT) sort_entries<4>(sm, m);
+  else sort_entries<8>(sm, m);
 }
 
 // The tiles of the collected entries [0, cm) that came without them, and the
@@ -415,9 +417,10 @@ __device__ __forceinline__ uint32_t finish_tiles(const RasterWs &ws, BinSmem &sm
 // One block per bin of the band.  Bound by latency: the collection's two
 // memory round trips, the test of long rectangles, about 20 LDS barriers of
 // the sort (lists of a few hundred to a thousand entries, three digit passes):
-// on a 1920 x 1080 view of 862k pairs a block takes 22 us (collection 5.7,
-// listing and testing long rectangles 6.3, counts 1.3, sort 6.3, writes 1.4) and
-// the kernel 25; on 3840 x 2160 there are two rounds of blocks, 60.
+// on a 1920 x 1080 view of 862k pairs a block takes 18 us (collection 5.7,
+// listing and testing long rectangles 6.3, counts 1.3, sort 4, writes 1.4) and
+// the kernel 21; on 3840 x 2160 there are two rounds of blocks, 49.  (With the
+// long bins' runs in this kernel its registers spilled: 25 and 60.)
 __global__ __launch_bounds__(kNT, 4) void k_bin_sort(RasterWs ws, int band_row0, uint32_t nband) {
   __shared__ BinSmem sm;
   const uint32_t item = xcd_item(blockIdx.x, nband);
@@ -431,14 +434,15 @@ __global__ __launch_bounds__(kNT, 4) void k_bin_sort(RasterWs ws, int band_row0,
   const bool reach = bx < (uint32_t)bg.gx;
   const int local = reach ? (int)((by - (uint32_t)band_row0) * (uint32_t)bg.gx + bx) : 0;
   if (t < 32) sm.tcnt[t] = 0u;
-  uint32_t m = collect<true>(ws, sm, local, bx, by, nblk, reach,
-                             [&](uint32_t p, uint32_t key, uint32_t slot, uint32_t tiles) {
-                               if (p < (uint32_t)kBinCap) {
-                                 sm.kk[p] = key;
-                                 sm.su[p] = slot;
-                                 sm.mm[p] = tiles;
-                               }
-                             });
+  collect<true>(
+      ws, sm, local, bx, by, 0u, nblk, reach, [&](uint32_t n) { return atomicAdd(&sm.m, n); },
+      [&](uint32_t p, uint32_t key, uint32_t slot, uint32_t tiles) {
+        if (p < (uint32_t)kBinCap) {
+          sm.kk[p] = key;
+          sm.su[p] = slot;
+          sm.mm[p] = tiles;
+        }
+      });
   // candidates of the whole view: nothing is listed if they exceed the capacity
   const uint32_t cand = (uint32_t)std::min<uint64_t>(sm.cand, kLbVal);
   const bool over = cand > (uint64_t)ws.pcap;
@@ -447,58 +451,43 @@ __global__ __launch_bounds__(kNT, 4) void k_bin_sort(RasterWs ws, int band_row0,
     ws.hdr->n_candidates = cand;
     ws.hdr->pair_overflow = over ? 1u : 0u;
   }
-  if (over) m = 0;
-  uint32_t mine = 0;
-  if (m > 0) {
-    // every entry stands for at least one candidate tile of its own, so the
-    // lists of all bins fit the capacity
-    uint32_t base = 0;
-    const bool longer = m > (uint32_t)kBinCap;
-    uint32_t *gkey = ws.tkey, *gslot = ws.bin_slot[0], *gmask = ws.bin_mask[0];
-    if (longer) {
-      // more than a block sorts at once: the entries to memory, then runs of
-      // kBinCap, sorted one after the other; the tile scan merges them
-      if (t == 0) {
-        sm.base = atomicAdd(&ws.hdr->bin_cursor, m);
-        ws.over_bin[atomicAdd(&ws.hdr->n_over, 1u)] = bin;
-      }
-      __syncthreads();
-      const uint32_t gb = sm.base;
-      collect<false>(ws, sm, local, bx, by, nblk, reach,
-                     [&](uint32_t p, uint32_t key, uint32_t slot, uint32_t tiles) {
-                       gkey[gb + p] = key;
-                       gslot[gb + p] = slot;
-                       gmask[gb + p] = tiles;
-                     });
+  const uint32_t m = over ? 0u : sm.m;
+  // (every entry stands for at least one candidate tile of its own, so the lists
+  // of all bins fit the capacity)
+  if (m > (uint32_t)kBinCap) {
+    // a long bin: its place, its slices
+    const uint32_t ns = long_slices(m);
+    if (t == 0) {
+      ws.bin_range[bin] = make_uint2(atomicAdd(&ws.hdr->bin_cursor, m), m);
+      const uint32_t q = atomicAdd(&ws.hdr->n_over, 1u);
+      ws.over_bin[2 * q] = bin;
+      ws.over_bin[2 * q + 1] = 0u;
+      sm.unit = atomicAdd(&ws.hdr->n_slices, ns);
     }
-    for (uint32_t c0 = 0; c0 < m; c0 += kBinCap) {
-      const uint32_t cm = min((uint32_t)kBinCap, m - c0);
-      if (longer) {
-        __syncthreads();  // the last run's readers are done; the collected entries are written
-        const uint32_t gb = sm.base;
-        for (uint32_t i = t; i < cm; i += kNT) {
-          sm.kk[i] = gkey[gb + c0 + i];
-          sm.su[i] = gslot[gb + c0 + i];
-          sm.mm[i] = gmask[gb + c0 + i];
-        }
-        __syncthreads();
-      }
-      mine += finish_tiles(ws, sm, cm, bx, by);
-      // all bins ask at about the same time, and the answers come one after
-      // the other: the sort, which loads nothing, covers the wait
-      if (!longer && t == 0) base = atomicAdd(&ws.hdr->bin_cursor, m);
-      sort_any(sm, cm, longer ? gkey + sm.base + c0 : nullptr);
-      if (!longer && t == 0) sm.base = base;
-      lds_barrier();
-      const uint32_t gb = sm.base;
-      for (uint32_t i = t; i < cm; i += kNT) {
-        const uint32_t p = sm.vv[i] & ((1u << kPosBits) - 1u);
-        gslot[gb + c0 + i] = sm.su[p];
-        gmask[gb + c0 + i] = sm.mm[p];
-      }
+    __syncthreads();
+    for (uint32_t i = t; i < ns; i += kNT) {
+      ws.slices[kSliceRow * (size_t)(sm.unit + i)] = bin;
+      ws.slices[kSliceRow * (size_t)(sm.unit + i) + 1] = i;
+    }
+  } else if (m > 0) {
+    const uint32_t mine = finish_tiles(ws, sm, m, bx, by);
+    // all bins ask at about the same time, and the answers come one after
+    // the other: the sort, which loads nothing, covers the wait
+    uint32_t base = 0;
+    if (t == 0) base = atomicAdd(&ws.hdr->bin_cursor, m);
+    sort_any(sm, m);
+    if (t == 0) {
+      sm.base = base;
+      ws.bin_range[bin] = make_uint2(base, m);
     }
     if (l < 32 && mine) atomicAdd(&sm.tcnt[l], mine);
-    if (t == 0) ws.bin_range[bin] = make_uint2(sm.base, m);
+    lds_barrier();
+    const uint32_t gb = sm.base;
+    for (uint32_t i = t; i < m; i += kNT) {
+      const uint32_t p = sm.vv[i] & ((1u << kPosBits) - 1u);
+      ws.bin_slot[0][gb + i] = sm.su[p];
+      ws.bin_mask[0][gb + i] = sm.mm[p];
+    }
   } else if (t == 0) {
     ws.bin_range[bin] = make_uint2(0u, 0u);
   }
@@ -510,32 +499,260 @@ __global__ __launch_bounds__(kNT, 4) void k_bin_sort(RasterWs ws, int band_row0,
   }
 }
 
-// Entries of run r (entries [r0, r1) of a long list, sorted by (key, slot))
-// that come before (k, s).
-__device__ __forceinline__ uint32_t run_rank(const uint32_t *key, const uint32_t *slot, uint32_t r0,
-                                             uint32_t r1, uint32_t k, uint32_t s) {
-  uint32_t lo = r0, hi = r1;
-  while (lo < hi) {
-    const uint32_t mid = lo + (hi - lo) / 2;
-    const uint32_t mk = key[mid];
-    if (mk < k || (mk == k && slot[mid] < s)) lo = mid + 1;
-    else hi = mid;
+// ---- long bins --------------------------------------------------------------
+// Bins of more than kBinCap entries, done by all blocks of the scan kernel
+// together in two phases of units, each taken by the next free block: first
+// their entries to memory (a unit: one bin's from some slot blocks), then the
+// slices of their depths.  A block that finds no more units waits for those that
+// are taken, which running blocks work on: no wait is on a block that has not
+// started.
+// Bound by latency: about 30 us for the copies and 60 for a block's slice, most
+// of it the pass over the bin's keys where a bin has 100k entries.  300k
+// Gaussians, projection and binning (us), with two global sorts / one block per
+// bin and a merge by rank / now: within 64 x 64 px 176 / 4,700 / 230, 200 x 200
+// 175 / - / 193, 400 x 400 175 / 290 / 167, 600 x 600 174 / - / 164.  256 blocks for
+// them: with 64 and 128, 500 and 360 instead of 270 within 64 x 64 px.  Four
+// waves per SIMD although that spills: at 207 registers the blocks, there in
+// every view, made four 1080p views in flight 2 to 4 percent slower.
+
+// Waits (thread 0) until *done reaches want; false if the wait hit its bound
+// (then *err is set).  What was written before the counts is visible after it.
+__device__ __forceinline__ bool wait_units(BinSmem &sm, const uint32_t *done, uint32_t want,
+                                           uint32_t *err) {
+  if (threadIdx.x == 0) {
+    uint32_t spins = 0;
+    while (ld_acq(done) < want && ++spins <= kSpinLimit) __builtin_amdgcn_s_sleep(1);
+    sm.flag = spins <= kSpinLimit ? 1u : 0u;
+    if (!sm.flag) atomicOr(err, 1u);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   }
-  return lo - r0;
+  __syncthreads();
+  const bool ok = sm.flag != 0u;
+  __syncthreads();
+  return ok;
 }
 
-constexpr int kMergeBlocks = 128;
+// Units [0, total) by work(unit), as many as this block gets, then their number
+// is added to *done.
+template <typename Work>
+__device__ __forceinline__ void take_units(BinSmem &sm, uint32_t *next, uint32_t *done,
+                                           uint32_t total, Work work) {
+  uint32_t n = 0;
+  for (;; ++n) {
+    if (threadIdx.x == 0) sm.unit = atomicAdd(next, 1u);
+    __syncthreads();
+    const uint32_t u = sm.unit;
+    if (u >= total) break;
+    work(u);
+    __syncthreads();  // the block's writes are out, the LDS may be reused
+  }
+  if (threadIdx.x == 0 && n) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    atomicAdd(done, n);
+  }
+}
 
+// One unit of the first phase: entries of long bin q (of the band from bin row
+// band_row0 on) from slot blocks [b0, b1).
+__device__ __forceinline__ void long_copy(const RasterWs &ws, BinSmem &sm, uint32_t q, uint32_t b0,
+                                          uint32_t b1, uint32_t band_row0) {
+  const BinGrid &bg = ws.bins;
+  const uint32_t bin = ws.over_bin[2 * q], bx = bin % (uint32_t)bg.nx, by = bin / (uint32_t)bg.nx;
+  const uint32_t gb = ws.bin_range[bin].x;
+  collect<false>(
+      ws, sm, (int)((by - band_row0) * (uint32_t)bg.gx + bx), bx, by, b0, b1,
+      true, [&](uint32_t n) { return atomicAdd(&ws.over_bin[2 * q + 1], n); },
+      [&](uint32_t p, uint32_t key, uint32_t slot, uint32_t tiles) {
+        ws.tkey[gb + p] = key;
+        ws.bin_slot[0][gb + p] = slot;
+        ws.bin_mask[0][gb + p] = tiles;
+      });
+}
+
+// Entries of a long bin whose (key, slot) lie in [lo, hi): their positions into
+// sm.su while there are no more than kBinCap, their number, and in sm.vis the
+// number of those before lo.  Reads all keys (slots only where a key equals a
+// bound's), eight loads per thread in flight, a step ahead of their use.
+__device__ __forceinline__ uint32_t pick(BinSmem &sm, const uint32_t *key, const uint32_t *slot,
+                                         uint32_t m, uint64_t lo, uint64_t hi) {
+  constexpr int kU = 8;
+  const int t = threadIdx.x, l = __lane_id();
+  const uint32_t klo = (uint32_t)(lo >> 32), khi = (uint32_t)(hi >> 32);
+  __syncthreads();  // the last readers of sm.m and sm.vis
+  if (t == 0) sm.m = sm.vis = 0u;
+  __syncthreads();
+  uint32_t before = 0, next[kU];
+  auto load = [&](uint32_t e0) {
+#pragma unroll
+    for (int u = 0; u < kU; ++u) next[u] = key[min(e0 + (uint32_t)(u * kNT + t), m - 1u)];
+  };
+  load(0u);
+  for (uint32_t e0 = 0; e0 < m; e0 += kU * kNT) {
+    uint64_t v[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const uint32_t e = e0 + (uint32_t)(u * kNT + t);
+      v[u] = (uint64_t)next[u] << 32;
+      if (next[u] == klo || next[u] == khi) v[u] |= slot[min(e, m - 1u)];
+    }
+    load(min(e0 + (uint32_t)(kU * kNT), m - 1u));
+    uint64_t im[kU];
+    uint32_t n = 0;
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const bool on = e0 + (uint32_t)(u * kNT + t) < m;
+      before += on && v[u] < lo ? 1u : 0u;
+      im[u] = ballot(on && v[u] >= lo && v[u] < hi);
+      n += (uint32_t)__popcll(im[u]);
+    }
+    if (n == 0u) continue;
+    uint32_t p = 0;
+    if (l == 0) p = atomicAdd(&sm.m, n);
+    p = (uint32_t)__builtin_amdgcn_readfirstlane((int)p);
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const uint32_t at = p + (uint32_t)__popcll(im[u] & lanemask_lt());
+      if (((im[u] >> l) & 1ull) && at < (uint32_t)kBinCap) sm.su[at] = e0 + (uint32_t)(u * kNT + t);
+      p += (uint32_t)__popcll(im[u]);
+    }
+  }
+  before = wave_sum(before);
+  if (l == 0 && before) atomicAdd(&sm.vis, before);
+  __syncthreads();
+  return sm.m;
+}
+
+// One unit of the second phase: slice `unit` of a long bin, the entries between
+// two of the splitters that divide an even sample of the bin into its slices.
+// (key, slot) differs for all entries, so the slices are a partition whatever
+// the keys, every block that works on one bin sorts the same sample, and none
+// needs another's result: the entries before the slice are counted.  A slice
+// that is more than a block sorts at once (the sample's luck, or more slices
+// than samples) is halved until it is not.
+__device__ __forceinline__ void long_slice(const RasterWs &ws, BinSmem &sm, uint32_t unit) {
+  const int t = threadIdx.x, l = __lane_id();
+  const BinGrid &bg = ws.bins;
+  uint32_t *row = ws.slices + kSliceRow * (size_t)unit;
+  const uint32_t bin = row[0], s = row[1];
+  const uint32_t bx = bin % (uint32_t)bg.nx, by = bin / (uint32_t)bg.nx;
+  const uint2 rg = ws.bin_range[bin];
+  const uint32_t m = rg.y, ns = long_slices(m);
+  const uint32_t *key = ws.tkey + rg.x, *slot = ws.bin_slot[0] + rg.x, *mask = ws.bin_mask[0] + rg.x;
+  // 64 samples a slice, but no more than 2,048 in all (m > kBinCap, so they differ)
+  const int lg = ns <= 8u ? 9 : (ns <= 16u ? 10 : 11);
+  uint32_t c = 1u << lg;
+  for (uint32_t i = t; i < c; i += kNT) {
+    const uint32_t e = (uint32_t)(((uint64_t)i * m) >> lg);
+    sm.kk[i] = key[e];
+    sm.su[i] = slot[e];
+  }
+  if (t < 32) sm.tcnt[t] = 0u;
+  auto splitter = [&](uint32_t i) -> uint64_t {
+    const uint32_t p = (uint32_t)(((uint64_t)i << lg) / ns);
+    return ((uint64_t)sm.kk[p] << 32) | sm.su[sm.vv[p] & ((1u << kPosBits) - 1u)];
+  };
+  uint64_t lo = 0, hi = 0;
+  uint32_t pos = 0, size = 0, mine = 0, at = 0;
+  // the sample, then the slice (in as many parts as it takes)
+  for (bool sample = true;; sample = false) {
+    lds_barrier();
+    if (!sample && c) mine += finish_tiles(ws, sm, c, bx, by);
+    if (c) sort_any(sm, c);
+    lds_barrier();
+    if (sample) {
+      lo = s > 0u ? splitter(s) : 0ull;
+      hi = s + 1u < ns ? splitter(s + 1u) : ~0ull;
+    } else {
+      for (uint32_t i = t; i < c; i += kNT) {
+        const uint32_t p = sm.vv[i] & ((1u << kPosBits) - 1u);
+        ws.bin_slot[1][rg.x + at + i] = sm.su[p];
+        ws.bin_mask[1][rg.x + at + i] = sm.mm[p];
+      }
+      if (lo >= hi) break;
+    }
+    uint64_t h = hi;
+    c = pick(sm, key, slot, m, lo, h);
+    while (c > (uint32_t)kBinCap) {
+      h = lo + (h - lo) / 2u;
+      c = pick(sm, key, slot, m, lo, h);
+    }
+    at = sm.vis;
+    if (sample) pos = at;
+    lo = h;
+    size += c;
+    for (uint32_t i = t; i < c; i += kNT) {
+      const uint32_t e = sm.su[i];
+      sm.kk[i] = key[e];
+      sm.su[i] = slot[e];
+      sm.mm[i] = mask[e];
+    }
+  }
+  if (l < 32 && mine) atomicAdd(&sm.tcnt[l], mine);
+  __syncthreads();
+  if (t == 0) {
+    row[2] = pos;
+    row[3] = size;
+  }
+  if (t < 32) {
+    row[4 + t] = sm.tcnt[t];
+    const uint32_t tx = (bx << bg.sx) + (t & ((1u << bg.sx) - 1u)), ty = (by << bg.sy) + (t >> bg.sx);
+    if (sm.tcnt[t]) atomicAdd(&ws.tile_count[(size_t)ty * ws.tiles_x + tx], sm.tcnt[t]);
+  }
+}
+
+// The first phase alone, where bands of bin rows share the groups.
+__global__ __launch_bounds__(kNT) void k_long_copy(RasterWs ws, int band_row0, int rows) {
+  __shared__ BinSmem sm;
+  const uint32_t nblk = slot_blocks(ws.hdr->n_slots), nover = ws.hdr->n_over;
+  for (uint32_t q = 0; q < nover; ++q) {
+    const uint32_t by = ws.over_bin[2 * q] / (uint32_t)ws.bins.nx;
+    if (by < (uint32_t)band_row0 || by >= (uint32_t)(band_row0 + rows)) continue;
+    for (uint32_t b0 = blockIdx.x * kLongSeg; b0 < nblk; b0 += gridDim.x * kLongSeg) {
+      __syncthreads();
+      long_copy(ws, sm, q, b0, min(b0 + kLongSeg, nblk), (uint32_t)band_row0);
+    }
+  }
+}
+
+constexpr int kLongBlocks = 256;  // blocks that are there for long bins only
+
+// Slot blocks per unit of the first phase: about a unit per block.
+__device__ __forceinline__ uint32_t long_seg(uint32_t nover, uint32_t nblk) {
+  const uint64_t all = (uint64_t)nover * nblk;
+  return (uint32_t)min((all + kLongBlocks - 1u) / kLongBlocks + kLongSeg - 1u, (uint64_t)nblk);
+}
+
+// Long bins first (COPIED: their entries are in memory already).  Then:
 // Blocks [0, scan): ranges of kScanThreads * kScanTiles consecutive tiles each, chained
 // by decoupled look-back; the block number is a ticket taken in the order
 // blocks start, so every block that one waits on is already running.
 // Block scan: pair numbers of the slot blocks (training).
-// The others: entry by entry, the merge of long lists (an entry's place is its
-// rank in its own run plus its ranks in the others).
-__global__ __launch_bounds__(kScanThreads) void k_tile_scan(RasterWs ws, int train) {
-  __shared__ uint32_t tmp[kScanThreads / kWave];
+__global__ __launch_bounds__(kScanThreads, 4) void k_tile_scan(RasterWs ws, int train, int copied) {
+  static_assert(kScanThreads == kNT, "long bins are done by the same blocks");
+  __shared__ BinSmem sm;
   __shared__ uint32_t s_b, s_excl;
+  uint32_t *tmp = sm.tmp;
   const int t = threadIdx.x, w = t / kWave, l = __lane_id();
+  bool ok = true;
+  const uint32_t nover = ws.hdr->n_over;
+  if (nover > 0u) {
+    if (!copied) {
+      const uint32_t nblk = slot_blocks(ws.hdr->n_slots), seg = long_seg(nover, nblk);
+      const uint32_t per = (nblk + seg - 1u) / seg;
+      take_units(sm, &ws.hdr->copy_next, &ws.hdr->copy_done, nover * per, [&](uint32_t u) {
+        const uint32_t b0 = u % per * seg;
+        long_copy(ws, sm, u / per, b0, min(b0 + seg, nblk), 0u);
+      });
+      ok = wait_units(sm, &ws.hdr->copy_done, nover * per, &ws.hdr->sync_error);
+    }
+    const uint32_t ns = ws.hdr->n_slices;
+    if (ok)
+      take_units(sm, &ws.hdr->slice_next, &ws.hdr->slice_done, ns,
+                 [&](uint32_t u) { long_slice(ws, sm, u); });
+    // (blocks that are there for the long bins need not wait)
+    if (blockIdx.x < (uint32_t)ws.scan_blocks)
+      ok = wait_units(sm, &ws.hdr->slice_done, ns, &ws.hdr->sync_error) && ok;
+  }
   if (blockIdx.x < (uint32_t)ws.scan_blocks) {
     if (t == 0) s_b = ws.scan_blocks > 1 ? atomicAdd(&ws.hdr->scan_ticket, 1u) : 0u;
     __syncthreads();
@@ -553,7 +770,8 @@ __global__ __launch_bounds__(kScanThreads) void k_tile_scan(RasterWs ws, int tra
     }
 #pragma unroll
     for (int q = 0; q < kScanTiles; ++q) {
-      if (t0 + q >= ntiles) c[q] = 0u;
+      // (no lists at all if a wait hit its bound)
+      if (t0 + q >= ntiles || !ok) c[q] = 0u;
       sum += c[q];
     }
     uint32_t tot;
@@ -578,8 +796,7 @@ __global__ __launch_bounds__(kScanThreads) void k_tile_scan(RasterWs ws, int tra
     }
     return;
   }
-  if (blockIdx.x == (uint32_t)ws.scan_blocks) {
-    if (!train) return;
+  if (blockIdx.x == (uint32_t)ws.scan_blocks && train) {
     const uint32_t nblk = slot_blocks(ws.hdr->n_slots);
     uint32_t run = 0;
     for (uint32_t r0 = 0; r0 < nblk; r0 += kScanThreads) {
@@ -590,40 +807,6 @@ __global__ __launch_bounds__(kScanThreads) void k_tile_scan(RasterWs ws, int tra
       run += tot;
     }
     if (t == 0) ws.hdr->n_emit = ws.hdr->pair_overflow ? 0u : run;
-    return;
-  }
-  // long lists: their entries, kScanThreads at a time, are dealt over the blocks
-  __shared__ uint2 range[kScanThreads];
-  __shared__ uint32_t chunk0[kScanThreads];
-  const uint32_t nover = ws.hdr->n_over;
-  const uint32_t mb = blockIdx.x - (uint32_t)ws.scan_blocks - 1u;
-  const uint32_t *key = ws.tkey, *slot = ws.bin_slot[0];
-  for (uint32_t q0 = 0; q0 < nover; q0 += kScanThreads) {
-    const bool on = q0 + t < nover;
-    const uint2 rt = on ? ws.bin_range[ws.over_bin[q0 + t]] : make_uint2(0u, 0u);
-    uint32_t chunks;
-    const uint32_t c0 = block_scan<kScanThreads>((rt.y + kScanThreads - 1) / kScanThreads, tmp, &chunks);
-    range[t] = rt;
-    chunk0[t] = c0;
-    __syncthreads();
-    for (uint32_t u = mb; u < chunks; u += kMergeBlocks) {
-      uint32_t q = 0;  // the list of chunk u: the last that starts at or before it
-#pragma unroll
-      for (int st = kScanThreads / 2; st > 0; st >>= 1)
-        if (q0 + q + st < nover && chunk0[q + st] <= u) q += st;
-      const uint2 rg = range[q];
-      const uint32_t i = (u - chunk0[q]) * kScanThreads + t;
-      if (i >= rg.y) continue;
-      const uint32_t own = i / kBinCap;
-      const uint32_t k = key[rg.x + i], s = slot[rg.x + i];
-      uint32_t rank = i - own * kBinCap;
-      for (uint32_t c = 0; c * kBinCap < rg.y; ++c)
-        if (c != own)
-          rank += run_rank(key, slot, rg.x + c * kBinCap, rg.x + min((c + 1) * kBinCap, rg.y), k, s);
-      ws.bin_slot[1][rg.x + rank] = s;
-      ws.bin_mask[1][rg.x + rank] = ws.bin_mask[0][rg.x + i];
-    }
-    __syncthreads();  // before the next lists take their place
   }
 }
 
@@ -731,67 +914,64 @@ struct ListSmem {
   uint32_t nfull;
 };
 
-// The tile lists of one bin per block (blocks from `order0` on: the
-// compositing order, OCTGS_RASTER_TILE_ORDER).  The bin's ordered entries are
+constexpr int kTilesPerWave = 32 / kLW;
+
+// The tiles of a bin that a wave writes the lists of, and where in them it is.
+struct ListTiles {
+  uint32_t tile[kTilesPerWave], run[kTilesPerWave];
+  bool on[kTilesPerWave];
+};
+
+__device__ __forceinline__ ListTiles list_tiles(const RasterWs &ws, uint32_t bx, uint32_t by, int w) {
+  const BinGrid &bg = ws.bins;
+  const int nt = 1 << (bg.sx + bg.sy);
+  ListTiles r;
+#pragma unroll
+  for (int q = 0; q < kTilesPerWave; ++q) {
+    const int j = w + q * kLW;
+    const uint32_t tx = (bx << bg.sx) + (uint32_t)(j & ((1 << bg.sx) - 1));
+    const uint32_t ty = (by << bg.sy) + (uint32_t)(j >> bg.sx);
+    r.on[q] = j < nt && tx < (uint32_t)ws.tiles_x && ty < (uint32_t)ws.tiles_y;
+    r.tile[q] = ty * (uint32_t)ws.tiles_x + tx;
+    r.run[q] = r.on[q] ? ws.ranges[2 * (size_t)r.tile[q]] : 0u;
+  }
+  return r;
+}
+
+// Appends n ordered entries of bin (bx, by) to its tiles' lists.  The entries are
 // staged in LDS kLStage at a time; each wave walks them for up to four of the
 // bin's tiles and appends those whose mask has the tile's bit.
 // Training: rectangles with more than kKeepBits tiles number all their tiles
 // as pairs; the rows of the numbers without a pair are cleared here, half a
 // wave per entry, a tile per lane.
 template <bool TRAIN>
-__global__ __launch_bounds__(kLT) void k_tile_lists(RasterWs ws, uint32_t order0) {
-  __shared__ union {
-    ListSmem<TRAIN> ls;
-    OrderSmem os;
-  } sm;
-  if (blockIdx.x >= order0) {
-    order_tiles(ws, blockIdx.x - order0, sm.os);
-    return;
-  }
+__device__ __forceinline__ void append(const RasterWs &ws, ListSmem<TRAIN> &ls, ListTiles &lt,
+                                       const uint32_t *slots, const uint32_t *masks, uint32_t n,
+                                       uint32_t bx, uint32_t by, uint32_t nblk) {
   const int t = threadIdx.x, w = t / kWave, l = __lane_id();
-  const uint64_t lt = lanemask_lt();
+  const uint64_t lmask = lanemask_lt();
   const BinGrid &bg = ws.bins;
-  const uint32_t nbins = (uint32_t)(bg.nx * bg.ny), bin = xcd_item(blockIdx.x, nbins);
-  if (bin >= nbins) return;
-  const uint2 rg = ws.bin_range[bin];
-  if (rg.y == 0) return;
-  const uint32_t bx = bin % (uint32_t)bg.nx, by = bin / (uint32_t)bg.nx;
-  const uint32_t nblk = TRAIN ? slot_blocks(ws.hdr->n_slots) : 1u;
-  const int src = rg.y > (uint32_t)kBinCap;  // long lists are in the merged copy
-  const uint32_t *slots = ws.bin_slot[src] + rg.x, *masks = ws.bin_mask[src] + rg.x;
-  constexpr int kT = 32 / kLW;  // tiles per wave
   const int nt = 1 << (bg.sx + bg.sy);
-  uint32_t tile[kT], run[kT];
-  bool on[kT];
-#pragma unroll
-  for (int q = 0; q < kT; ++q) {
-    const int j = w + q * kLW;
-    const uint32_t tx = (bx << bg.sx) + (uint32_t)(j & ((1 << bg.sx) - 1));
-    const uint32_t ty = (by << bg.sy) + (uint32_t)(j >> bg.sx);
-    on[q] = j < nt && tx < (uint32_t)ws.tiles_x && ty < (uint32_t)ws.tiles_y;
-    tile[q] = ty * (uint32_t)ws.tiles_x + tx;
-    run[q] = on[q] ? ws.ranges[2 * (size_t)tile[q]] : 0u;
-  }
-  for (uint32_t c0 = 0; c0 < rg.y; c0 += kLStage) {
-    const uint32_t cm = min((uint32_t)kLStage, rg.y - c0);
+  for (uint32_t c0 = 0; c0 < n; c0 += kLStage) {
+    const uint32_t cm = min((uint32_t)kLStage, n - c0);
     __syncthreads();
     if (TRAIN) {
-      if (t == 0) sm.ls.nfull = 0u;
+      if (t == 0) ls.nfull = 0u;
       __syncthreads();
     }
     for (uint32_t i = t; i < cm; i += kLT) {
       const uint32_t s = slots[c0 + i];
-      sm.ls.slot[i] = s;
-      sm.ls.mask[i] = masks[c0 + i];
+      ls.slot[i] = s;
+      ls.mask[i] = masks[c0 + i];
       if (TRAIN) {
         const uint64_t rc = ws.rect[s].x;
         const uint32_t first = ws.blk_pairs[slot_block(s, nblk)] + ws.pair_base[s];
         if (rect_tiles(unpack_rect(rc)) > kKeepBits) {
-          const uint32_t k = atomicAdd(&sm.ls.nfull, 1u);
-          sm.ls.index[k] = (uint16_t)i;
-          sm.ls.first[k] = first;
-          sm.ls.org[k] = (uint32_t)rc;
-          sm.ls.end[k] = (uint32_t)(rc >> 32);
+          const uint32_t k = atomicAdd(&ls.nfull, 1u);
+          ls.index[k] = (uint16_t)i;
+          ls.first[k] = first;
+          ls.org[k] = (uint32_t)rc;
+          ls.end[k] = (uint32_t)(rc >> 32);
         }
       }
     }
@@ -799,35 +979,87 @@ __global__ __launch_bounds__(kLT) void k_tile_lists(RasterWs ws, uint32_t order0
     if (TRAIN) {
       const uint32_t tx = (bx << bg.sx) + (uint32_t)(l & ((1 << bg.sx) - 1));
       const uint32_t ty = (by << bg.sy) + (uint32_t)((l & 31) >> bg.sx);
-      for (uint32_t k = 2 * w + (l >> 5); k < sm.ls.nfull; k += 2 * kLW) {
-        const TileRect r = unpack_rect(sm.ls.org[k] | ((uint64_t)sm.ls.end[k] << 32));
-        const uint32_t i = sm.ls.index[k];
+      for (uint32_t k = 2 * w + (l >> 5); k < ls.nfull; k += 2 * kLW) {
+        const TileRect r = unpack_rect(ls.org[k] | ((uint64_t)ls.end[k] << 32));
+        const uint32_t i = ls.index[k];
         if ((l & 31) < nt && tx >= r.x0 && tx < r.x1 && ty >= r.y0 && ty < r.y1 &&
-            !((sm.ls.mask[i] >> (l & 31)) & 1u)) {
+            !((ls.mask[i] >> (l & 31)) & 1u)) {
           float2 *row = reinterpret_cast<float2 *>(
-              ws.gpair + (size_t)kPairRow * (sm.ls.first[k] + pair_rank(r, 0ull, tx, ty)));
+              ws.gpair + (size_t)kPairRow * (ls.first[k] + pair_rank(r, 0ull, tx, ty)));
 #pragma unroll
           for (int q = 0; q < 4; ++q) row[q] = make_float2(0.0f, 0.0f);
-          row[4] = make_float2(0.0f, __uint_as_float(sm.ls.slot[i]));
+          row[4] = make_float2(0.0f, __uint_as_float(ls.slot[i]));
         }
       }
     }
     for (uint32_t i0 = 0; i0 < cm; i0 += kWave) {
       const uint32_t i = min(i0 + (uint32_t)l, cm - 1u);
-      const uint32_t s = sm.ls.slot[i];
-      const uint32_t bits = i0 + (uint32_t)l < cm ? sm.ls.mask[i] : 0u;
+      const uint32_t s = ls.slot[i];
+      const uint32_t bits = i0 + (uint32_t)l < cm ? ls.mask[i] : 0u;
 #pragma unroll
-      for (int q = 0; q < kT; ++q) {
-        const bool hit = on[q] && ((bits >> (w + q * kLW)) & 1u);
+      for (int q = 0; q < kTilesPerWave; ++q) {
+        const bool hit = lt.on[q] && ((bits >> (w + q * kLW)) & 1u);
         const uint64_t hm = ballot(hit);
         if (hit) {
-          const uint32_t dst = run[q] + (uint32_t)__popcll(hm & lt);
-          ws.tkey[dst] = tile[q];
+          const uint32_t dst = lt.run[q] + (uint32_t)__popcll(hm & lmask);
+          ws.tkey[dst] = lt.tile[q];
           ws.tval[dst] = s;
         }
-        run[q] += (uint32_t)__popcll(hm);
+        lt.run[q] += (uint32_t)__popcll(hm);
       }
     }
+  }
+}
+
+constexpr int kSliceBlocks = 256;  // blocks that write the lists of long bins
+
+// The tile lists of one bin per block; those of long bins by the blocks from
+// `slice0` on, a slice at a time, whose place in its tiles' lists is what the
+// bin's earlier slices have counted; blocks from `order0` on: the compositing
+// order (OCTGS_RASTER_TILE_ORDER).
+template <bool TRAIN>
+__global__ __launch_bounds__(kLT) void k_tile_lists(RasterWs ws, uint32_t slice0, uint32_t order0) {
+  __shared__ union {
+    ListSmem<TRAIN> ls;
+    OrderSmem os;
+  } sm;
+  __shared__ uint32_t before[32];
+  if (blockIdx.x >= order0) {
+    order_tiles(ws, blockIdx.x - order0, sm.os);
+    return;
+  }
+  const int t = threadIdx.x, w = t / kWave;
+  const BinGrid &bg = ws.bins;
+  const uint32_t nblk = TRAIN ? slot_blocks(ws.hdr->n_slots) : 1u;
+  if (blockIdx.x < slice0) {
+    const uint32_t nbins = (uint32_t)(bg.nx * bg.ny), bin = xcd_item(blockIdx.x, nbins);
+    if (bin >= nbins) return;
+    const uint2 rg = ws.bin_range[bin];
+    if (rg.y == 0 || rg.y > (uint32_t)kBinCap) return;
+    const uint32_t bx = bin % (uint32_t)bg.nx, by = bin / (uint32_t)bg.nx;
+    ListTiles lt = list_tiles(ws, bx, by, w);
+    append<TRAIN>(ws, sm.ls, lt, ws.bin_slot[0] + rg.x, ws.bin_mask[0] + rg.x, rg.y, bx, by, nblk);
+    return;
+  }
+  const uint32_t ns = ws.hdr->n_slices;
+  if (ns == 0u || ws.hdr->sync_error) return;
+  for (uint32_t u = blockIdx.x - slice0; u < ns; u += order0 - slice0) {
+    const uint32_t *row = ws.slices + kSliceRow * (size_t)u;
+    const uint32_t bin = row[0], bx = bin % (uint32_t)bg.nx, by = bin / (uint32_t)bg.nx;
+    const uint32_t at = ws.bin_range[bin].x + row[2];
+    __syncthreads();  // the last slice's readers are done
+    if (t < 32) before[t] = 0u;
+    __syncthreads();
+    // 16 slices at a time, a tile's count per thread
+    uint32_t sum = 0;
+    for (uint32_t i = (uint32_t)t / 32u; i < row[1]; i += kLT / 32)
+      sum += row[(int64_t)(t % 32 + 4) - (int64_t)kSliceRow * (i + 1)];
+    if (sum) atomicAdd(&before[t % 32], sum);
+    __syncthreads();
+    ListTiles lt = list_tiles(ws, bx, by, w);
+#pragma unroll
+    for (int q = 0; q < kTilesPerWave; ++q) lt.run[q] += before[w + q * kLW];
+    append<TRAIN>(ws, sm.ls, lt, ws.bin_slot[1] + at, ws.bin_mask[1] + at, row[3], bx, by, nblk);
   }
 }
 
@@ -836,22 +1068,26 @@ __global__ __launch_bounds__(kLT) void k_tile_lists(RasterWs ws, uint32_t order0
 hipError_t launch_bin_sort(const RasterWs &ws, int band_row0, int rows, hipStream_t s) {
   const uint32_t nband = (uint32_t)(rows * ws.bins.nx);
   hipLaunchKernelGGL(k_bin_sort, dim3(xcd_blocks(nband)), dim3(kNT), 0, s, ws, band_row0, nband);
+  if (rows < ws.bins.ny)
+    hipLaunchKernelGGL(k_long_copy, dim3(kLongBlocks), dim3(kNT), 0, s, ws, band_row0, rows);
   return hipGetLastError();
 }
 
 hipError_t launch_tile_scan(const RasterWs &ws, bool train, hipStream_t s) {
-  hipLaunchKernelGGL(k_tile_scan, dim3((unsigned)(ws.scan_blocks + 1 + kMergeBlocks)),
-                     dim3(kScanThreads), 0, s, ws, train ? 1 : 0);
+  const int copied = ws.bins.band_rows < ws.bins.ny ? 1 : 0;
+  hipLaunchKernelGGL(k_tile_scan, dim3((unsigned)(ws.scan_blocks + 1 + kLongBlocks)),
+                     dim3(kScanThreads), 0, s, ws, train ? 1 : 0, copied);
   return hipGetLastError();
 }
 
 hipError_t launch_tile_lists(const RasterWs &ws, bool train, bool ordered, hipStream_t s) {
-  const uint32_t order0 = xcd_blocks((uint32_t)(ws.bins.nx * ws.bins.ny));
+  const uint32_t slice0 = xcd_blocks((uint32_t)(ws.bins.nx * ws.bins.ny));
+  const uint32_t order0 = slice0 + kSliceBlocks;
   const dim3 grid(order0 + (ordered ? kXcds : 0u));
   if (train)
-    hipLaunchKernelGGL(k_tile_lists<true>, grid, dim3(kLT), 0, s, ws, order0);
+    hipLaunchKernelGGL(k_tile_lists<true>, grid, dim3(kLT), 0, s, ws, slice0, order0);
   else
-    hipLaunchKernelGGL(k_tile_lists<false>, grid, dim3(kLT), 0, s, ws, order0);
+    hipLaunchKernelGGL(k_tile_lists<false>, grid, dim3(kLT), 0, s, ws, slice0, order0);
   return hipGetLastError();
 }
 

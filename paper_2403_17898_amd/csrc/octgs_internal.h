@@ -205,7 +205,10 @@ struct RasterHeader {
   uint32_t scan_ticket;   // tile scan: block numbers in the order blocks start
   uint32_t bin_cursor;    // bin-list entries handed out
   uint32_t n_over;        // bins whose list is longer than one block sorts (kBinCap)
-  uint32_t reserved[20];
+  uint32_t n_slices;      // and the slices of their depths
+  uint32_t copy_next, copy_done;    // their entries' copy and the slices: units handed out,
+  uint32_t slice_next, slice_done;  // and units done
+  uint32_t reserved[15];
 };
 
 // Screen bins: rectangles of 2^sx x 2^sy tiles (at most 32, one mask bit per
@@ -230,7 +233,13 @@ constexpr int kMaxTileCoord = 65535;              // tiles past this column or r
 constexpr int kBinThreads = 512;
 constexpr int kBinItems = 8;
 constexpr int kBinCap = kBinThreads * kBinItems;  // longest list that one block sorts at once
-constexpr int kScanThreads = 1024, kScanTiles = 8;  // tile scan: threads, tiles per thread
+constexpr int kScanThreads = 512, kScanTiles = 16;  // tile scan: threads, tiles per thread
+constexpr uint32_t kLongSeg = 8;                  // fewest slot blocks of a unit that copies a long bin
+constexpr uint32_t kSliceRow = 36;                // words per slice: bin, index, start, entries, tiles
+// Slices of a bin of m > kBinCap entries: 1,536 each on average, so that few are
+// more than the 2,048 that four entries per thread sort.
+constexpr uint32_t kSliceEntries = 1536;
+__host__ __device__ inline uint32_t long_slices(uint32_t m) { return (m + kSliceEntries - 1) / kSliceEntries; }
 constexpr int kPairRow = 10;                      // words per pair of gpair: 9 gradients, slot
 
 struct RasterWs {
@@ -253,9 +262,11 @@ struct RasterWs {
   uint4 *large;           // [nblk_g][kSlots] survivors over more bins than that: rectangle (2
                           // words), depth key, slot; every bin looks through these
   uint2 *bin_range;       // [bins] start and length of the bin's list
-  uint32_t *bin_slot[2];  // [pcap] bin lists in depth order: slots ([1]: merged long lists)
+  uint32_t *bin_slot[2];  // [pcap] bin lists in depth order: slots ([0]: long lists before they
+                          // are sorted, [1]: after)
   uint32_t *bin_mask[2];  // [pcap] and the bin's tiles that each is listed in
-  uint32_t *over_bin;     // [pcap / kBinCap + 1] bins with longer lists
+  uint32_t *over_bin;     // [pcap / kBinCap + 1][2] bins with longer lists, entries copied
+  uint32_t *slices;       // [long_slices of all of them][kSliceRow]
   uint32_t *tile_count;   // [tiles], padded to whole scan blocks
   uint32_t *lb_scan;      // [scan blocks] look-back status of the tile scan
   uint32_t *tkey;         // [pcap] tile of each listed pair, in list order (bin keys of long
@@ -443,8 +454,8 @@ RasterWs raster_layout(void *base, int64_t gcap, int64_t pcap, int32_t W, int32_
 // arrays); enqueues one kernel on s.
 hipError_t launch_round_bf16(const float *src, uint16_t *dst, int64_t count, hipStream_t s);
 // The bins of each band, in depth order, into the tile lists (after the
-// projection has grouped the survivors): one call per band of bin rows, then
-// finish_bins once.
+// projection has grouped the survivors): the bin sort once per band of bin rows,
+// then the scan and the lists once.
 hipError_t launch_bin_sort(const RasterWs &ws, int band_row0, int rows, hipStream_t s);
 hipError_t launch_tile_scan(const RasterWs &ws, bool train, hipStream_t s);
 hipError_t launch_tile_lists(const RasterWs &ws, bool train, bool ordered, hipStream_t s);

@@ -977,7 +977,10 @@ RasterWs raster_layout(void *base, int64_t gcap, int64_t pcap, int32_t W, int32_
   ws.bin_range = (uint2 *)take((size_t)nbins * 8);
   for (int i = 0; i < 2; ++i) ws.bin_slot[i] = (uint32_t *)take((size_t)pc * 4);
   for (int i = 0; i < 2; ++i) ws.bin_mask[i] = (uint32_t *)take((size_t)pc * 4);
-  ws.over_bin = (uint32_t *)take((size_t)(pc / kBinCap + 1) * 4);
+  ws.over_bin = (uint32_t *)take((size_t)(pc / kBinCap + 1) * 8);
+  // a long bin has more than kBinCap entries, so at most one slice more than
+  // its share of pc / kSliceEntries
+  ws.slices = (uint32_t *)take((size_t)(pc / kSliceEntries + pc / kBinCap + 1) * kSliceRow * 4);
   ws.tile_count = (uint32_t *)take((size_t)ws.scan_blocks * kScanTiles * kScanThreads * 4);
   ws.lb_scan = (uint32_t *)take((size_t)ws.scan_blocks * 4);
   ws.tkey = (uint32_t *)take((size_t)pc * 4);

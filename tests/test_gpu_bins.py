@@ -133,3 +133,129 @@ def test_bands(P, orc):
         _check_lists(vb, pj, bs)
         del vb
         torch.cuda.empty_cache()
+
+
+def _crowd(n, W, H, span, big, seed, offset=(0.0, 0.0), scale=(0.005, 0.02), opacity=(0.02, 0.3)):
+    """n small Gaussians whose centres lie within `span` pixels, `big` of them
+    grown to tens of tiles."""
+    cam = S.look_at((0.0, -8.0, 0.0), (0.0, 0.0, 0.0), W, H, 60.0)
+    g = np.random.default_rng(seed)
+    gf = S.random_gaussians(n, cam, seed, depth=(5.0, 40.0), scale=scale, margin=0.0, opacity=opacity)
+    px = (gf[1] + 8.0) / (W / 2 / np.tan(np.radians(30.0)))  # the camera looks along +y
+    for a, o in ((0, offset[0]), (2, offset[1])):
+        gf[a] = (g.uniform(o - span / 2, o + span / 2, n) * px).astype(np.float32)
+    k = g.choice(n, big, replace=False)
+    gf[3:6, k] = g.uniform(0.5, 3.0, (3, big)).astype(np.float32)
+    return cam, gf
+
+
+def _long_bins(ref, W, H, sx, sy):
+    """Entries of each bin of 2^sx x 2^sy tiles, from the oracle's lists."""
+    tx = (W + 15) // 16
+    tile, slot = ref["bs"]["tile_of"].astype(np.int64), ref["bs"]["gid_of"].astype(np.int64)
+    b = ((tile // tx) >> sy) * 4096 + ((tile % tx) >> sx)
+    return {k: (np.unique(slot[b == k]), tile[b == k], slot[b == k]) for k in np.unique(b)}
+
+
+@pytest.mark.parametrize("W,H,n,span,big,sx,sy,depths", [
+    (640, 481, 9000, 24, 60, 1, 1, 0),      # bins of 2 x 2 tiles
+    (1000, 701, 14000, 50, 40, 2, 2, 0),    # 4 x 4
+    (1601, 1067, 30000, 90, 30, 3, 2, 0),   # 8 x 4: some ten slices
+    (1601, 1067, 14000, 90, 30, 3, 2, 5),   # ties by slot across slices
+])
+def test_long_bins_of_several_tiles(P, orc, W, H, n, span, big, sx, sy, depths):
+    """Bins of several tiles with more entries than one block sorts, listed in
+    different tiles each, some of them over more than 64 tiles (whose pair
+    numbers without a pair are cleared)."""
+    cam, gf = _crowd(n, W, H, span, big, n)
+    if depths:
+        z = gf[1] + 8.0
+        zn = np.float32(0.5) * np.round(2.0 * np.linspace(6.0, 30.0, depths))[
+            np.random.default_rng(n).integers(0, depths, n)].astype(np.float32)
+        gf[0] *= zn / z
+        gf[2] *= zn / z
+        gf[1] = zn - 8.0
+    ref = _check(P, orc, cam, gf, f"long bins of {1 << sx} x {1 << sy} tiles, depths {depths}")
+    bins = _long_bins(ref, W, H, sx, sy)
+    long = [b for b in bins.values() if len(b[0]) > 4096]
+    assert long
+    for _, tile, slot in long:  # the tiles' lists differ
+        assert len(np.unique(tile)) > 1 and len(np.unique(slot[tile == tile[0]])) < len(np.unique(slot))
+    r = ref["pj"]["rect"][ref["pj"]["vis"] > 0].astype(np.int64)
+    assert ((r[:, 2] - r[:, 0]) * (r[:, 3] - r[:, 1]) > 64).any()
+
+
+def test_long_bins_in_bands(P, orc):
+    """Bins of more than 4,096 entries in both bands of 65,536 x 1,040 pixels
+    (bin rows 0 to 15, and 16): their entries are copied before the next band
+    takes the groups."""
+    cam, a = _crowd(7000, 65536, 1040, 60, 0, 3, offset=(-9000.0, 470.0), scale=(0.0001, 0.0004))
+    _, b = _crowd(7000, 65536, 1040, 10, 0, 4, offset=(8000.0, -511.0), scale=(0.0001, 0.0004))
+    gf = np.ascontiguousarray(np.concatenate([a, b], axis=1))
+    say("bins, long ones in bands")
+    pj = orc.project(gf, cam, orc.params_array())
+    bs = orc.bin_sort(pj, cam)
+    bins = _long_bins({"bs": bs}, cam.width, cam.height, 3, 2)
+    rows = {k // 4096 for k, v in bins.items() if len(v[0]) > 4096}
+    assert 0 in rows and 16 in rows
+    for train in (False, True):
+        vb, _ = _raster(P, cam, gf, bs["n_rect_pairs"], train)
+        _check_lists(vb, pj, bs)
+        del vb
+        torch.cuda.empty_cache()
+
+
+def test_long_bins_in_flight(P):
+    """Views with long bins on eight streams at once, several times over: the
+    lists of each are those of the view alone."""
+    views = []
+    for i in range(8):
+        cam, gf = _crowd(60000, 960, 540, 40 + 10 * i, 20, 50 + i)
+        vb = P.ViewBuffers(gf.shape[1], 1, 960, 540, 4 << 20, gauss_capacity=gf.shape[1])
+        vb.gauss.copy_(torch.as_tensor(gf).cuda())
+        vb.gauss_count.fill_(gf.shape[1])
+        views.append((vb, P.make_camera(cam)))
+    prm = P.raster_params()
+    alone = []
+    for vb, cam in views:
+        vb.rasterize(cam, prm)
+        torch.cuda.synchronize()
+        assert vb.stats()["sync_error"] == 0 and vb.stats()["pair_overflow"] == 0
+        alone.append([x.copy() for x in vb.sorted_lists()] + [vb.rgb.clone()])
+    say("bins, long ones in flight")
+    streams = [torch.cuda.Stream() for _ in views]
+    for _ in range(5):
+        for (vb, cam), s in zip(views, streams):
+            vb.rasterize(cam, prm, stream=s)
+    torch.cuda.synchronize()
+    for (vb, _), (tile, slot, ranges, rgb) in zip(views, alone):
+        assert vb.stats()["sync_error"] == 0
+        t, s, r = vb.sorted_lists()
+        assert np.array_equal(t, tile) and np.array_equal(s, slot) and np.array_equal(r, ranges)
+        assert torch.equal(vb.rgb, rgb)
+
+
+def test_long_bins_time(P):
+    """300k Gaussians within 64 x 64 pixels, every pixel done after one entry (so
+    that the binning is what counts), take no more than four times as long as
+    spread over 1000 x 1000: as long with two global sorts, 43 times as long where
+    one block sorted all runs of a bin."""
+    us = []
+    for span in (64, 1000):
+        cam, gf = _crowd(300000, 1920, 1080, span, 0, 9)
+        vb = P.ViewBuffers(gf.shape[1], 1, 1920, 1080, 4 << 20, gauss_capacity=gf.shape[1])
+        vb.gauss.copy_(torch.as_tensor(gf).cuda())
+        vb.gauss_count.fill_(gf.shape[1])
+        c, prm = P.make_camera(cam), P.raster_params(t_min=2.0)
+        best = 1e9
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            vb.rasterize(c, prm)
+            b.record()
+            b.synchronize()
+            best = min(best, 1e3 * a.elapsed_time(b))
+        assert vb.stats()["pair_overflow"] == 0
+        us.append(best)
+    say(f"bins, 300k Gaussians in 64 x 64 px {us[0]:.0f} us, in 1000 x 1000 {us[1]:.0f}")
+    assert us[0] <= 4.0 * us[1]
