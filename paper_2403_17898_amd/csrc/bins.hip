@@ -148,11 +148,11 @@ __device__ __forceinline__ void collect(const RasterWs &ws, BinSmem &sm, int loc
       uint4 e = make_uint4(0u, 0u, 0u, 0u);
       if (small) {
         const uint32_t o = owner_of(sm.pre, i);
-        const uint4 v = ws.group[(size_t)(r0 + o) * kGroupCap + sm.first[o] + (i - sm.pre[o])];
-        put(run + i, v.x, v.y, v.z);
+        const GroupEntry v = *group_entry(ws, r0 + o, sm.first[o] + (i - sm.pre[o]));
+        put(run + i, v.key, v.slot, v.tiles);
       } else if (large) {
         const uint32_t o = owner_of(sm.lpre, i - ts);
-        e = ws.large[(size_t)(r0 + o) * kSlots + (i - ts - sm.lpre[o])];
+        e = *group_large(ws, r0 + o, i - ts - sm.lpre[o]);
         const TileRect q = clip_to_bin(unpack_rect(e.x | ((uint64_t)e.y << 32)), ws.bins, bx, by);
         hit = q.x0 < q.x1 && q.y0 < q.y1;
       }

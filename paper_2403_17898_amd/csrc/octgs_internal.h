@@ -223,9 +223,9 @@ struct BinGrid {
 };
 
 constexpr int kSlots = 512;                       // Gaussian slots per projection block
-constexpr int kGroupCap = 4 * kSlots;             // grouped entries of a block of kSlots slots
 constexpr uint32_t kGroupBins = 16;               // bins that a survivor hands itself to directly
-constexpr uint32_t kGroupBinsFull = 4;            // ... where the block's would not fit kGroupCap
+constexpr uint32_t kGroupBinsFull = 4;            // ... where the block's would not fit its stretch
+constexpr uint32_t kGroupWords = 3u * kGroupBinsFull * kSlots;  // a block's stretch of the groups
 constexpr uint32_t kTilesUnknown = ~0u;
 constexpr uint32_t kKeepBits = 64;                // rectangle tiles that a slot's keep mask holds
 constexpr int kMaxBandBins = 8192;                // bins of one grouping pass
@@ -247,7 +247,7 @@ struct RasterWs {
   uint64_t *vis_mask;     // [gcap / 64]
   uint32_t *blk_vis;      // [nblk_g] survivors of each block of kSlots slots
   uint32_t *blk_cand;     // [nblk_g] their rectangle tiles (saturated at kLbVal)
-  uint32_t *blk_large;    // [nblk_g] survivors listed in large
+  uint32_t *blk_large;    // [nblk_g] large survivors in the block's group
   uint32_t *blk_pairs;    // [nblk_g] training: pair numbers of the block, then their prefix
   float4 *proj;           // [gcap][3]: (mx, my, A, B) (C, log2 opacity, r, g) (b, qa, qb, qc);
                           // A, B, C = conic scaled for exp2: -0.5 log2e ca, -log2e cb, -0.5 log2e cc;
@@ -257,17 +257,17 @@ struct RasterWs {
   uint32_t *pair_base;    // [gcap] training: first pair number of the slot within its block's
                           // (slot_block)
   uint16_t *group_off;    // [nblk_g][group_pitch] start of each bin's entries in the block's group
-  uint4 *group;           // [nblk_g][kGroupCap] grouped by bin: depth key, slot, the bin's tiles
-                          // that it is listed in (kTilesUnknown: to be tested)
-  uint4 *large;           // [nblk_g][kSlots] survivors over more bins than that: rectangle (2
-                          // words), depth key, slot; every bin looks through these
+  uint32_t *group;        // [nblk_g][kGroupWords] from the front, grouped by bin: depth key, slot,
+                          // the bin's tiles that it is listed in (kTilesUnknown: to be tested);
+                          // from the back the large survivors, over more bins than that:
+                          // rectangle (2 words), depth key, slot; every bin looks through these
   uint2 *bin_range;       // [bins] start and length of the bin's list
   uint32_t *bin_slot[2];  // [pcap] bin lists in depth order: slots ([0]: long lists before they
                           // are sorted, [1]: after)
   uint32_t *bin_mask[2];  // [pcap] and the bin's tiles that each is listed in
   uint32_t *over_bin;     // [pcap / kBinCap + 1][2] bins with longer lists, entries copied
   uint32_t *slices;       // [long_slices of all of them][kSliceRow]
-  uint32_t *tile_count;   // [tiles], padded to whole scan blocks
+  uint32_t *tile_count;   // [tiles], padded to whole scan blocks (in tile_order's place)
   uint32_t *lb_scan;      // [scan blocks] look-back status of the tile scan
   uint32_t *tkey;         // [pcap] tile of each listed pair, in list order (bin keys of long
                           // lists before)
@@ -446,6 +446,17 @@ __host__ __device__ inline uint32_t xcd_blocks(uint32_t n) { return (n + kXcds -
 __device__ __forceinline__ uint32_t xcd_item(uint32_t b, uint32_t n) {
   const uint32_t per = (n + kXcds - 1) / kXcds;
   return b % kXcds * per + b / kXcds;
+}
+
+// Entry i of a block's group from the front, large survivor i from the back.
+struct GroupEntry {
+  uint32_t key, slot, tiles;
+};
+__device__ __forceinline__ GroupEntry *group_entry(const RasterWs &ws, uint32_t block, uint32_t i) {
+  return reinterpret_cast<GroupEntry *>(ws.group + (size_t)block * kGroupWords) + i;
+}
+__device__ __forceinline__ uint4 *group_large(const RasterWs &ws, uint32_t block, uint32_t i) {
+  return reinterpret_cast<uint4 *>(ws.group + ((size_t)block + 1) * kGroupWords) - 1 - i;
 }
 
 RasterWs raster_layout(void *base, int64_t gcap, int64_t pcap, int32_t W, int32_t H);

@@ -157,10 +157,10 @@ struct ProjArgs {
 //   - each survivor is handed to the bins in which it keeps a tile: counted
 //     per bin in LDS, then written to the block's own stretch of ws.group,
 //     where the bins' entries are contiguous (ws.group_off).  A survivor over
-//     more than kGroupBins bins goes to the block's list of large ones
-//     instead, which every bin looks through.  (A block whose direct entries
-//     would not fit its stretch keeps those of up to kGroupBinsFull bins,
-//     which always fit.)
+//     more than kGroupBins bins goes to the block's large ones instead, at the
+//     stretch's end, which every bin looks through.  (A block whose survivors
+//     would not fit its stretch so keeps the entries of those of up to
+//     kGroupBinsFull bins: 48 bytes a survivor either way at most.)
 // Nothing here depends on another block, so nothing has to be cleared before
 // and no global atomic is made: a bin later collects its entries from the
 // blocks' stretches (a column of ws.group_off).
@@ -295,10 +295,10 @@ __global__ __launch_bounds__(kSlots) void k_project(ProjArgs a) {
   const uint32_t bx0 = r.x0 >> bg.sx, nbx = vis ? ((r.x1 - 1u) >> bg.sx) - bx0 + 1u : 0u;
   const uint32_t by0 = r.y0 >> bg.sy, nby = vis ? ((r.y1 - 1u) >> bg.sy) - by0 + 1u : 0u;
   const uint32_t nb = nbx * nby;
-  uint32_t direct, pn = TRAIN ? (flat ? (uint32_t)__popcll(keep) : tiles) : 0u, pairs;
-  uint32_t want = nb <= kGroupBins ? nb : 0u;
-  block_scan2<kSlots>(want, pn, tmp, tmp2, direct, pairs);
-  const uint32_t most = direct <= (uint32_t)kGroupCap ? kGroupBins : kGroupBinsFull;
+  uint32_t words, pn = TRAIN ? (flat ? (uint32_t)__popcll(keep) : tiles) : 0u, pairs;
+  uint32_t want = nb <= kGroupBins ? 3u * nb : 4u;
+  block_scan2<kSlots>(want, pn, tmp, tmp2, words, pairs);
+  const uint32_t most = words <= kGroupWords ? kGroupBins : kGroupBinsFull;
   const bool small = vis && nb <= most;
   if (TRAIN) {
     if (vis) ws.pair_base[s] = pn;
@@ -345,7 +345,7 @@ __global__ __launch_bounds__(kSlots) void k_project(ProjArgs a) {
   lbase = (uint32_t)__builtin_amdgcn_readfirstlane((int)lbase);
   if (vis && !small) {
     const uint64_t rc = pack_rect(o.x0, o.y0, o.x1, o.y1);
-    ws.large[(size_t)blockIdx.x * kSlots + lbase + (uint32_t)__popcll(lm & lanemask_lt())] =
+    *group_large(ws, blockIdx.x, lbase + (uint32_t)__popcll(lm & lanemask_lt())) =
         make_uint4((uint32_t)rc, (uint32_t)(rc >> 32), __float_as_uint(o.zc), s);
   }
   lds_barrier();
@@ -368,18 +368,18 @@ __global__ __launch_bounds__(kSlots) void k_project(ProjArgs a) {
     if (t == 0) row[nbins] = (uint16_t)tot;
   }
   lds_barrier();
-  uint4 *grp = ws.group + (size_t)blockIdx.x * kGroupCap;
+  GroupEntry *grp = group_entry(ws, blockIdx.x, 0u);
   const uint32_t key = __float_as_uint(o.zc);
 #pragma unroll
   for (int j = 0; j < kInReg; ++j)
-    if (bits[j]) grp[hist[bin[j]] + at[j]] = make_uint4(key, s, bits[j], 0u);
+    if (bits[j]) grp[hist[bin[j]] + at[j]] = GroupEntry{key, s, bits[j]};
   if (meets) {
     uint32_t j = 0;
     for (uint32_t y = by0; y < by0 + nby; ++y)
       for (uint32_t x = bx0; x < bx0 + nbx; ++x, ++j)
         if ((meets >> j) & 1u)
           grp[hist[(y - row0) * (uint32_t)bg.gx + x] + placed[t][j]] =
-              make_uint4(key, s, flat ? bin_tiles(r, keep, bg, x, y) : kTilesUnknown, 0u);
+              GroupEntry{key, s, flat ? bin_tiles(r, keep, bg, x, y) : kTilesUnknown};
   }
   if (t == 0) {
     ws.blk_vis[blockIdx.x] = s_vis;
@@ -981,17 +981,19 @@ RasterWs raster_layout(void *base, int64_t gcap, int64_t pcap, int32_t W, int32_
   // a long bin has more than kBinCap entries, so at most one slice more than
   // its share of pc / kSliceEntries
   ws.slices = (uint32_t *)take((size_t)(pc / kSliceEntries + pc / kBinCap + 1) * kSliceRow * 4);
-  ws.tile_count = (uint32_t *)take((size_t)ws.scan_blocks * kScanTiles * kScanThreads * 4);
   ws.lb_scan = (uint32_t *)take((size_t)ws.scan_blocks * 4);
   ws.tkey = (uint32_t *)take((size_t)pc * 4);
   ws.tval = (uint32_t *)take((size_t)pc * 4);
   ws.ranges = (uint32_t *)take((size_t)ntiles * 8);
-  ws.tile_order = (uint32_t *)take((size_t)tile_grid_blocks(ws.tiles_x, ws.tiles_y) * 4);
-  // the groups are read by the bin sort only, before anything writes the
+  // the scan reads the counts before the lists' kernel writes the order
+  ws.tile_order = (uint32_t *)take(
+      4 * std::max<size_t>(tile_grid_blocks(ws.tiles_x, ws.tiles_y),
+                           (size_t)ws.scan_blocks * kScanTiles * kScanThreads));
+  ws.tile_count = ws.tile_order;
+  // the groups are read by the bin sort and the scan, before anything writes the
   // backward's arrays (the tile lists clear rows of gpair): one place for both
   const size_t shared = off;
-  ws.group = (uint4 *)take((size_t)ws.nblk_g * kGroupCap * 16);
-  ws.large = (uint4 *)take((size_t)ws.nblk_g * kSlots * 16);
+  ws.group = (uint32_t *)take((size_t)ws.nblk_g * kGroupWords * 4);
   const size_t fwd_end = off;
   off = shared;
   ws.dproj = (float *)take((size_t)g * 9 * 4);

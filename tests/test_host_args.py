@@ -120,3 +120,16 @@ def test_raster_views_inside_workspace(lib, gcap, pcap, W, H):
     assert lib.octgs_raster_views(ctypes.c_void_p(base + (1 << 20)), gcap, pcap, W, H,
                                   *[ctypes.byref(o) for o in out2]) == L.OCTGS_OK
     assert [o.value - (1 << 20) for o in out2] == [stats, tile, slot, ranges]
+
+
+@pytest.mark.parametrize("gcap,pcap,W,H,most", [
+    (1, 1, 16, 16, 88064), (1, 1, 7680, 4320, 1652480), (100, 100, 64, 64, 103936),
+    (1000, 5000, 1920, 1080, 632832), (130000, 1, 16, 16, 15712256),
+    (27000, 200000, 128, 128, 16464640), (270000, 2000000, 1920, 1080, 165082880),
+    (1000000, 100000, 640, 480, 126973952), (1200000, 4000000, 3840, 2160, 409650688),
+    (10000000, 1000000, 3840, 2160, 1269264128), (10000000, 4000000, 7680, 4320, 1471155712),
+])
+def test_raster_workspace_no_larger(lib, gcap, pcap, W, H, most):
+    """The screen bins' workspace is no larger than that of two global sorts
+    was, where there are many slots to a pair, or many tiles, too."""
+    assert lib.octgs_raster_workspace_bytes(gcap, pcap, W, H) <= most
