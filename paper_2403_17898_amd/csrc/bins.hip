@@ -455,19 +455,34 @@ __global__ __launch_bounds__(kNT, 4) void k_bin_sort(RasterWs ws, int band_row0,
   // (every entry stands for at least one candidate tile of its own, so the lists
   // of all bins fit the capacity)
   if (m > (uint32_t)kBinCap) {
-    // a long bin: its place, its slices
+    // a long bin: its place and its slices; its entries to memory, or, if they
+    // are many, on the list of those that all blocks copy
     const uint32_t ns = long_slices(m);
     if (t == 0) {
-      ws.bin_range[bin] = make_uint2(atomicAdd(&ws.hdr->bin_cursor, m), m);
-      const uint32_t q = atomicAdd(&ws.hdr->n_over, 1u);
-      ws.over_bin[2 * q] = bin;
-      ws.over_bin[2 * q + 1] = 0u;
+      sm.base = atomicAdd(&ws.hdr->bin_cursor, m);
       sm.unit = atomicAdd(&ws.hdr->n_slices, ns);
+      ws.bin_range[bin] = make_uint2(sm.base, m);
+      if (m > kCopyCap) {
+        const uint32_t q = atomicAdd(&ws.hdr->n_over, 1u);
+        ws.over_bin[2 * q] = bin;
+        ws.over_bin[2 * q + 1] = 0u;
+      }
     }
     __syncthreads();
+    if (t == 0) sm.m = 0u;
     for (uint32_t i = t; i < ns; i += kNT) {
       ws.slices[kSliceRow * (size_t)(sm.unit + i)] = bin;
       ws.slices[kSliceRow * (size_t)(sm.unit + i) + 1] = i;
+    }
+    if (m <= kCopyCap) {
+      const uint32_t gb = sm.base;
+      collect<false>(
+          ws, sm, local, bx, by, 0u, nblk, reach, [&](uint32_t n) { return atomicAdd(&sm.m, n); },
+          [&](uint32_t p, uint32_t key, uint32_t slot, uint32_t tiles) {
+            ws.tkey[gb + p] = key;
+            ws.bin_slot[0][gb + p] = slot;
+            ws.bin_mask[0][gb + p] = tiles;
+          });
     }
   } else if (m > 0) {
     const uint32_t mine = finish_tiles(ws, sm, m, bx, by);
@@ -502,18 +517,21 @@ __global__ __launch_bounds__(kNT, 4) void k_bin_sort(RasterWs ws, int band_row0,
 // ---- long bins --------------------------------------------------------------
 // Bins of more than kBinCap entries, done by all blocks of the scan kernel
 // together in two phases of units, each taken by the next free block: first
-// their entries to memory (a unit: one bin's from some slot blocks), then the
-// slices of their depths.  A block that finds no more units waits for those that
-// are taken, which running blocks work on: no wait is on a block that has not
-// started.
-// Bound by latency: about 30 us for the copies and 60 for a block's slice, most
-// of it the pass over the bin's keys where a bin has 100k entries.  300k
-// Gaussians, projection and binning (us), with two global sorts / one block per
-// bin and a merge by rank / now: within 64 x 64 px 176 / 4,700 / 230, 200 x 200
-// 175 / - / 193, 400 x 400 175 / 290 / 167, 600 x 600 174 / - / 164.  256 blocks for
-// them: with 64 and 128, 500 and 360 instead of 270 within 64 x 64 px.  Four
-// waves per SIMD although that spills: at 207 registers the blocks, there in
-// every view, made four 1080p views in flight 2 to 4 percent slower.
+// the entries of those that are too many for the bin's block to copy (a unit:
+// one bin's from some slot blocks), then the slices of their depths.  A block
+// that finds no more units waits for those that are taken, which running blocks
+// work on: no wait is on a block that has not started.
+// Bound by latency: about 20 us for the copies and 35 for a block's slice (sample
+// 7, pass over the bin's keys 5 for 5,000 of them, tile tests 5, sort 9), more of
+// it for the pass where a bin has 100k entries.  300k Gaussians, projection and
+// binning (us), with two global sorts / one block per bin and a merge by rank /
+// now: within 64 x 64 px 176 / 4,700 / 235, 200 x 200 175 / - / 191, 400 x 400
+// 175 / 290 / 161, 600 x 600 174 / - / 131.  Four 1080p views in flight, 64 bins
+// of 4 to 8 thousand entries among 1,020: 961 with the merge, 953 now (1,020
+// where all long bins were copied in the first phase).  256 blocks for them: with
+// 64 and 128, 500 and 360 instead of 270 within 64 x 64 px.  Four waves per SIMD
+// although that spills: at 207 registers the blocks, there in every view, made
+// four 1080p views in flight 2 to 4 percent slower.
 
 // Waits (thread 0) until *done reaches want; false if the wait hit its bound
 // (then *err is set).  What was written before the counts is visible after it.
@@ -734,9 +752,10 @@ __global__ __launch_bounds__(kScanThreads, 4) void k_tile_scan(RasterWs ws, int 
   uint32_t *tmp = sm.tmp;
   const int t = threadIdx.x, w = t / kWave, l = __lane_id();
   bool ok = true;
-  const uint32_t nover = ws.hdr->n_over;
-  if (nover > 0u) {
-    if (!copied) {
+  const uint32_t ns = ws.hdr->n_slices;
+  if (ns > 0u) {
+    const uint32_t nover = copied ? 0u : ws.hdr->n_over;
+    if (nover > 0u) {
       const uint32_t nblk = slot_blocks(ws.hdr->n_slots), seg = long_seg(nover, nblk);
       const uint32_t per = (nblk + seg - 1u) / seg;
       take_units(sm, &ws.hdr->copy_next, &ws.hdr->copy_done, nover * per, [&](uint32_t u) {
@@ -745,7 +764,6 @@ __global__ __launch_bounds__(kScanThreads, 4) void k_tile_scan(RasterWs ws, int 
       });
       ok = wait_units(sm, &ws.hdr->copy_done, nover * per, &ws.hdr->sync_error);
     }
-    const uint32_t ns = ws.hdr->n_slices;
     if (ok)
       take_units(sm, &ws.hdr->slice_next, &ws.hdr->slice_done, ns,
                  [&](uint32_t u) { long_slice(ws, sm, u); });

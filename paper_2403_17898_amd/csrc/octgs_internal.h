@@ -234,6 +234,7 @@ constexpr int kBinThreads = 512;
 constexpr int kBinItems = 8;
 constexpr int kBinCap = kBinThreads * kBinItems;  // longest list that one block sorts at once
 constexpr int kScanThreads = 512, kScanTiles = 16;  // tile scan: threads, tiles per thread
+constexpr uint32_t kCopyCap = 16384;              // longest list that its bin's block copies by itself
 constexpr uint32_t kLongSeg = 8;                  // fewest slot blocks of a unit that copies a long bin
 constexpr uint32_t kSliceRow = 36;                // words per slice: bin, index, start, entries, tiles
 // Slices of a bin of m > kBinCap entries: 1,536 each on average, so that few are
