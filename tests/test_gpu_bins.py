@@ -186,18 +186,22 @@ def test_long_bins_of_several_tiles(P, orc, W, H, n, span, big, sx, sy, depths):
 
 
 def test_long_bins_in_bands(P, orc):
-    """Bins of more than 4,096 entries in both bands of 65,536 x 1,040 pixels
-    (bin rows 0 to 15, and 16): their entries are copied before the next band
-    takes the groups."""
-    cam, a = _crowd(7000, 65536, 1040, 60, 0, 3, offset=(-9000.0, 470.0), scale=(0.0001, 0.0004))
-    _, b = _crowd(7000, 65536, 1040, 10, 0, 4, offset=(8000.0, -511.0), scale=(0.0001, 0.0004))
-    gf = np.ascontiguousarray(np.concatenate([a, b], axis=1))
+    """Bins of more than 4,096 entries (copied by their block) and of more than
+    16,384 (by all) in both bands of 65,536 x 1,040 pixels (bin rows 0 to 15, and
+    16): their entries are copied before the next band takes the groups."""
+    parts = [_crowd(n, 65536, 1040, span, 0, i, offset=o, scale=(0.0001, 0.0004))
+             for i, (n, span, o) in enumerate([
+                 (7000, 60, (-9000.0, 470.0)), (18000, 10, (5000.0, 470.0)),
+                 (7000, 10, (8000.0, -511.0)), (18000, 10, (-7000.0, -511.0))])]
+    cam = parts[0][0]
+    gf = np.ascontiguousarray(np.concatenate([p[1] for p in parts], axis=1))
     say("bins, long ones in bands")
     pj = orc.project(gf, cam, orc.params_array())
     bs = orc.bin_sort(pj, cam)
     bins = _long_bins({"bs": bs}, cam.width, cam.height, 3, 2)
-    rows = {k // 4096 for k, v in bins.items() if len(v[0]) > 4096}
-    assert 0 in rows and 16 in rows
+    for row in (0, 16):
+        longest = [len(v[0]) for k, v in bins.items() if k // 4096 == row and len(v[0]) > 4096]
+        assert min(longest) <= 16384 < max(longest)
     for train in (False, True):
         vb, _ = _raster(P, cam, gf, bs["n_rect_pairs"], train)
         _check_lists(vb, pj, bs)
