@@ -134,7 +134,7 @@ typedef struct {
 
 /* Status bits OR-ed into octgs_gaussians.status. */
 #define OCTGS_STATUS_PAIR_OVERFLOW 1u /* octgs_rasterize_fwd: the pair list overflowed (image incomplete) */
-#define OCTGS_STATUS_SYNC_ERROR 2u    /* octgs_rasterize_fwd: a look-back wait hit its bound (invalid) */
+#define OCTGS_STATUS_SYNC_ERROR 2u    /* octgs_rasterize_fwd: a wait on another block hit its bound (invalid) */
 #define OCTGS_STATUS_TRUNCATED 4u     /* octgs_decode*: more listed anchors than capacity / k (the rest dropped) */
 
 /* Rasterizer constants.  alpha_max clamps each per-pixel alpha; entries with
@@ -154,12 +154,12 @@ typedef struct {
  * the same frame, off for rendering only. */
 #define OCTGS_RASTER_TRAIN 1u
 /* flags: before compositing, order each XCD's tiles by list length, longest
- * first (one small extra kernel), so the last blocks to run are short ones;
- * the backward of the same frame then uses the same order.  It shortens the
- * compositing kernels when the frame runs alone on the GPU (a training step,
- * a single view); with several frames in flight their kernels already fill
- * each other's tails, and the extra kernel costs more than it saves.  The
- * image is the same bit for bit either way. */
+ * first (eight extra blocks beside the tile lists), so the last blocks to run
+ * are short ones; the backward of the same frame then uses the same order.  It
+ * shortens the compositing kernels when the frame runs alone on the GPU (a
+ * training step, a single view); with several frames in flight their kernels
+ * already fill each other's tails, and the order costs more than it saves.
+ * The image is the same bit for bit either way. */
 #define OCTGS_RASTER_TILE_ORDER 2u
 
 #define OCTGS_RASTER_STAGES 5
@@ -171,8 +171,9 @@ typedef struct {
   uint32_t n_pairs;       /* (tile, Gaussian) pairs listed: tiles the 3-sigma ellipse meets
                              (0 on overflow) */
   uint32_t pair_overflow; /* 1 if n_candidates exceeded the pair capacity (image incomplete) */
-  uint32_t sync_error;    /* 1 if a look-back wait (the tile scan's) hit its bound (output
-                             invalid); its blocks are numbered in the order they start, so
+  uint32_t sync_error;    /* 1 if a wait of the tile scan's kernel on another block hit its
+                             bound (output invalid); blocks are numbered in the order they
+                             start and units of work belong to the blocks that took them, so
                              every wait is on a running block and this is not expected */
   uint32_t n_candidates;  /* tiles of the survivors' 3-sigma rectangles, tested against the
                              ellipse; the pair capacity must hold this many (saturates) */

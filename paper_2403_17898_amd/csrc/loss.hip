@@ -529,12 +529,13 @@ extern "C" {
 
 size_t octgs_photometric_workspace_bytes(int64_t n_images, int32_t height, int32_t width) {
   if (n_images < 0 || height < 0 || width < 0) return 0;
-  // Three maps and two partial sums per tile, as the tiled passes use.  The
-  // strip kernel writes 2 * ssim_blocks partial sums only, fewer than the
-  // maps hold (a block has at least 8 x 236 pixels, or is an image's only one
-  // in that direction).
-  return (size_t)(3 * n_images * (int64_t)height * width +
-                  2 * tile_blocks(n_images, height, width)) * sizeof(float) + 256;
+  // Three maps and two partial sums per tile, as the tiled passes use, or two
+  // partial sums per strip (a strip covers the whole of a small image, but the
+  // last ones of a row or column of strips may be of one pixel's width).
+  if (n_images == 0 || height == 0 || width == 0) return 256;
+  return (size_t)std::max(3 * n_images * (int64_t)height * width +
+                              2 * tile_blocks(n_images, height, width),
+                          2 * ssim_blocks(n_images, height, width)) * sizeof(float) + 256;
 }
 
 int octgs_photometric_loss_grad(const float *img, const float *target, int64_t n_images,

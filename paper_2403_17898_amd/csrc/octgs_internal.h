@@ -158,7 +158,7 @@ __device__ __forceinline__ void st_rel(uint32_t *p, uint32_t v) {
 // dense and sparse regions of a view across the XCDs, while the tiles of one
 // group, which share most of their Gaussians, stay in one L2.  On request
 // (OCTGS_RASTER_TILE_ORDER) the rasterizer then orders each XCD's tiles by
-// list length, longest first (k_tile_order), so its last blocks are short.
+// list length, longest first (order_tiles), so its last blocks are short.
 constexpr uint32_t kXcds = 8;
 constexpr uint32_t kTileGroup = 4;
 // Largest number of 16x16 tiles per image (about 4.3 gigapixels): tile ids,
@@ -480,7 +480,7 @@ struct CamParams {
   int W, H;
 };
 
-constexpr uint32_t kSpinLimit = 1u << 22;  // look-back wait bound
+constexpr uint32_t kSpinLimit = 1u << 22;  // bound of a wait on other blocks
 
 // ---------------------------------------------------------------------------
 // chained scan: decoupled look-back over one value per partition

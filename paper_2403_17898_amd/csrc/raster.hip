@@ -9,7 +9,8 @@
 //             (tile_meets_ellipse); survivors grouped by screen bin
 //   bin sort  per bin of up to 8 x 4 tiles, one block: collects the bin's
 //             entries, sorts them by (depth, slot) in LDS, counts its tiles
-//   tile scan [start, end) per tile
+//   tile scan bins of more than 4,096 entries, by all blocks; [start, end) per
+//             tile
 //   tile lists per bin: each tile takes its entries from the bin's ordered
 //             list
 //   composite one wave per 16x16 tile (four pixels of a column per lane),
@@ -23,7 +24,7 @@
 // radix-sorted by depth (4 passes), their pairs emitted in that order and
 // radix-sorted by tile (2 passes): eleven dependent kernels of 5 to 23 us,
 // 138 us together on a 1080p view of 270k slots and 862k pairs; these four
-// take 66 us (25, 25, 6 and 10).
+// take 63 us (25, 21, 7 and 10).
 //
 // Decisions (culls, rectangle, depth key, tile test) use the fixed FP32
 // operation sequences documented at project_decide and tile_meets_ellipse;
@@ -170,7 +171,7 @@ struct ProjArgs {
 // Bound by latency and the tests' vector work: a 1080p view of 270k slots has
 // 528 blocks of about 16 us (loads and projection 4, tests 6, grouping 3, the
 // rest scans and writes), all resident at once: 25 us; 1.2M slots on 3840 x
-// 2160 take 55, in two to three rounds.
+// 2160 take 53, in two to three rounds.
 // Block 0 clears the header and the scan's look-back words for the later
 // kernels.
 template <bool TRAIN>
