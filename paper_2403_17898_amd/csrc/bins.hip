@@ -542,9 +542,9 @@ __global__ __launch_bounds__(kNT, 4) void k_bin_sort(RasterWs ws, int band_row0,
 // 7, pass over the bin's keys 5 for 5,000 of them, tile tests 5, sort 9), more of
 // it for the pass where a bin has 100k entries.  300k Gaussians, projection and
 // binning (us), with two global sorts / one block per bin and a merge by rank /
-// now: within 64 x 64 px 176 / 4,700 / 235, 200 x 200 175 / - / 191, 400 x 400
-// 175 / 290 / 161, 600 x 600 174 / - / 131.  Four 1080p views in flight, 64 bins
-// of 4 to 8 thousand entries among 1,020: 961 with the merge, 953 now (1,020
+// now: within 64 x 64 px 176 / 4,700 / 246, 200 x 200 175 / - / 203, 400 x 400
+// 175 / 290 / 171, 600 x 600 174 / - / 130.  Four 1080p views in flight, 64 bins
+// of 4 to 8 thousand entries among 1,020: 961 with the merge, 945 now (1,020
 // where all long bins were copied in the first phase).  256 blocks for them: with
 // 64 and 128, 500 and 360 instead of 270 within 64 x 64 px.  Four waves per SIMD
 // although that spills: at 207 registers the blocks, there in every view, made
@@ -559,17 +559,22 @@ __device__ __forceinline__ bool wait_units(BinSmem &sm, const uint32_t *done, ui
     while (ld_acq(done) < want && ++spins <= kSpinLimit) __builtin_amdgcn_s_sleep(1);
     sm.flag = spins <= kSpinLimit ? 1u : 0u;
     if (!sm.flag) atomicOr(err, 1u);
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   }
   __syncthreads();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // every wave, for its own loads
   const bool ok = sm.flag != 0u;
   __syncthreads();
   return ok;
 }
 
 // Units [0, total) by work(unit), as many as this block gets, then their number
-// is added to *done.
-template <typename Work>
+// is added to *done.  A barrier does not wait for the waves' stores and atomics,
+// so each wave waits for its own before the barrier that leads to the count.
+// STORES: other blocks read what the units store, so the XCD's L2, where the
+// stores are by then, is written back; atomics are done in memory (all eight
+// waves writing it back took 10 to 30 us more).
+constexpr int kVmcnt0 = 0x0f70;  // s_waitcnt operand: vmcnt(0), the other counters as they are
+template <bool STORES, typename Work>
 __device__ __forceinline__ void take_units(BinSmem &sm, uint32_t *next, uint32_t *done,
                                            uint32_t total, Work work) {
   uint32_t n = 0;
@@ -579,10 +584,17 @@ __device__ __forceinline__ void take_units(BinSmem &sm, uint32_t *next, uint32_t
     const uint32_t u = sm.unit;
     if (u >= total) break;
     work(u);
-    __syncthreads();  // the block's writes are out, the LDS may be reused
+    __syncthreads();  // the LDS may be reused
   }
-  if (threadIdx.x == 0 && n) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  if (n == 0) return;
+  __builtin_amdgcn_s_waitcnt(kVmcnt0);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    if (STORES) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      // the fence's own wait is dropped where nothing but its write-back is counted
+      __builtin_amdgcn_s_waitcnt(kVmcnt0);
+    }
     atomicAdd(done, n);
   }
 }
@@ -775,15 +787,16 @@ __global__ __launch_bounds__(kScanThreads, 4) void k_tile_scan(RasterWs ws, int 
     if (nover > 0u) {
       const uint32_t nblk = slot_blocks(ws.hdr->n_slots), seg = long_seg(nover, nblk);
       const uint32_t per = (nblk + seg - 1u) / seg;
-      take_units(sm, &ws.hdr->copy_next, &ws.hdr->copy_done, nover * per, [&](uint32_t u) {
+      take_units<true>(sm, &ws.hdr->copy_next, &ws.hdr->copy_done, nover * per, [&](uint32_t u) {
         const uint32_t b0 = u % per * seg;
         long_copy(ws, sm, u / per, b0, min(b0 + seg, nblk), 0u);
       });
       ok = wait_units(sm, &ws.hdr->copy_done, nover * per, &ws.hdr->sync_error);
     }
     if (ok)
-      take_units(sm, &ws.hdr->slice_next, &ws.hdr->slice_done, ns,
-                 [&](uint32_t u) { long_slice(ws, sm, u); });
+      // (only their counts, added by atomics, are read in this kernel)
+      take_units<false>(sm, &ws.hdr->slice_next, &ws.hdr->slice_done, ns,
+                        [&](uint32_t u) { long_slice(ws, sm, u); });
     // (blocks that are there for the long bins need not wait)
     if (blockIdx.x < (uint32_t)ws.scan_blocks)
       ok = wait_units(sm, &ws.hdr->slice_done, ns, &ws.hdr->sync_error) && ok;

@@ -383,7 +383,7 @@ __device__ __forceinline__ uint32_t bin_tiles(const TileRect &r, uint64_t keep, 
 }
 
 // Barrier that orders LDS only: global loads and atomics stay in flight across
-// it (__syncthreads waits for them).
+// it.  (So do stores across __syncthreads, which orders them within the block.)
 __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
   __builtin_amdgcn_s_barrier();
